@@ -51,13 +51,17 @@ int make_shape(const ntbc_model_desc* d, Shape* s);
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// log2(2 * blocks) when that is a power of two and every numerator of the grid-corner arithmetic
-// ((2b + 1) res - blocks, and the clamp bound (res - 1) 2 blocks) fits in 31 bits at the finest level,
-// else -1: the corner computation then takes shifts instead of divisions.
-inline int pow2_shift(const Shape& s, int blocks) {
+// How the grid corners of an axis of `blocks` blocks are computed (dev::corner_of).  When every numerator
+// of the corner arithmetic ((2b + 1) res - blocks, and the clamp bound (res - 1) 2 blocks) fits in 31
+// bits at the finest level: log2(2 * blocks) if that is a power of two (shifts), else kCornerRcp for
+// 2 * blocks <= 2^18 (one product with the reciprocal and a correction, shown exact up to there); else
+// kCornerDiv (64-bit divisions, some hundred instructions a level).
+constexpr int kCornerDiv = -1, kCornerRcp = -2;
+inline int corner_kind(const Shape& s, int blocks) {
   const int64_t den = 2 * (int64_t)blocks;
   const int64_t top = (int64_t)s.base_res << (s.n_levels - 1);
-  if ((den & (den - 1)) != 0 || (2 * (int64_t)blocks + 1) * top >= (1ll << 31) || top * den >= (1ll << 31)) return -1;
+  if ((2 * (int64_t)blocks + 1) * top >= (1ll << 31) || top * den >= (1ll << 31)) return kCornerDiv;
+  if ((den & (den - 1)) != 0) return den <= (1ll << 18) ? kCornerRcp : kCornerDiv;
   int sh = 0;
   while ((1ll << sh) < den) ++sh;
   return sh;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "common.h"
 #include "ntbc.h"
 
 namespace ntbc {
@@ -90,11 +91,10 @@ struct GridView {
   const float* scale;    // per level (U8)
   const int32_t* zero;   // per level (U8)
   int n_levels, base_res, n_features, blocks_w, blocks_h;
-  // shift_x = log2(2*blocks_w) when that is a power of two and every numerator fits in 31 bits,
-  // else -1 (general path); likewise shift_y
-  int shift_x, shift_y;
-  // fast8: uint8 grid, 8 features per vertex, both shifts >= 0 and every byte offset below 2^31
-  // (sample8_fast: 32-bit offsets from the grid base)
+  int kind_x, kind_y;    // corner_kind of the two axes
+  float inv_x, inv_y;    // 1 / (2 * blocks)
+  // fast8: uint8 grid, 8 features per vertex and every byte offset below 2^31 (sample8_fast: 32-bit offsets
+  // from the grid base): 1 both axes shifts, 2 neither axis kCornerDiv
   int fast8;
   int64_t level_offset[NTBC_MAX_LEVELS + 1];
 };
@@ -111,13 +111,55 @@ __device__ __forceinline__ Corner corner_pow2(int b, int blocks, int res, int sh
   return c;
 }
 
+// corner() for kCornerRcp, inv = 1 / (2 * blocks): the quotient from one float product is off by at most one
+// (num < 2^31, i0 < 2^15), which the exact remainder corrects; the fraction takes the product q0 = rem *
+// inv and one residual step, q0 + inv * (rem - den q0), which rounds like the division (checked for
+// every remainder of every denominator up to 2^18).
+__device__ __forceinline__ Corner corner_rcp(int b, int blocks, int res, float inv) {
+  const int den = 2 * blocks, num = (2 * b + 1) * res - blocks;
+  int q = (int)((float)num * inv);
+  int rem = num - q * den;
+  if (rem < 0) {
+    --q;
+    rem += den;
+  } else if (rem >= den) {
+    ++q;
+    rem -= den;
+  }
+  const float a = (float)rem, q0 = __fmul_rn(a, inv);
+  const float f = fmaf(fmaf(-(float)den, q0, a), inv, q0);
+  const bool lo = num <= 0, hi = num >= (res - 1) * den;
+  Corner c;
+  c.i0 = lo ? 0 : (hi ? res - 2 : q);
+  c.f = lo ? 0.0f : (hi ? 1.0f : f);
+  return c;
+}
+
+// The corner of an axis by its corner_kind (uniform).
+__device__ __forceinline__ Corner corner_of(int b, int blocks, int res, int kind, float inv) {
+  if (kind >= 0) return corner_pow2(b, blocks, res, kind);
+  return kind == kCornerRcp ? corner_rcp(b, blocks, res, inv) : corner(b, blocks, res);
+}
+
+// Block coordinates of position id, whose range ends at `last` (uniform): 32-bit division where it fits.
+__device__ __forceinline__ void block_of(int64_t id, int64_t last, int blocks_w, int* bx, int* by) {
+  if (last <= 0x7fffffff) {
+    const uint32_t q = (uint32_t)id / (uint32_t)blocks_w;
+    *by = (int)q;
+    *bx = (int)((uint32_t)id - q * (uint32_t)blocks_w);
+  } else {
+    *bx = (int)(id % blocks_w);
+    *by = (int)(id / blocks_w);
+  }
+}
+
 // Bilinear feature values of features [f0, f0+FE) of `level` at block (bx, by):
 // sum over the four corners of w_c * value_c, value = scale*(q - zero) for U8 grids.
 template <int FE>
 __device__ __forceinline__ void sample(const GridView& g, int level, int f0, int bx, int by, float out[FE]) {
   const int res = g.base_res << level;
-  const Corner cx = g.shift_x >= 0 ? corner_pow2(bx, g.blocks_w, res, g.shift_x) : corner(bx, g.blocks_w, res);
-  const Corner cy = g.shift_y >= 0 ? corner_pow2(by, g.blocks_h, res, g.shift_y) : corner(by, g.blocks_h, res);
+  const Corner cx = corner_of(bx, g.blocks_w, res, g.kind_x, g.inv_x);
+  const Corner cy = corner_of(by, g.blocks_h, res, g.kind_y, g.inv_y);
   const int64_t v00 = g.level_offset[level] + (int64_t)cy.i0 * res + cx.i0;
   const int64_t F = g.n_features;
   const float w00 = (1.0f - cx.f) * (1.0f - cy.f), w10 = cx.f * (1.0f - cy.f);
@@ -144,10 +186,12 @@ __device__ __forceinline__ void sample(const GridView& g, int level, int f0, int
 
 // sample<8> for a fast8 grid: the same corners and blend, with 32-bit byte offsets from the grid base
 // (a scalar base plus a per-lane offset in the loads instead of 64-bit per-lane addresses).
+template <bool POW2>
 __device__ __forceinline__ void sample8_fast(const GridView& g, int level, int bx, int by, float out[8]) {
   const int res = g.base_res << level;
-  const Corner cx = corner_pow2(bx, g.blocks_w, res, g.shift_x);
-  const Corner cy = corner_pow2(by, g.blocks_h, res, g.shift_y);
+  // (the reciprocal is as exact for a power of two)
+  const Corner cx = POW2 ? corner_pow2(bx, g.blocks_w, res, g.kind_x) : corner_rcp(bx, g.blocks_w, res, g.inv_x);
+  const Corner cy = POW2 ? corner_pow2(by, g.blocks_h, res, g.kind_y) : corner_rcp(by, g.blocks_h, res, g.inv_y);
   const uint32_t o00 = ((uint32_t)g.level_offset[level] + (uint32_t)(cy.i0 * res + cx.i0)) * 8u;
   const uint32_t row = 8u * (uint32_t)res;
   const float w00 = (1.0f - cx.f) * (1.0f - cy.f), w10 = cx.f * (1.0f - cy.f);
@@ -181,8 +225,12 @@ __device__ __forceinline__ void features(const GridView& g, int c0, int bx, int 
 #pragma unroll
     for (int m = 0; m < 8; ++m) v[m] = 0.0f;
     if (c0 >= in_dim) return;
-    if (g.fast8) {
-      sample8_fast(g, c0 / 8, bx, by, v);
+    if (g.fast8 == 1) {
+      sample8_fast<true>(g, c0 / 8, bx, by, v);
+      return;
+    }
+    if (g.fast8 == 2) {
+      sample8_fast<false>(g, c0 / 8, bx, by, v);
       return;
     }
     switch (g.n_features) {
@@ -232,7 +280,12 @@ struct Bc1Pal {
 };
 
 // tab (optional): tab[c] = c / 255 as float32 (correctly rounded), replacing the division.
-__device__ __forceinline__ float unit8(int c, const float* tab) { return tab ? tab[c] : (float)c / 255.0f; }
+// Without it, the product with 1 / 255 and one residual step, which rounds as the division for every c.
+__device__ __forceinline__ float unit8(int c, const float* tab) {
+  if (tab) return tab[c];
+  const float a = (float)c, q = __fmul_rn(a, 1.0f / 255.0f);
+  return fmaf(fmaf(-255.0f, q, a), 1.0f / 255.0f, q);
+}
 
 // Palette of two quantised RGB565 endpoints: the larger word becomes c0 (four-colour mode, Sec. 3),
 // entries in weight order a, (2a+b)/3, (a+2b)/3, b of the expanded 8-bit channels.
@@ -292,6 +345,13 @@ struct Bc4Pal {
   float pal[8];  // weight order
 };
 
+// Stored 3-bit codes in weight order, 3 bits each: eight 0,2,3,4,5,6,7,1; six 6,0,2,3,4,5,1,7.
+__device__ __forceinline__ uint32_t bc4_map(bool eight) {
+  constexpr uint32_t kMap8 = 0u | 2u << 3 | 3u << 6 | 4u << 9 | 5u << 12 | 6u << 15 | 7u << 18 | 1u << 21;
+  constexpr uint32_t kMap6 = 6u | 0u << 3 | 2u << 6 | 3u << 9 | 4u << 12 | 5u << 15 | 1u << 18 | 7u << 21;
+  return eight ? kMap8 : kMap6;
+}
+
 // Palette of two quantised 8-bit endpoints: eight-value mode when e0 > e1, else six values plus 0 and
 // 255.  Stored codes in weight order: eight 0,2,3,4,5,6,7,1; six 6,0,2,3,4,5,1,7.
 __device__ __forceinline__ Bc4Pal bc4_palette(int e0, int e1, const float* tab = nullptr) {
@@ -313,9 +373,7 @@ __device__ __forceinline__ Bc4Pal bc4_palette(int e0, int e1, const float* tab =
 #pragma unroll
     for (int j = 1; j <= 4; ++j) v[1 + j] = ((5 - j) * e0 + j * e1 + 2) / 5;
   }
-  constexpr uint32_t kMap8 = 0u | 2u << 3 | 3u << 6 | 4u << 9 | 5u << 12 | 6u << 15 | 7u << 18 | 1u << 21;
-  constexpr uint32_t kMap6 = 6u | 0u << 3 | 2u << 6 | 3u << 9 | 4u << 12 | 5u << 15 | 1u << 18 | 7u << 21;
-  p.map = p.eight ? kMap8 : kMap6;
+  p.map = bc4_map(p.eight);
 #pragma unroll
   for (int n = 0; n < 8; ++n) p.pal[n] = unit8(v[n], tab);
   return p;
@@ -329,19 +387,17 @@ __device__ __forceinline__ Bc4Pal bc4_from_heads(const float* ep, const float* t
 // monotone in weight order in both modes (eight: e0 > interpolants > e1; six: 0 <= e0 <= interpolants
 // <= e1 <= 1) and rounding is monotone, so the float32 squared distances are unimodal in the weight
 // index: the first minimum is the last index whose distance is strictly below its predecessor's.
+// Squares of differing |d| differ too (their gap is at least two units in the last place before
+// rounding, and no two distinct entries are both near enough to x to underflow), so the |d| themselves
+// are compared: a subtraction, a comparison and a select per entry.
 __device__ __forceinline__ uint32_t bc4_code(const Bc4Pal& p, float x) {
-  float prev;
-  {
-    const float d = __fsub_rn(x, p.pal[0]);
-    prev = __fmul_rn(d, d);
-  }
+  float prev = __fsub_rn(x, p.pal[0]);
   uint32_t sh = 0;  // 3 * weight index of the first minimum so far
 #pragma unroll
   for (int n = 1; n < 8; ++n) {
     const float d = __fsub_rn(x, p.pal[n]);
-    const float e = __fmul_rn(d, d);
-    sh = e < prev ? 3u * n : sh;
-    prev = e;
+    sh = fabsf(d) < fabsf(prev) ? 3u * n : sh;
+    prev = d;
   }
   return (p.map >> sh) & 7u;
 }

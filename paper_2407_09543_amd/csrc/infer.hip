@@ -175,8 +175,8 @@ __global__ void k_pack_lp(PackArgs a, typename LpOp<L>::type* __restrict__ pack,
   const int64_t total = (int64_t)a.otiles[layer] * a.ksteps[layer] * 64;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int l = (int)(e % 64);
-    const int s = (int)((e / 64) % a.ksteps[layer]);
-    const int t = (int)(e / (64 * (int64_t)a.ksteps[layer]));
+    const int t = (int)((uint32_t)(e / 64) / (uint32_t)a.ksteps[layer]);
+    const int s = (int)(e / 64) - t * a.ksteps[layer];
     const int prow = 32 * t + (l % 32);
     const int row = a.head_perm && layer == a.n_layers - 1 ? (prow < kHeadRows ? a.head_src[prow] : -1) : prow;
     float v[8];
@@ -212,8 +212,8 @@ __global__ void k_pack_f32(PackArgs a, float* __restrict__ pack, float* __restri
   const int64_t total = (int64_t)a.otiles[layer] * a.ksteps[layer] * 64;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int l = (int)(e % 64);
-    const int s = (int)((e / 64) % a.ksteps[layer]);
-    const int t = (int)(e / (64 * (int64_t)a.ksteps[layer]));
+    const int t = (int)((uint32_t)(e / 64) / (uint32_t)a.ksteps[layer]);
+    const int s = (int)(e / 64) - t * a.ksteps[layer];
     const int row = 16 * t + (l % 16);
     const int col = f32_col(layer, s, l / 16);
     pack[a.pack_off[layer] + e] = (row < a.out_dim[layer] && col < a.in_dim[layer])
@@ -330,7 +330,8 @@ __global__ void __launch_bounds__(64 * kWaves) k_infer_lp(InferArgs a) {
   const int64_t pos0 = a.first + (tile * kWaves + wave) * 32;
   const int64_t last = a.first + a.n - 1;
   const int64_t id = pos0 + j <= last ? pos0 + j : last;
-  const int bx = (int)(id % a.grid.blocks_w), by = (int)(id / a.grid.blocks_w);
+  int bx, by;
+  dev::block_of(id, last, a.grid.blocks_w, &bx, &by);
 
   u32x4 bin[S];
 #pragma unroll
@@ -784,7 +785,8 @@ __device__ __forceinline__ void infer_tile(ArgsT a, ChunksT ct, int64_t tile) {
   const int64_t pos0 = a.first + (tile * W + wave) * 32;
   const int64_t last = a.first + a.n - 1;
   const int64_t id = pos0 + j <= last ? pos0 + j : last;
-  const int bx = (int)(id % a.grid.blocks_w), by = (int)(id / a.grid.blocks_w);
+  int bx, by;
+  dev::block_of(id, last, a.grid.blocks_w, &bx, &by);
   const u32x4* wp = reinterpret_cast<const u32x4*>(a.wpack);
   const Fp8Factors f8 = fp8_factors<L>(a);
 
@@ -1017,7 +1019,8 @@ __global__ void __launch_bounds__(64 * kWaves) k_infer_f32(InferArgs a) {
   const int64_t last = a.first + a.n - 1;
   int64_t id = pos0 + j <= last ? pos0 + j : last;
   if constexpr (CALIB) id *= a.stride;  // first = 0: sample index -> block id
-  const int bx = (int)(id % a.grid.blocks_w), by = (int)(id / a.grid.blocks_w);
+  int bx, by;
+  dev::block_of(id, CALIB ? last * a.stride : last, a.grid.blocks_w, &bx, &by);
 
   float bin[S];
   float m_in = 0.0f;
@@ -1196,7 +1199,8 @@ k_infer_f32_lds(InferArgs a, ChunkTable ct) {
   const int64_t pos0 = a.first + (xcd_tile(blockIdx.x, gridDim.x) * kF32Waves + wave) * 16;
   const int64_t last = a.first + a.n - 1;
   const int64_t id = pos0 + j <= last ? pos0 + j : last;
-  const int bx = (int)(id % a.grid.blocks_w), by = (int)(id / a.grid.blocks_w);
+  int bx, by;
+  dev::block_of(id, last, a.grid.blocks_w, &bx, &by);
   const u32x4* wp = reinterpret_cast<const u32x4*>(a.wpack);
 
   chunk_dma<PR, NT>(wp, ct.src[0], ct.len[0], smem, tid);
@@ -1691,10 +1695,13 @@ InferArgs infer_args(const Plan& p, const ntbc_model_desc* d, const ntbc_params*
   a.grid.blocks_w = s.blocks_w;
   a.grid.blocks_h = s.blocks_h;
   for (int l = 0; l <= s.n_levels; ++l) a.grid.level_offset[l] = s.level_offset[l];
-  a.grid.shift_x = pow2_shift(s, s.blocks_w);
-  a.grid.shift_y = pow2_shift(s, s.blocks_h);
-  a.grid.fast8 = a.grid.u8 != nullptr && s.n_features == 8 && a.grid.shift_x >= 0 && a.grid.shift_y >= 0 &&
-                 s.level_offset[s.n_levels] * 8 < (1ll << 31);
+  a.grid.kind_x = corner_kind(s, s.blocks_w);
+  a.grid.kind_y = corner_kind(s, s.blocks_h);
+  a.grid.inv_x = 1.0f / (2.0f * (float)s.blocks_w);
+  a.grid.inv_y = 1.0f / (2.0f * (float)s.blocks_h);
+  if (a.grid.u8 != nullptr && s.n_features == 8 && a.grid.kind_x != kCornerDiv && a.grid.kind_y != kCornerDiv &&
+      s.level_offset[s.n_levels] * 8 < (1ll << 31) && 2 * (int64_t)s.blocks_w <= (1 << 18) && 2 * (int64_t)s.blocks_h <= (1 << 18))
+    a.grid.fast8 = a.grid.kind_x >= 0 && a.grid.kind_y >= 0 ? 1 : 2;
   for (int k = 0; k < s.n_layers; ++k) {
     a.pack_off[k] = p.pack_off[k];
     a.bias_off[k] = p.bias_off[k];
@@ -2269,35 +2276,51 @@ extern "C" int ntbc_infer_batch(const void* table, const void* table_device, voi
 // inputs: one K-step), three hidden layers of 64 SELU units and sigmoid outputs, with half-precision
 // operands and float32 accumulation.  A wave owns 32 blocks: one endpoint-network run and 16
 // colour-network runs (texel i of the 32 blocks at a time), all with the layers chained in registers
-// as in the kernels above; the sigmoid outputs go to LDS in the NTBC head layout and the LDS-staged BC
-// epilogue packs them (Eq. dist), exactly as for the one-trunk model.
-#if NTBC_PART(9)
+// as in the kernels above, and Eq. dist as for the one-trunk model.
+//
+// The kernel is bound by its VALU work (per block 3,264 SELU evaluations, the gathers and the searches;
+// the matrix products are an eighth of that time), so what counts is waves to hide the chained layers'
+// latency behind.  A block's colour heads are therefore never staged: the output rows are permuted so
+// that the two lanes of a position hold the outputs of different textures (lane group g: the BC1 and
+// BC4 textures 2k + g), the endpoint run leaves each lane the palettes of its textures in LDS, and each
+// texel's codes are taken as its colours come out and shifted into the lane's words.  The colour
+// network's weights are read from LDS.  Four waves a SIMD (128 registers) instead of two with 1.5 filled
+// (249 registers and the staged heads, 23 KB a wave): 4096^2, two BC1 and four BC4 textures, uint8
+// grids, 2,997 -> 1,044 us.
+#if NTBC_PART(9) || NTBC_PART(11)
 namespace {
 
-constexpr int kFaWaves = 2;                    // waves (of 32 blocks) per workgroup
-constexpr int kFaHidden = 64;
+constexpr int kFaMaxWaves = 8;                 // waves (of 32 blocks) per workgroup
 constexpr int kFaLayers = 4;                   // three hidden layers and the head
+constexpr int kFaColUnits = (2 + 8 + 8 + 4) * 64;  // packed colour network: 2, 2 x 4, 2 x 4 and 1 x 4 operands
+constexpr int kFaColBias = 7 * 32;
 constexpr float kSeluLambda = 1.0507009873554805f;
 constexpr float kSeluLambdaAlpha = 1.0507009873554805f * 1.6732632423543772f;
 
 struct FaNet {
   int64_t pack_off[kFaLayers];  // u32x4 units in the packed weights
   int bias_off[kFaLayers];      // floats in the padded biases
-  int ksteps[kFaLayers];        // 1, 4, 4, 4
-  int head_tiles;               // 32-row tiles of the outputs
-  int n_out;
 };
 
 struct FaithArgs {
-  InferArgs pk;                 // texture layout, block range, outputs, head stride (for pack_blocks)
   dev::GridView eg, cg;         // endpoint grid (cells = blocks), colour grid (cells = texels)
   const u32x4* wpack;
   const float* bias;
   FaNet ep, col;
+  int64_t first, n;
+  uint64_t* out;                // [n_textures][n]
+  float* heads;                 // optional [n][endpoint_dim + 16 channels]
+  int endpoint_dim, channels;
+  // texture of slot k in lane group g, -1 = none; the offsets of its endpoint and colour heads
+  int tex1[2][4], tex4[2][4], ep1[2][4], ep4[2][4], ch1[2][4], ch4[2][4];
 };
 
+// SELU with the operations of z > 0 ? lambda z : lambda alpha (e^z - 1): the exponential clamped to [0, 1]
+// makes the second term 0 for z > 0, and the NaN-propagating maximum makes the first 0 for z <= 0, so the
+// fused sum adds exactly one of them (NaN stays NaN, -inf gives -lambda alpha).
 __device__ __forceinline__ float selu(float z) {
-  return z > 0.0f ? kSeluLambda * z : kSeluLambdaAlpha * (__expf(z) - 1.0f);
+  const float e = __builtin_amdgcn_fmed3f(__expf(z), 0.0f, 1.0f);
+  return fmaf(kSeluLambda, __builtin_elementwise_maximum(z, 0.0f), kSeluLambdaAlpha * (e - 1.0f));
 }
 
 // SELU of a hidden tile's accumulators (started from the biases) -> the next layer's two B operands.
@@ -2309,141 +2332,306 @@ __device__ __forceinline__ void selu_epilogue(const f32x16_t& acc, u32x4* lo, u3
   *hi = x8_of<Lp::FP16>(r + 8);
 }
 
-// One network run on the 32 positions of the wave (layer-0 operand x0): the first n.n_out sigmoid
-// outputs of position j go to y[j * hs + col0 + k].
-__device__ __forceinline__ void fa_net(const FaithArgs& a, const FaNet& n, const u32x4& x0, float* y, int hs, int col0,
-                                       int lane) {
-  const int j = lane & 31, g = lane >> 5;
-  // the weights and biases are re-read from the cache on every run (opaque base pointers keep the
-  // compiler from hoisting all of them into registers across the 17 runs, which would leave one wave
-  // per SIMD)
-  const u32x4* wp = a.wpack;
-  const float* bias = a.bias;
-  asm volatile("" : "+s"(wp), "+s"(bias));
-  u32x4 h[4], o[4];
+// The hidden layers on the wave's 32 positions: h = the last one's operands.  w, bias: the packed operands and
+// padded biases of a network (in LDS or global memory), its layers one after the other.
+__device__ __forceinline__ void fa_hidden(const u32x4* w, const float* bias, const u32x4& x0, u32x4 (&h)[4], int lane) {
+  const int g = lane >> 5;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    f32x16_t acc = acc_init<Lp::FP16>(bias + n.bias_off[0] + 32 * t, g);
-    acc = mfma16<Lp::FP16>(wp[n.pack_off[0] + (int64_t)t * 64 + lane], x0, acc);
+    f32x16_t acc = acc_init<Lp::FP16>(bias + 32 * t, g);
+    acc = mfma16<Lp::FP16>(w[t * 64 + lane], x0, acc);
     selu_epilogue(acc, &h[2 * t], &h[2 * t + 1]);
   }
 #pragma unroll
   for (int l = 1; l < kFaLayers - 1; ++l) {
+    u32x4 o[4];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      f32x16_t acc = acc_init<Lp::FP16>(bias + n.bias_off[l] + 32 * t, g);
+      f32x16_t acc = acc_init<Lp::FP16>(bias + 64 * l + 32 * t, g);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) acc = mfma16<Lp::FP16>(wp[n.pack_off[l] + ((int64_t)t * 4 + s) * 64 + lane], h[s], acc);
+      for (int s = 0; s < 4; ++s) acc = mfma16<Lp::FP16>(w[(2 + 8 * (l - 1) + 4 * t + s) * 64 + lane], h[s], acc);
       selu_epilogue(acc, &o[2 * t], &o[2 * t + 1]);
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s) h[s] = o[s];
   }
-  for (int t = 0; t < n.head_tiles; ++t) {
-    f32x16_t acc = acc_init<Lp::FP16>(bias + n.bias_off[kFaLayers - 1] + 32 * t, g);
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      acc = mfma16<Lp::FP16>(wp[n.pack_off[kFaLayers - 1] + ((int64_t)t * 4 + s) * 64 + lane], h[s], acc);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int neuron = 32 * t + 8 * (v / 4) + 4 * g + (v % 4);
-      if (neuron < n.n_out) y[j * hs + col0 + neuron] = sigmoid(acc[v]);
-    }
-  }
 }
 
-// Colour-grid gather of a texel split in two so that the loads of the next texel are in flight while
-// the current texel's network runs: the corner loads (uint8 grid, 2 features a vertex: one 16-bit load
-// per corner) and bilinear weights of the lane's four levels (features 8g .. 8g+7), then the blend.
-struct FaTaps {
-  uint32_t raw[4][4];
-  float w[4][4];
-};
-
-__device__ __forceinline__ void fa_load_u8(const dev::GridView& g, int gi, int tx, int ty, FaTaps& t) {
+// Output tile t of a network (pre-activations).
+__device__ __forceinline__ f32x16_t fa_head(const u32x4* w, const float* bias, const u32x4 (&h)[4], int t, int lane) {
+  f32x16_t acc = acc_init<Lp::FP16>(bias + 192 + 32 * t, lane >> 5);
 #pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int level = 4 * gi + h;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      t.raw[h][c] = 0;
-      t.w[h][c] = 0.0f;
-    }
-    if (level < g.n_levels) {
-      const int res = g.base_res << level;
-      const dev::Corner cx = g.shift_x >= 0 ? dev::corner_pow2(tx, g.blocks_w, res, g.shift_x) : dev::corner(tx, g.blocks_w, res);
-      const dev::Corner cy = g.shift_y >= 0 ? dev::corner_pow2(ty, g.blocks_h, res, g.shift_y) : dev::corner(ty, g.blocks_h, res);
-      const int64_t v00 = g.level_offset[level] + (int64_t)cy.i0 * res + cx.i0;
-      const uint16_t* p = reinterpret_cast<const uint16_t*>(g.u8);
-      t.raw[h][0] = p[v00];
-      t.raw[h][1] = p[v00 + 1];
-      t.raw[h][2] = p[v00 + res];
-      t.raw[h][3] = p[v00 + res + 1];
-      t.w[h][0] = (1.0f - cx.f) * (1.0f - cy.f);
-      t.w[h][1] = cx.f * (1.0f - cy.f);
-      t.w[h][2] = (1.0f - cx.f) * cy.f;
-      t.w[h][3] = cx.f * cy.f;
-    }
-  }
+  for (int s = 0; s < 4; ++s) acc = mfma16<Lp::FP16>(w[(18 + 4 * t + s) * 64 + lane], h[s], acc);
+  return acc;
 }
 
-__device__ __forceinline__ void fa_blend_u8(const dev::GridView& g, int gi, const FaTaps& t, float v[8]) {
-#pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int level = 4 * gi + h;
-    const bool on = level < g.n_levels;
-    const float s = on ? g.scale[level] : 0.0f;
-    const float sz = on ? -s * (float)g.zero[level] : 0.0f;
-#pragma unroll
-    for (int f = 0; f < 2; ++f) {
-      float q[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) q[c] = (float)((t.raw[h][c] >> (8 * f)) & 255u);
-      v[2 * h + f] = on ? fmaf(s, fmaf(t.w[h][0], q[0], fmaf(t.w[h][1], q[1], fmaf(t.w[h][2], q[2], t.w[h][3] * q[3]))), sz)
-                        : 0.0f;
-    }
-  }
+// A colour-grid level in LDS: resolution, vertex offset, and scale and -scale * zero point (FP32 grids: 1 and
+// 0).  A level the grid does not have is level 0 with scale 0.  Lane group g takes levels 4g .. 4g+3
+// (features 8g .. 8g+7).
+constexpr int kFaLevels = 8;
+
+__device__ __forceinline__ uint4 fa_level(const dev::GridView& c, int l) {
+  if (l >= c.n_levels) return uint4{(uint32_t)c.base_res, 0u, 0u, 0u};
+  const float s = c.u8 ? c.scale[l] : 1.0f, sz = c.u8 ? -s * (float)c.zero[l] : 0.0f;
+  return uint4{(uint32_t)(c.base_res << l), (uint32_t)c.level_offset[l], __float_as_uint(s), __float_as_uint(sz)};
 }
 
-__global__ void __launch_bounds__(64 * kFaWaves) k_faithful(FaithArgs a) {
-  extern __shared__ float lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = lane & 31, g = lane >> 5;
-  const int64_t pos0 = a.pk.first + ((int64_t)blockIdx.x * kFaWaves + wave) * 32;
-  const int64_t last = a.pk.first + a.pk.n - 1;
-  const int64_t id = pos0 + j <= last ? pos0 + j : last;
-  const int bx = (int)(id % a.eg.blocks_w), by = (int)(id / a.eg.blocks_w);
-  const int hs = a.pk.head_stride;
-  float* y = lds + wave * 32 * hs;
-  float v[8];
-  dev::features<8>(a.eg, 8 * g, bx, by, v);
-  fa_net(a, a.ep, x8_of<Lp::FP16>(v), y, hs, 0, lane);
-  if (a.cg.u8) {
-    // texel i + 1's corner loads are issued before texel i's network runs
-    FaTaps taps;
-    fa_load_u8(a.cg, g, 4 * bx, 4 * by, taps);
-#pragma unroll 1
-    for (int i = 0; i < 16; ++i) {
-      fa_blend_u8(a.cg, g, taps, v);
-      const u32x4 x = x8_of<Lp::FP16>(v);
-      if (i < 15) fa_load_u8(a.cg, g, 4 * bx + ((i + 1) & 3), 4 * by + ((i + 1) >> 2), taps);
-      fa_net(a, a.col, x, y, hs, a.pk.endpoint_dim + i * a.pk.channels, lane);
-    }
+// Corners of axis position b in the lane's four levels.
+__device__ __forceinline__ void fa_corners(const uint4* lv, int b, int blocks, int kind, float inv, dev::Corner (&c)[4]) {
+  if (kind >= 0) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) c[h] = dev::corner_pow2(b, blocks, (int)lv[h].x, kind);
+  } else if (kind == kCornerRcp) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) c[h] = dev::corner_rcp(b, blocks, (int)lv[h].x, inv);
   } else {
 #pragma unroll 1
-    for (int i = 0; i < 16; ++i) {
-      dev::features<8>(a.cg, 8 * g, 4 * bx + (i & 3), 4 * by + (i >> 2), v);
-      fa_net(a, a.col, x8_of<Lp::FP16>(v), y, hs, a.pk.endpoint_dim + i * a.pk.channels, lane);
+    for (int h = 0; h < 4; ++h) {
+      const dev::Corner x = dev::corner(b, blocks, (int)lv[h].x);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k == h) c[k] = x;
+    }
+  }
+}
+
+// The texel's features: both vertices of a row in one load (they are adjacent), blended as dev::sample does.
+// v0[h]: the first vertex of level h's upper row; fy[h]: the fraction down.
+__device__ __forceinline__ void fa_features(const dev::GridView& c, const uint4* lv, const dev::Corner (&cx)[4],
+                                            const uint32_t (&v0)[4], const float (&fy)[4], float v[8]) {
+  typedef uint32_t pair_u8 __attribute__((aligned(2)));
+  typedef float pair_f32 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    const uint32_t v00 = v0[h] + (uint32_t)cx[h].i0, v01 = v00 + lv[h].x;
+    const float w00 = (1.0f - cx[h].f) * (1.0f - fy[h]), w10 = cx[h].f * (1.0f - fy[h]);
+    const float w01 = (1.0f - cx[h].f) * fy[h], w11 = cx[h].f * fy[h];
+    const float s = __uint_as_float(lv[h].z), sz = __uint_as_float(lv[h].w);
+    if (c.u8) {
+      const uint32_t lo = *reinterpret_cast<const pair_u8*>(c.u8 + 2u * (uint64_t)v00);
+      const uint32_t hi = *reinterpret_cast<const pair_u8*>(c.u8 + 2u * (uint64_t)v01);
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        const float q0 = (float)((lo >> (8 * f)) & 255u), q1 = (float)((lo >> (16 + 8 * f)) & 255u);
+        const float q2 = (float)((hi >> (8 * f)) & 255u), q3 = (float)((hi >> (16 + 8 * f)) & 255u);
+        v[2 * h + f] = fmaf(s, fmaf(w00, q0, fmaf(w10, q1, fmaf(w01, q2, w11 * q3))), sz);
+      }
+    } else {
+      const pair_f32 lo = *reinterpret_cast<const pair_f32*>(c.f32 + 2u * (uint64_t)v00);
+      const pair_f32 hi = *reinterpret_cast<const pair_f32*>(c.f32 + 2u * (uint64_t)v01);
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        const float x = fmaf(w00, lo[f], fmaf(w10, lo[2 + f], fmaf(w01, hi[f], w11 * hi[2 + f])));
+        v[2 * h + f] = s != 0.0f ? x : 0.0f;
+      }
+    }
+  }
+}
+
+// N1, N4: BC1 and BC4 slots of a lane group (half the textures of a format, rounded up).  A lane's endpoint
+// outputs: BC1 slot k at 6k .. 6k+5, BC4 slot k at 6 N1 + 2k, +1; its colour outputs of a texel: BC1 slot
+// k at 3k .. 3k+2, BC4 slot k at 3 N1 + k.  Palettes in LDS: BC1 slot k in words 3k .. 3k+2 of the lane,
+// BC4 slot k in words 3 N1 + 2k, +1 (float4, the lanes' words side by side).
+template <int N1, int N4>
+struct FaSlots {
+  static constexpr int kEpTiles = (6 * N1 + 2 * N4 + 15) / 16;
+  static constexpr int kPalWords = 3 * N1 + 2 * N4;
+};
+
+template <int N1, int N4>
+__global__ void __launch_bounds__(64 * kFaMaxWaves) __attribute__((amdgpu_waves_per_eu(4))) k_faithful(FaithArgs a) {
+  using Z = FaSlots<N1, N4>;
+  extern __shared__ u32x4 smem[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int j = lane & 31, g = lane >> 5;
+  float* bias_s = reinterpret_cast<float*>(smem + kFaColUnits);
+  uint4* lv_s = reinterpret_cast<uint4*>(smem + kFaColUnits + kFaColBias / 4);
+  float4* pal = reinterpret_cast<float4*>(lv_s + kFaLevels) + wave * Z::kPalWords * 64 + lane;
+  if (threadIdx.x < kFaLevels) lv_s[threadIdx.x] = fa_level(a.cg, threadIdx.x);
+  for (int e = threadIdx.x; e < kFaColUnits; e += blockDim.x) smem[e] = a.wpack[a.col.pack_off[0] + e];
+  for (int e = threadIdx.x; e < kFaColBias; e += blockDim.x) bias_s[e] = a.bias[a.col.bias_off[0] + e];
+
+  const int64_t pos0 = a.first + (xcd_tile(blockIdx.x, gridDim.x) * waves + wave) * 32;
+  const int64_t last = a.first + a.n - 1;
+  const int64_t id = pos0 + j <= last ? pos0 + j : last;
+  const bool valid = pos0 + j <= last;
+  int bx, by;
+  dev::block_of(id, last, a.eg.blocks_w, &bx, &by);
+  const int64_t row = id - a.first;
+  float* hrow = a.heads ? a.heads + row * (a.endpoint_dim + 16 * a.channels) : nullptr;
+
+  // endpoint network: the palettes of the lane's textures
+  uint32_t ends1[N1 > 0 ? N1 : 1], ends4[N4 > 0 ? N4 : 1];
+  {
+    float v[8];
+    dev::features<8>(a.eg, 8 * g, bx, by, v);
+    u32x4 h[4];
+    const u32x4* we = a.wpack + a.ep.pack_off[0];
+    const float* be = a.bias + a.ep.bias_off[0];
+    fa_hidden(we, be, x8_of<Lp::FP16>(v), h, lane);
+    float y[16 * Z::kEpTiles];
+#pragma unroll
+    for (int t = 0; t < Z::kEpTiles; ++t) {
+      const f32x16_t acc = fa_head(we, be, h, t, lane);
+#pragma unroll
+      for (int s = 0; s < 16; ++s)
+        if (16 * t + s < 6 * N1 + 2 * N4) y[16 * t + s] = sigmoid(acc[s]);
+    }
+#pragma unroll
+    for (int k = 0; k < N1; ++k) {
+      const dev::Bc1Pal p = dev::bc1_from_heads(y + 6 * k);
+      ends1[k] = p.c0 | (p.c1 << 16);
+      pal[(3 * k) * 64] = float4{p.pal[0][0], p.pal[0][1], p.pal[0][2], p.pal[1][0]};
+      pal[(3 * k + 1) * 64] = float4{p.pal[1][1], p.pal[1][2], p.pal[2][0], p.pal[2][1]};
+      pal[(3 * k + 2) * 64] = float4{p.pal[2][2], p.pal[3][0], p.pal[3][1], p.pal[3][2]};
+      if (hrow && valid && (g ? a.tex1[1][k] : a.tex1[0][k]) >= 0) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) hrow[(g ? a.ep1[1][k] : a.ep1[0][k]) + c] = y[6 * k + c];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < N4; ++k) {
+      const dev::Bc4Pal p = dev::bc4_from_heads(y + 6 * N1 + 2 * k);
+      ends4[k] = (uint32_t)p.e0 | ((uint32_t)p.e1 << 8);
+      pal[(3 * N1 + 2 * k) * 64] = float4{p.pal[0], p.pal[1], p.pal[2], p.pal[3]};
+      pal[(3 * N1 + 2 * k + 1) * 64] = float4{p.pal[4], p.pal[5], p.pal[6], p.pal[7]};
+      if (hrow && valid && (g ? a.tex4[1][k] : a.tex4[0][k]) >= 0) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) hrow[(g ? a.ep4[1][k] : a.ep4[0][k]) + c] = y[6 * N1 + 2 * k + c];
+      }
     }
   }
   __syncthreads();
-  // inlined here: an out-of-line call would take the kernel argument by address, i.e. copy it to scratch
-  [[clang::always_inline]] pack_blocks<32>(a.pk, y, lane, pos0);
+
+  // colour network, texel 4 ty + tx: its codes enter the words from the top, so after sixteen texels the
+  // BC1 word holds texel i at 2i and the BC4 pair (lo, hi) is the block's word above bit 16
+  uint32_t codes1[N1 > 0 ? N1 : 1] = {}, lo4[N4 > 0 ? N4 : 1] = {}, hi4[N4 > 0 ? N4 : 1] = {};
+  const uint4* lv = lv_s + 4 * g;
+#pragma unroll 1
+  for (int ty = 0; ty < 4; ++ty) {
+    uint32_t v0[4];
+    float fy[4];
+    {
+      dev::Corner cy[4];
+      fa_corners(lv, 4 * by + ty, a.cg.blocks_h, a.cg.kind_y, a.cg.inv_y, cy);
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        v0[h] = lv[h].y + (uint32_t)cy[h].i0 * lv[h].x;
+        fy[h] = cy[h].f;
+      }
+    }
+#pragma unroll 1
+    for (int tx = 0; tx < 4; ++tx) {
+      // the level table, the weights and the palettes are read again for every texel: an opaque offset keeps
+      // the compiler from hoisting them into registers across the sixteen runs
+      uint32_t zero = 0;
+      asm volatile("" : "+v"(zero));
+      float v[8];
+      {
+        dev::Corner cx[4];
+        fa_corners(lv + zero, 4 * bx + tx, a.cg.blocks_w, a.cg.kind_x, a.cg.inv_x, cx);
+        fa_features(a.cg, lv + zero, cx, v0, fy, v);
+      }
+      u32x4 h[4];
+      fa_hidden(smem + zero, bias_s + zero, x8_of<Lp::FP16>(v), h, lane);
+      const f32x16_t acc = fa_head(smem + zero, bias_s + zero, h, 0, lane);
+      float y[3 * N1 + N4];
+#pragma unroll
+      for (int s = 0; s < 3 * N1 + N4; ++s) y[s] = sigmoid(acc[s]);
+      const float4* pw = pal + zero;
+#pragma unroll
+      for (int k = 0; k < N1; ++k) {
+        const float4 p0 = pw[(3 * k) * 64], p1 = pw[(3 * k + 1) * 64], p2 = pw[(3 * k + 2) * 64];
+        dev::Bc1Pal p;
+        p.map = (ends1[k] & 0xFFFFu) == (ends1[k] >> 16) ? 0u : 0x78u;
+        const float e[12] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, p2.x, p2.y, p2.z, p2.w};
+#pragma unroll
+        for (int q = 0; q < 12; ++q) p.pal[q / 3][q % 3] = e[q];
+        codes1[k] = __builtin_amdgcn_alignbit(dev::bc1_code(p, y[3 * k], y[3 * k + 1], y[3 * k + 2]), codes1[k], 2);
+      }
+#pragma unroll
+      for (int k = 0; k < N4; ++k) {
+        const float4 p0 = pw[(3 * N1 + 2 * k) * 64], p1 = pw[(3 * N1 + 2 * k + 1) * 64];
+        dev::Bc4Pal p;
+        p.map = dev::bc4_map((ends4[k] & 255u) > (ends4[k] >> 8));
+        const float e[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) p.pal[q] = e[q];
+        const uint32_t code = dev::bc4_code(p, y[3 * N1 + k]);
+        lo4[k] = __builtin_amdgcn_alignbit(hi4[k], lo4[k], 3);
+        hi4[k] = __builtin_amdgcn_alignbit(code, hi4[k], 3);
+      }
+      if (hrow && valid) {
+        float* hc = hrow + a.endpoint_dim + (4 * ty + tx) * a.channels;
+#pragma unroll
+        for (int k = 0; k < N1; ++k) {
+          if ((g ? a.tex1[1][k] : a.tex1[0][k]) < 0) continue;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) hc[(g ? a.ch1[1][k] : a.ch1[0][k]) + c] = y[3 * k + c];
+        }
+#pragma unroll
+        for (int k = 0; k < N4; ++k)
+          if ((g ? a.tex4[1][k] : a.tex4[0][k]) >= 0) hc[g ? a.ch4[1][k] : a.ch4[0][k]] = y[3 * N1 + k];
+      }
+    }
+  }
+  if (!valid) return;
+#pragma unroll
+  for (int k = 0; k < N1; ++k) {
+    const int t = g ? a.tex1[1][k] : a.tex1[0][k];
+    if (t >= 0) a.out[(int64_t)t * a.n + row] = (uint64_t)ends1[k] | ((uint64_t)codes1[k] << 32);
+  }
+#pragma unroll
+  for (int k = 0; k < N4; ++k) {
+    const int t = g ? a.tex4[1][k] : a.tex4[0][k];
+    if (t >= 0) a.out[(int64_t)t * a.n + row] = (uint64_t)(lo4[k] | ends4[k]) | ((uint64_t)hi4[k] << 32);
+  }
 }
+
+}  // namespace
+
+namespace ntbc {
+typedef void (*FaLaunch)(dim3, dim3, size_t, hipStream_t, const void* args);
+// The kernel of (N1, N4) slots: every mix of at most eight textures, N1 <= 1 in one part, the others in another.
+bool fa_instance_lo(int n1, int n4, const void** fn, FaLaunch* launch);
+bool fa_instance_hi(int n1, int n4, const void** fn, FaLaunch* launch);
+#define NTBC_FA_INSTANCE(A, B)                                                                        \
+  if (n1 == A && n4 == B) {                                                                           \
+    *fn = (const void*)k_faithful<A, B>;                                                              \
+    *launch = [](dim3 gr, dim3 bl, size_t sh, hipStream_t st, const void* x) {                        \
+      hipLaunchKernelGGL((k_faithful<A, B>), gr, bl, sh, st, *static_cast<const FaithArgs*>(x));      \
+    };                                                                                                \
+    return true;                                                                                      \
+  }
+#if NTBC_PART(9)
+bool fa_instance_lo(int n1, int n4, const void** fn, FaLaunch* launch) {
+  NTBC_FA_INSTANCE(0, 1) NTBC_FA_INSTANCE(0, 2) NTBC_FA_INSTANCE(0, 3) NTBC_FA_INSTANCE(0, 4)
+  NTBC_FA_INSTANCE(1, 0) NTBC_FA_INSTANCE(1, 1) NTBC_FA_INSTANCE(1, 2) NTBC_FA_INSTANCE(1, 3) NTBC_FA_INSTANCE(1, 4)
+  return false;
+}
+#endif
+#if NTBC_PART(11)
+bool fa_instance_hi(int n1, int n4, const void** fn, FaLaunch* launch) {
+  NTBC_FA_INSTANCE(2, 0) NTBC_FA_INSTANCE(2, 1) NTBC_FA_INSTANCE(2, 2) NTBC_FA_INSTANCE(2, 3)
+  NTBC_FA_INSTANCE(3, 0) NTBC_FA_INSTANCE(3, 1) NTBC_FA_INSTANCE(3, 2) NTBC_FA_INSTANCE(4, 0) NTBC_FA_INSTANCE(4, 1)
+  return false;
+}
+#endif
+#undef NTBC_FA_INSTANCE
+}  // namespace ntbc
+#endif  // NTBC_PART(9) || NTBC_PART(11)
+
+#if NTBC_PART(9)
+namespace {
+
+constexpr int kFaHidden = 64;
 
 // Shape of one model of the paper's layout.
 struct FaShape {
-  int E, C, in_ep, in_col, ep_tiles;
+  int E, C, in_ep, in_col;
+  int n1, n4;                           // BC1 and BC4 slots of a lane group
+  int tex1[2][4], tex4[2][4];           // texture of slot k in lane group g (texture 2k + g of its format), -1 = none
+  int ep_off[NTBC_MAX_TEXTURES], ch_off[NTBC_MAX_TEXTURES];
   int64_t n_ep, n_col;                  // canonical FP32 weights of each network
   int64_t pack_units, bias_floats;      // packed operands (u32x4) and padded biases of both networks
   FaNet ep, col;
@@ -2454,13 +2642,29 @@ int64_t fa_net_weights(int in, int out) {
   return (int64_t)in * kFaHidden + kFaHidden + 2 * ((int64_t)kFaHidden * kFaHidden + kFaHidden) + (int64_t)kFaHidden * out + out;
 }
 
-void fa_plan_net(int in, int out, int64_t* units, int64_t* bias, FaNet* n, PackArgs* pa) {
+// Canonical output of packed head row `row` (FaSlots), -1 for a padding row: endpoint network or colour network.
+int fa_source(const FaShape& s, int row, bool endpoints) {
+  const int t = row / 32, q = (row % 32) / 8, g = (row % 8) / 4, slot = 16 * t + 4 * q + row % 4;
+  const int per1 = endpoints ? 6 : 3, per4 = endpoints ? 2 : 1;
+  const int* off = endpoints ? s.ep_off : s.ch_off;
+  if (slot < per1 * s.n1) {
+    const int tex = s.tex1[g][slot / per1];
+    return tex < 0 ? -1 : off[tex] + slot % per1;
+  }
+  const int r = slot - per1 * s.n1;
+  if (r >= per4 * s.n4) return -1;
+  const int tex = s.tex4[g][r / per4];
+  return tex < 0 ? -1 : off[tex] + r % per4;
+}
+
+void fa_plan_net(const FaShape& s, int in, int out, int head_tiles, bool endpoints, int64_t* units, int64_t* bias, FaNet* n,
+                 PackArgs* pa) {
   const int dims[kFaLayers + 1] = {in, kFaHidden, kFaHidden, kFaHidden, out};
   *pa = PackArgs{};
   pa->n_layers = kFaLayers;
+  pa->head_perm = 1;
+  for (int r = 0; r < kHeadRows; ++r) pa->head_src[r] = (int16_t)(r < 32 * head_tiles ? fa_source(s, r, endpoints) : -1);
   int64_t w = 0;
-  n->n_out = out;
-  n->head_tiles = (out + 31) / 32;
   for (int k = 0; k < kFaLayers; ++k) {
     pa->in_dim[k] = dims[k];
     pa->out_dim[k] = dims[k + 1];
@@ -2468,9 +2672,8 @@ void fa_plan_net(int in, int out, int64_t* units, int64_t* bias, FaNet* n, PackA
     w += (int64_t)dims[k] * dims[k + 1];
     pa->b_off[k] = w;
     w += dims[k + 1];
-    n->ksteps[k] = k == 0 ? 1 : 4;
-    pa->ksteps[k] = n->ksteps[k];
-    pa->otiles[k] = k == kFaLayers - 1 ? n->head_tiles : 2;
+    pa->ksteps[k] = k == 0 ? 1 : 4;
+    pa->otiles[k] = k == kFaLayers - 1 ? head_tiles : 2;
     pa->pack_off[k] = *units;
     n->pack_off[k] = *units;
     *units += (int64_t)pa->otiles[k] * pa->ksteps[k] * 64;
@@ -2493,19 +2696,28 @@ int fa_shape(const ntbc_faithful_desc* d, FaShape* s) {
   NTBC_REQUIRE(d->blocks_w >= 1 && d->blocks_h >= 1 && (int64_t)d->blocks_w * 4 <= 65536 && (int64_t)d->blocks_h * 4 <= 65536,
                "block grid %dx%d out of range", d->blocks_w, d->blocks_h);
   *s = FaShape{};
+  int nb1 = 0, nb4 = 0;
+  for (int k = 0; k < 8; ++k) s->tex1[k / 4][k % 4] = s->tex4[k / 4][k % 4] = -1;
   for (int t = 0; t < d->n_textures; ++t) {
     NTBC_REQUIRE(d->formats[t] == NTBC_BC1 || d->formats[t] == NTBC_BC4, "formats[%d] = %d", t, d->formats[t]);
-    s->E += d->formats[t] == NTBC_BC1 ? 6 : 2;
-    s->C += d->formats[t] == NTBC_BC1 ? 3 : 1;
+    const bool bc1 = d->formats[t] == NTBC_BC1;
+    s->ep_off[t] = s->E;
+    s->ch_off[t] = s->C;
+    s->E += bc1 ? 6 : 2;
+    s->C += bc1 ? 3 : 1;
+    const int k = bc1 ? nb1++ : nb4++;
+    (bc1 ? s->tex1 : s->tex4)[k % 2][k / 2] = t;
   }
+  s->n1 = (nb1 + 1) / 2;
+  s->n4 = (nb4 + 1) / 2;
   NTBC_REQUIRE(s->E <= 64 && s->C <= 32, "endpoint outputs %d > 64 or colour outputs %d > 32", s->E, s->C);
   s->in_ep = 2 * d->ep_levels;
   s->in_col = 2 * d->col_levels;
   s->n_ep = fa_net_weights(s->in_ep, s->E);
   s->n_col = fa_net_weights(s->in_col, s->C);
-  fa_plan_net(s->in_ep, s->E, &s->pack_units, &s->bias_floats, &s->ep, &s->pa_ep);
-  fa_plan_net(s->in_col, s->C, &s->pack_units, &s->bias_floats, &s->col, &s->pa_col);
-  s->ep_tiles = s->ep.head_tiles;
+  const int ep_tiles = (6 * s->n1 + 2 * s->n4 + 15) / 16;
+  fa_plan_net(*s, s->in_ep, s->E, ep_tiles, true, &s->pack_units, &s->bias_floats, &s->ep, &s->pa_ep);
+  fa_plan_net(*s, s->in_col, s->C, 1, false, &s->pack_units, &s->bias_floats, &s->col, &s->pa_col);
   return NTBC_OK;
 }
 
@@ -2532,8 +2744,10 @@ dev::GridView fa_grid(int levels, int base, int blocks_w, int blocks_h, int u8, 
     off += ((int64_t)base << l) * ((int64_t)base << l);
   }
   g.level_offset[levels] = off;
-  g.shift_x = pow2_shift(sh, blocks_w);
-  g.shift_y = pow2_shift(sh, blocks_h);
+  g.kind_x = corner_kind(sh, blocks_w);
+  g.kind_y = corner_kind(sh, blocks_h);
+  g.inv_x = 1.0f / (2.0f * (float)blocks_w);
+  g.inv_y = 1.0f / (2.0f * (float)blocks_h);
   g.fast8 = 0;
   return g;
 }
@@ -2577,24 +2791,20 @@ extern "C" int ntbc_faithful_infer(const ntbc_faithful_desc* d, const ntbc_faith
   st = check_launch("ntbc_faithful_infer: pack");
   if (st != NTBC_OK) return st;
   FaithArgs a{};
-  InferArgs& k = a.pk;
-  k.n_textures = d->n_textures;
-  int e = 0, c = 0;
-  for (int t = 0; t < d->n_textures; ++t) {
-    k.formats[t] = d->formats[t];
-    k.ep_off[t] = e;
-    k.ch_off[t] = c;
-    e += d->formats[t] == NTBC_BC1 ? 6 : 2;
-    c += d->formats[t] == NTBC_BC1 ? 3 : 1;
-  }
-  k.endpoint_dim = s.E;
-  k.channels = s.C;
-  k.head_dim = s.E + 16 * s.C;
-  k.head_stride = k.head_dim | 1;
-  k.first = first_block;
-  k.n = n_blocks;
-  k.out = blocks_out;
-  k.heads = heads_out;
+  a.first = first_block;
+  a.n = n_blocks;
+  a.out = blocks_out;
+  a.heads = heads_out;
+  a.endpoint_dim = s.E;
+  a.channels = s.C;
+  for (int g = 0; g < 2; ++g)
+    for (int k = 0; k < 4; ++k) {
+      const int t1 = a.tex1[g][k] = s.tex1[g][k], t4 = a.tex4[g][k] = s.tex4[g][k];
+      a.ep1[g][k] = t1 < 0 ? 0 : s.ep_off[t1];
+      a.ch1[g][k] = t1 < 0 ? 0 : s.ch_off[t1];
+      a.ep4[g][k] = t4 < 0 ? 0 : s.ep_off[t4];
+      a.ch4[g][k] = t4 < 0 ? 0 : s.ch_off[t4];
+    }
   const int u8 = d->grid_dtype == NTBC_GRID_U8;
   a.eg = fa_grid(d->ep_levels, d->ep_base_res, d->blocks_w, d->blocks_h, u8, p->ep_grid, p->ep_scale, p->ep_zero);
   a.cg = fa_grid(d->col_levels, d->col_base_res, 4 * d->blocks_w, 4 * d->blocks_h, u8, p->col_grid, p->col_scale,
@@ -2603,11 +2813,18 @@ extern "C" int ntbc_faithful_infer(const ntbc_faithful_desc* d, const ntbc_faith
   a.bias = bias;
   a.ep = s.ep;
   a.col = s.col;
-  const size_t lds = (size_t)kFaWaves * 32 * k.head_stride * sizeof(float);
-  NTBC_REQUIRE(lds <= 160 * 1024, "heads need %zu bytes of LDS", lds);
-  NTBC_HIP(hipFuncSetAttribute((const void*)k_faithful, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  const unsigned blocks = (unsigned)ceil_div(n_blocks, 32 * kFaWaves);
-  hipLaunchKernelGGL(k_faithful, dim3(blocks), dim3(64 * kFaWaves), lds, strm, a);
+  const void* fn = nullptr;
+  FaLaunch launch = nullptr;
+  NTBC_REQUIRE(s.n1 <= 1 ? fa_instance_lo(s.n1, s.n4, &fn, &launch) : fa_instance_hi(s.n1, s.n4, &fn, &launch),
+               "no kernel instance for %d BC1 and %d BC4 slots", s.n1, s.n4);
+  // waves per workgroup: eight share the weights' LDS copy (two such workgroups fill a CU); fewer while that
+  // leaves CUs without a workgroup
+  const int64_t tiles = ceil_div(n_blocks, 32);
+  int waves = kFaMaxWaves;
+  while (waves > 1 && tiles < 512 * (int64_t)waves) waves /= 2;
+  const size_t lds = (size_t)(kFaColUnits + kFaColBias / 4 + kFaLevels) * 16 + (size_t)waves * (3 * s.n1 + 2 * s.n4) * 64 * 16;
+  NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  launch(dim3((unsigned)ceil_div(tiles, waves)), dim3(64 * waves), lds, strm, &a);
   return check_launch("k_faithful");
 }
 #endif  // NTBC_PART(9)

@@ -171,7 +171,9 @@ struct FeatArgs {
   const int32_t* ids;
   int64_t n;
   int n_levels, base_res, F, blocks_w, blocks_h;
-  int shift_x, shift_y;  // pow2_shift of the block grid, -1: the division path
+  int f_shift;           // log2(F)
+  int kind_x, kind_y;    // corner_kind of the two axes
+  float inv_x, inv_y;    // 1 / (2 * blocks)
   int64_t level_offset[NTBC_MAX_LEVELS + 1];
   float* x;          // [n][L*F]
 };
@@ -185,8 +187,8 @@ struct Tap {
 __device__ __forceinline__ Tap grid_tap_id(const FeatArgs& a, int id, int l) {
   const int bx = id % a.blocks_w, by = id / a.blocks_w;
   const int res = a.base_res << l;
-  const dev::Corner cx = a.shift_x >= 0 ? dev::corner_pow2(bx, a.blocks_w, res, a.shift_x) : dev::corner(bx, a.blocks_w, res);
-  const dev::Corner cy = a.shift_y >= 0 ? dev::corner_pow2(by, a.blocks_h, res, a.shift_y) : dev::corner(by, a.blocks_h, res);
+  const dev::Corner cx = dev::corner_of(bx, a.blocks_w, res, a.kind_x, a.inv_x);
+  const dev::Corner cy = dev::corner_of(by, a.blocks_h, res, a.kind_y, a.inv_y);
   const int64_t v00 = a.level_offset[l] + (int64_t)cy.i0 * res + cx.i0;
   Tap t;
   t.vtx[0] = v00;
@@ -204,15 +206,26 @@ __device__ __forceinline__ Tap grid_tap(const FeatArgs& a, int64_t p, int l) {
   return grid_tap_id(a, clamp_id(a.ids[p], (int64_t)a.blocks_w * a.blocks_h), l);
 }
 
+// e / d and its remainder, e and d below 2^31 when `small` (uniform).
+__device__ __forceinline__ int64_t div_mod(int64_t e, int d, bool small, int* rem) {
+  if (small) {
+    const uint32_t q = (uint32_t)e / (uint32_t)d;
+    *rem = (int)((uint32_t)e - q * (uint32_t)d);
+    return q;
+  }
+  *rem = (int)(e % d);
+  return e / d;
+}
+
 // One thread per (position, level, feature); the F lanes of a (position, level) read the F
 // consecutive features of each corner together.
 __global__ void __launch_bounds__(kBlock) k_features(FeatArgs a) {
   const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (gid >= a.n * a.n_levels * a.F) return;
-  const int f = (int)(gid % a.F);
-  const int64_t pl = gid / a.F;
-  const int64_t p = pl / a.n_levels;
-  const int l = (int)(pl % a.n_levels);
+  const int f = (int)gid & (a.F - 1);
+  const int64_t pl = gid >> a.f_shift;
+  int l;
+  const int64_t p = div_mod(pl, a.n_levels, a.n * a.n_levels <= 0x7fffffff, &l);
   const Tap t = grid_tap(a, p, l);
   const float s = a.stats ? reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l] : 1.0f;
   const int z = a.stats ? a.stats[3 * NTBC_MAX_LEVELS + l] : 0;
@@ -270,9 +283,10 @@ __global__ void __launch_bounds__(kBlock) k_scatter(FeatArgs a, const float* __r
   const int nl = a.n_levels - first_level;
   const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (gid >= a.n * nl * a.F) return;
-  const int f = (int)(gid % a.F);
-  const int64_t pl = gid / a.F;
-  scatter_one<Acc>(a, dx, pl / nl, first_level + (int)(pl % nl), f, dgrid, det_scale ? *det_scale : 1.0f);
+  const int f = (int)gid & (a.F - 1);
+  int l;
+  const int64_t p = div_mod(gid >> a.f_shift, nl, a.n * nl <= 0x7fffffff, &l);
+  scatter_one<Acc>(a, dx, p, first_level + l, f, dgrid, det_scale ? *det_scale : 1.0f);
 }
 
 // Levels [first_level, n_levels) when the positions are the texels of whole blocks (16 consecutive
@@ -288,18 +302,18 @@ __global__ void __launch_bounds__(kBlock) k_scatter_texels(FeatArgs a, const flo
   const int nl = a.n_levels - first_level;
   const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (gid >= (a.n / 16) * nl * a.F) return;
-  const int f = (int)(gid % a.F);
-  const int64_t pl = gid / a.F;
-  const int l = first_level + (int)(pl % nl);
-  const int64_t b = pl / nl;
+  const int f = (int)gid & (a.F - 1);
+  int l;
+  const int64_t b = div_mod(gid >> a.f_shift, nl, a.n * nl <= 0x7fffffff, &l);
+  l += first_level;
   const int t0 = clamp_id(a.ids[16 * b], (int64_t)a.blocks_w * a.blocks_h);
   const int tx0 = t0 % a.blocks_w, ty0 = t0 / a.blocks_w;
   const int res = a.base_res << l;
   dev::Corner cx[4], cy[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    cx[k] = a.shift_x >= 0 ? dev::corner_pow2(tx0 + k, a.blocks_w, res, a.shift_x) : dev::corner(tx0 + k, a.blocks_w, res);
-    cy[k] = a.shift_y >= 0 ? dev::corner_pow2(ty0 + k, a.blocks_h, res, a.shift_y) : dev::corner(ty0 + k, a.blocks_h, res);
+    cx[k] = dev::corner_of(tx0 + k, a.blocks_w, res, a.kind_x, a.inv_x);
+    cy[k] = dev::corner_of(ty0 + k, a.blocks_h, res, a.kind_y, a.inv_y);
   }
   // rows: T[y][c] = sum over x of wx(x, c) d(x, y), column c = vertex cx[0].i0 + c
   float tr[4][5];
@@ -366,8 +380,9 @@ __global__ void __launch_bounds__(kCoarseThreads) k_scatter_coarse(FeatArgs a, c
   const int64_t nv = a.level_offset[n_coarse] * a.F;
   for (int64_t i = threadIdx.x; i < nv; i += kCoarseThreads) acc[i] = (Acc)0;
   __syncthreads();
-  const int64_t per_pos = (int64_t)n_coarse * a.F;
+  const int per_pos = n_coarse * a.F;
   const int64_t total = a.n * per_pos;
+  const bool small = total <= 0x7fffffff;
   const int64_t share = (total + gridDim.x - 1) / gridDim.x;
   const int64_t e0 = (int64_t)blockIdx.x * share, e1 = e0 + share < total ? e0 + share : total;
   // four elements a round, their loads issued together (the loop is latency-bound otherwise)
@@ -380,14 +395,13 @@ __global__ void __launch_bounds__(kCoarseThreads) k_scatter_coarse(FeatArgs a, c
     for (int u = 0; u < kU; ++u) {
       const int64_t ee = e + (int64_t)u * kCoarseThreads;
       const bool ok = ee < e1;
-      const int64_t p = ok ? ee / per_pos : 0;
-      lf[u] = (int)(ee - p * per_pos);
+      const int64_t p = div_mod(ok ? ee : 0, per_pos, small, &lf[u]);
       df[u] = ok ? dx[p * a.n_levels * a.F + lf[u]] : 0.0f;
       id[u] = ok ? a.ids[p] : 0;
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u)
-      scatter_tap<Acc>(a, df[u], clamp_id(id[u], npos), lf[u] / a.F, lf[u] % a.F, acc, scale);
+      scatter_tap<Acc>(a, df[u], clamp_id(id[u], npos), lf[u] >> a.f_shift, lf[u] & (a.F - 1), acc, scale);
   }
   __syncthreads();
   Acc* row = part + (int64_t)blockIdx.x * nv;
@@ -1596,8 +1610,8 @@ __global__ void __launch_bounds__(256) k_pack_train(PackTrainArgs a) {
   const int64_t total = (int64_t)ot * ks * 64;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int l = (int)(e % 64);
-    const int s = (int)((e / 64) % ks);
-    const int t = (int)(e / (64 * (int64_t)ks));
+    const int t = (int)((uint32_t)(e / 64) / (uint32_t)ks);
+    const int s = (int)(e / 64) - t * ks;
     const int row = 32 * t + (l % 32), g = l / 32;
     float v[8];
 #pragma unroll
@@ -1628,7 +1642,8 @@ struct FwdArgs {
   const int32_t* ids;
   int64_t n, n_positions;
   int n_levels, base_res, F, blocks_w, blocks_h, in_dim;
-  int shift_x, shift_y;       // pow2_shift of the block grid, -1: the division path
+  int kind_x, kind_y;         // corner_kind of the two axes
+  float inv_x, inv_y;         // 1 / (2 * blocks)
   int64_t level_offset[NTBC_MAX_LEVELS + 1];
   const u32x4* wpack;
   const float* bias;
@@ -1643,63 +1658,54 @@ struct FwdArgs {
   FChunks ct;
 };
 
-// Features c0 .. c0+7 of a position (the layer-0 B operand values), from the FP32 master grid
-// fake-quantised per level when QAT is on: the arithmetic of k_features.
+// Bilinear values of the FE features from f0 of level l (FE = 8, 4 or 1 consecutive features of a vertex,
+// read as 16-byte words for 8 and 4), fake-quantised per level when QAT is on: the arithmetic of
+// k_features.
+template <int FE>
+__device__ __forceinline__ void fsample(const FwdArgs& a, int l, int f0, int bx, int by, float* v) {
+  const int res = a.base_res << l;
+  const dev::Corner cx = dev::corner_of(bx, a.blocks_w, res, a.kind_x, a.inv_x);
+  const dev::Corner cy = dev::corner_of(by, a.blocks_h, res, a.kind_y, a.inv_y);
+  const int64_t v00 = a.level_offset[l] + (int64_t)cy.i0 * res + cx.i0;
+  const int64_t vtx[4] = {v00, v00 + 1, v00 + res, v00 + res + 1};
+  const float w[4] = {(1.0f - cx.f) * (1.0f - cy.f), cx.f * (1.0f - cy.f), (1.0f - cx.f) * cy.f, cx.f * cy.f};
+  float q[4][FE];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) dev::load_f32<FE>(a.grid + vtx[c] * a.F + f0, q[c]);
+  if (a.stats) {
+    const float s = reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l];
+    const int z = a.stats[3 * NTBC_MAX_LEVELS + l];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int m = 0; m < FE; ++m) {
+        bool inside;
+        q[c][m] = fake_quant(q[c][m], s, z, &inside);
+      }
+  }
+#pragma unroll
+  for (int m = 0; m < FE; ++m) v[m] = fmaf(w[0], q[0][m], fmaf(w[1], q[1][m], fmaf(w[2], q[2][m], w[3] * q[3][m])));
+}
+
+// Features c0 .. c0+7 of a position (the layer-0 B operand values), zero past in_dim.  The vertices' features
+// are 16-byte words for F = 8 and F = 4 (F = 4: when the grid is 16-byte aligned), single loads otherwise.
 __device__ __forceinline__ void ffeatures(const FwdArgs& a, int c0, int bx, int by, float v[8]) {
 #pragma unroll
   for (int m = 0; m < 8; ++m) v[m] = 0.0f;
   if (a.F == 8) {
-    if (c0 >= a.in_dim) return;
-    const int l = c0 / 8;
-    const int res = a.base_res << l;
-    const dev::Corner cx = a.shift_x >= 0 ? dev::corner_pow2(bx, a.blocks_w, res, a.shift_x) : dev::corner(bx, a.blocks_w, res);
-    const dev::Corner cy = a.shift_y >= 0 ? dev::corner_pow2(by, a.blocks_h, res, a.shift_y) : dev::corner(by, a.blocks_h, res);
-    const int64_t v00 = a.level_offset[l] + (int64_t)cy.i0 * res + cx.i0;
-    const int64_t vtx[4] = {v00, v00 + 1, v00 + res, v00 + res + 1};
-    const float w[4] = {(1.0f - cx.f) * (1.0f - cy.f), cx.f * (1.0f - cy.f), (1.0f - cx.f) * cy.f, cx.f * cy.f};
-    float q[4][8];
+    if (c0 < a.in_dim) fsample<8>(a, c0 / 8, 0, bx, by, v);
+    return;
+  }
+  if (a.F == 4 && (reinterpret_cast<uintptr_t>(a.grid) & 15) == 0) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float4 lo = *reinterpret_cast<const float4*>(a.grid + vtx[c] * 8);
-      const float4 hi = *reinterpret_cast<const float4*>(a.grid + vtx[c] * 8 + 4);
-      q[c][0] = lo.x, q[c][1] = lo.y, q[c][2] = lo.z, q[c][3] = lo.w;
-      q[c][4] = hi.x, q[c][5] = hi.y, q[c][6] = hi.z, q[c][7] = hi.w;
-    }
-    if (a.stats) {
-      const float s = reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l];
-      const int z = a.stats[3 * NTBC_MAX_LEVELS + l];
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          bool inside;
-          q[c][m] = fake_quant(q[c][m], s, z, &inside);
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < 8; ++m) v[m] = fmaf(w[0], q[0][m], fmaf(w[1], q[1][m], fmaf(w[2], q[2][m], w[3] * q[3][m])));
+    for (int h = 0; h < 2; ++h)
+      if (c0 + 4 * h < a.in_dim) fsample<4>(a, c0 / 4 + h, 0, bx, by, v + 4 * h);
     return;
   }
   for (int m = 0; m < 8; ++m) {
     const int c = c0 + m;
     if (c >= a.in_dim) break;
-    const int l = c / a.F, f = c % a.F;
-    const int res = a.base_res << l;
-    const dev::Corner cx = a.shift_x >= 0 ? dev::corner_pow2(bx, a.blocks_w, res, a.shift_x) : dev::corner(bx, a.blocks_w, res);
-    const dev::Corner cy = a.shift_y >= 0 ? dev::corner_pow2(by, a.blocks_h, res, a.shift_y) : dev::corner(by, a.blocks_h, res);
-    const int64_t v00 = a.level_offset[l] + (int64_t)cy.i0 * res + cx.i0;
-    const int64_t vtx[4] = {v00, v00 + 1, v00 + res, v00 + res + 1};
-    const float w[4] = {(1.0f - cx.f) * (1.0f - cy.f), cx.f * (1.0f - cy.f), (1.0f - cx.f) * cy.f, cx.f * cy.f};
-    float q[4];
-    for (int k = 0; k < 4; ++k) {
-      q[k] = a.grid[vtx[k] * a.F + f];
-      if (a.stats) {
-        bool inside;
-        q[k] = fake_quant(q[k], reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l],
-                          a.stats[3 * NTBC_MAX_LEVELS + l], &inside);
-      }
-    }
-    v[m] = fmaf(w[0], q[0], fmaf(w[1], q[1], fmaf(w[2], q[2], w[3] * q[3])));
+    fsample<1>(a, c / a.F, c % a.F, bx, by, v + m);
   }
 }
 
@@ -2301,8 +2307,11 @@ FeatArgs feat_args(const Shape& s, const float* grid, const int* stats, const in
   f.F = s.n_features;
   f.blocks_w = s.blocks_w;
   f.blocks_h = s.blocks_h;
-  f.shift_x = pow2_shift(s, s.blocks_w);
-  f.shift_y = pow2_shift(s, s.blocks_h);
+  while ((1 << f.f_shift) < s.n_features) ++f.f_shift;
+  f.kind_x = corner_kind(s, s.blocks_w);
+  f.kind_y = corner_kind(s, s.blocks_h);
+  f.inv_x = 1.0f / (2.0f * (float)s.blocks_w);
+  f.inv_y = 1.0f / (2.0f * (float)s.blocks_h);
   for (int l = 0; l <= s.n_levels; ++l) f.level_offset[l] = s.level_offset[l];
   f.x = x;
   return f;
@@ -2775,8 +2784,10 @@ int fused_forward(Ctx& c, const FusedPlan& f, const float* grid, const float* we
   a.F = s.n_features;
   a.blocks_w = s.blocks_w;
   a.blocks_h = s.blocks_h;
-  a.shift_x = pow2_shift(s, s.blocks_w);
-  a.shift_y = pow2_shift(s, s.blocks_h);
+  a.kind_x = corner_kind(s, s.blocks_w);
+  a.kind_y = corner_kind(s, s.blocks_h);
+  a.inv_x = 1.0f / (2.0f * (float)s.blocks_w);
+  a.inv_y = 1.0f / (2.0f * (float)s.blocks_h);
   a.in_dim = s.in_dim;
   for (int i = 0; i <= s.n_levels; ++i) a.level_offset[i] = s.level_offset[i];
   a.wpack = pk.pack;
@@ -3247,9 +3258,10 @@ __global__ void k_texel_ids(const int32_t* __restrict__ ids, int64_t n, int bloc
 __global__ void k_fa_heads(float* __restrict__ heads, float* __restrict__ ye, float* __restrict__ yc, int64_t n,
                            int E, int C, int split) {
   const int H = E + 16 * C;
+  const bool small = n * H <= 0x7fffffff;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * H; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t p = e / H;
-    const int k = (int)(e - p * H);
+    int k;
+    const int64_t p = div_mod(e, H, small, &k);
     float* part = k < E ? ye + p * E + k : yc + p * 16 * C + (k - E);
     if (split) *part = heads[e];
     else heads[e] = *part;
