@@ -367,7 +367,7 @@ __global__ void __launch_bounds__(kBlock) k_scatter_texels(FeatArgs a, const flo
 // Levels [0, n_coarse) (their gradient fits in LDS): every block accumulates a contiguous share of the
 // batch in LDS and writes its sums to its own row of `part` ([gridDim.x][nv]); k_scatter_reduce then
 // adds the rows in block order.  No global atomics, and the sum does not depend on the schedule.
-constexpr int kCoarseBlocks = 512;
+constexpr int kCoarseBlocks = 512;  // at most (rows of the workspace)
 constexpr int kCoarseThreads = 1024;  // sixteen waves share a block's LDS sums: two blocks fill a CU
 constexpr int kCoarseLds = 48 * 1024;
 
@@ -2207,8 +2207,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   }
 }
 
-// dW (and db) += the sum of the partial tiles over the K ranges, in K-range order (= with a.assign); one
-// thread per element of a tile.
+// dW (and db) += the sum of the partial TS x TS tiles over the K ranges, in K-range order (= with a.assign);
+// one thread per element of a tile.
+template <int TS>
 __global__ void __launch_bounds__(256) k_train_dw_reduce(DwArgs a) {
   const int tile = blockIdx.y;
   int jb = 0;
@@ -2216,27 +2217,27 @@ __global__ void __launch_bounds__(256) k_train_dw_reduce(DwArgs a) {
   const DwJob& J = a.job[jb];
   const int lt = tile - J.tile0;
   const int tm = lt / J.tiles_n, tn = lt % J.tiles_n;
-  const float* part = a.part + (int64_t)tile * a.splits * (128 * 128);
-  const int e = blockIdx.x * 256 + threadIdx.x;  // gridDim.x = 64
-  const int r = e / 128, col = e % 128;
-  const int m = tm * 128 + r, nn = tn * 128 + col;
+  const float* part = a.part + (int64_t)tile * a.splits * (TS * TS);
+  const int e = blockIdx.x * 256 + threadIdx.x;  // gridDim.x = TS * TS / 256
+  const int r = e / TS, col = e % TS;
+  const int m = tm * TS + r, nn = tn * TS + col;
   bool bad = false;
   if (m < J.M && nn < J.N) {
     float s = 0.0f;
     // unrolled so that eight loads are in flight; the additions stay in split order
 #pragma unroll 8
-    for (int k = 0; k < a.splits; ++k) s += part[(int64_t)k * (128 * 128) + e];
+    for (int k = 0; k < a.splits; ++k) s += part[(int64_t)k * (TS * TS) + e];
     float* dst = J.c + (int64_t)m * J.N + nn;
     const float v = a.assign ? s : *dst + s;
     *dst = v;
     bad = !isfinite(v);
   }
-  if (tn == 0 && blockIdx.x == 0 && threadIdx.x < 128) {
-    const int mr = tm * 128 + threadIdx.x;
+  if (tn == 0 && blockIdx.x == 0 && threadIdx.x < TS) {
+    const int mr = tm * TS + threadIdx.x;
     if (mr < J.M) {
       float s = 0.0f;
 #pragma unroll 8
-      for (int k = 0; k < a.splits; ++k) s += a.dbpart[((int64_t)tile * a.splits + k) * 128 + threadIdx.x];
+      for (int k = 0; k < a.splits; ++k) s += a.dbpart[((int64_t)tile * a.splits + k) * TS + threadIdx.x];
       const float v = a.assign ? s : J.db[mr] + s;
       J.db[mr] = v;
       bad |= !isfinite(v);
@@ -2244,6 +2245,9 @@ __global__ void __launch_bounds__(256) k_train_dw_reduce(DwArgs a) {
   }
   if (a.flag != nullptr && __ballot(bad) != 0ull && (threadIdx.x & 63) == 0) atomicExch(a.flag, 1.0f);
 }
+
+// ------------------------------------------------------------------------------------------ FP32, chained
+#include "train_f32.h"
 
 // ------------------------------------------------------------------------------------------ batches
 __host__ __device__ __forceinline__ uint64_t splitmix_out(uint64_t z) {
@@ -2328,6 +2332,8 @@ struct Ctx {
   bool selu = false;    // SELU hidden layers (the paper's own layout) instead of ReLU
   bool texel_blocks = false;  // the positions are the 16 texels of each block in turn (texel-grid ids)
   int64_t det_off = 0;  // byte offset of the deterministic scatter's sums in the workspace
+  float* y = nullptr;   // heads and their gradient (unfused and chained FP32 paths)
+  float* dy = nullptr;
   int* stats() { return reinterpret_cast<int*>(ws + lay.stats); }
   float* act_in(int k) { return k == 0 ? ws + lay.x : ws + lay.h[k - 1]; }
 };
@@ -2424,19 +2430,24 @@ int scatter_grid(Ctx& c, const float* grid, bool qat, const int32_t* ids, const 
   // coarse levels whose gradient fits in kCoarseLds of LDS are pre-aggregated per block
   const int n_coarse = coarse_levels(s, vbytes);
   if (n_coarse > 0 && levels != 2) {
+    // two terms a thread, at least sixteen blocks: each block writes a row of up to 48 KB for the reduction to
+    // read, so 512 of them for 512 positions' 8,192 terms cost 10.9 + 8.0 us against 5.4 + 3.6 with sixteen
+    const int64_t terms = c.n * n_coarse * s.n_features;
+    const unsigned rows = (unsigned)std::min<int64_t>(
+        kCoarseBlocks, std::max(ceil_div(terms, 2 * kCoarseThreads), std::min<int64_t>(16, ceil_div(terms, 64))));
     const int64_t nv = s.level_offset[n_coarse] * s.n_features;
     const size_t lds = (size_t)nv * vbytes;
     char* part = reinterpret_cast<char*>(c.ws) + coarse_offset(s, c.n);
     if (c.det) {
-      hipLaunchKernelGGL(k_scatter_coarse<unsigned long long>, dim3(kCoarseBlocks), dim3(kCoarseThreads), lds, c.strm, fa, dx,
+      hipLaunchKernelGGL(k_scatter_coarse<unsigned long long>, dim3(rows), dim3(kCoarseThreads), lds, c.strm, fa, dx,
                          reinterpret_cast<unsigned long long*>(part), n_coarse, (const float*)scale);
       hipLaunchKernelGGL(k_scatter_reduce<unsigned long long>, dim3((unsigned)ceil_div(nv, 64)), dim3(256), 0, c.strm,
-                         reinterpret_cast<const unsigned long long*>(part), kCoarseBlocks, nv, acc);
+                         reinterpret_cast<const unsigned long long*>(part), (int)rows, nv, acc);
     } else {
-      hipLaunchKernelGGL(k_scatter_coarse<float>, dim3(kCoarseBlocks), dim3(kCoarseThreads), lds, c.strm, fa, dx,
+      hipLaunchKernelGGL(k_scatter_coarse<float>, dim3(rows), dim3(kCoarseThreads), lds, c.strm, fa, dx,
                          reinterpret_cast<float*>(part), n_coarse, (const float*)nullptr);
       hipLaunchKernelGGL(k_scatter_reduce<float>, dim3((unsigned)ceil_div(nv, 64)), dim3(256), 0, c.strm,
-                         reinterpret_cast<const float*>(part), kCoarseBlocks, nv, d_grid);
+                         reinterpret_cast<const float*>(part), (int)rows, nv, d_grid);
     }
   }
   // texel blocks: per-block sums when no fine level is finer than the texel grid
@@ -2470,7 +2481,7 @@ int scatter_grid(Ctx& c, const float* grid, bool qat, const int32_t* ids, const 
 int backward(Ctx& c, const float* grid, const float* weights, bool qat, const int32_t* ids, float* d_grid, float* d_weights) {
   const Shape& s = c.s;
   int st;
-  float* dz = c.ws + c.lay.dy;
+  float* dz = c.dy;
   float* bufs[2] = {c.ws + c.lay.da, c.ws + c.lay.db};
   int nb = 0;
   for (int k = s.n_layers - 1; k >= 0; --k) {
@@ -2841,6 +2852,38 @@ int side_stream(SideStream** out) {
   return NTBC_OK;
 }
 
+// The grid scatter around the weight products, which do not depend on each other: in atomic mode fork()
+// runs the coarse levels on the caller's stream and the fine levels' atomics on the side stream, and join()
+// makes the caller's stream wait for them; in deterministic mode, and for batches whose fine levels take
+// less time than the two events (below 8,192 positions), fork() runs everything on the caller's stream.
+// The side stream's lock is held from one to the other.
+class ScatterBeside {
+ public:
+  int fork(Ctx& c, const float* grid, bool qat, const int32_t* ids, const float* dx, float* d_grid) {
+    if (c.det || c.n < 8192) return scatter_grid(c, grid, qat, ids, dx, d_grid);
+    int st = side_stream(&side_);
+    if (st != NTBC_OK) return st;
+    hold_ = std::unique_lock<std::mutex>(side_->lock);
+    st = scatter_grid(c, grid, qat, ids, dx, d_grid, 1);
+    NTBC_HIP(hipEventRecord(side_->fork, c.strm));
+    NTBC_HIP(hipStreamWaitEvent(side_->s, side_->fork, 0));
+    Ctx cs = c;
+    cs.strm = side_->s;
+    if (st == NTBC_OK) st = scatter_grid(cs, grid, qat, ids, dx, d_grid, 2);
+    NTBC_HIP(hipEventRecord(side_->join, side_->s));
+    if (st != NTBC_OK) NTBC_HIP(hipStreamWaitEvent(c.strm, side_->join, 0));
+    return st;
+  }
+  int join(Ctx& c, int st) {
+    if (side_) NTBC_HIP(hipStreamWaitEvent(c.strm, side_->join, 0));
+    return st;
+  }
+
+ private:
+  SideStream* side_ = nullptr;
+  std::unique_lock<std::mutex> hold_;
+};
+
 // Backward of the batch from dZ of the head ([n][dz_ld]); the forward's workspace contents must be
 // current.  ADDS the gradients to d_grid and to d_weights, or writes d_weights (assign_dw; then dw_flag,
 // when set, becomes 1 if a weight gradient is not finite).  The fine levels' grid scatter (FP32 atomics from
@@ -2874,29 +2917,9 @@ int fused_backward(Ctx& c, const FusedPlan& f, const float* grid, bool qat, cons
   hipLaunchKernelGGL(bk, dim3((unsigned)(l.bpad / kFPos)), dim3(64 * kFW), lds, c.strm, b);
   int st = check_launch("k_train_bwd");
   if (st != NTBC_OK) return st;
-  SideStream* side = nullptr;
-  if (!c.det) {
-    st = side_stream(&side);
-    if (st != NTBC_OK) return st;
-  }
-  std::unique_lock<std::mutex> hold;
-  if (side) {
-    hold = std::unique_lock<std::mutex>(side->lock);
-    st = scatter_grid(c, grid, qat, ids, b.dx, d_grid, 1);
-    NTBC_HIP(hipEventRecord(side->fork, c.strm));
-    NTBC_HIP(hipStreamWaitEvent(side->s, side->fork, 0));
-    Ctx cs = c;
-    cs.strm = side->s;
-    if (st == NTBC_OK) st = scatter_grid(cs, grid, qat, ids, b.dx, d_grid, 2);
-    NTBC_HIP(hipEventRecord(side->join, side->s));
-    if (st != NTBC_OK) {
-      NTBC_HIP(hipStreamWaitEvent(c.strm, side->join, 0));
-      return st;
-    }
-  } else {
-    st = scatter_grid(c, grid, qat, ids, b.dx, d_grid);
-    if (st != NTBC_OK) return st;
-  }
+  ScatterBeside beside;
+  st = beside.fork(c, grid, qat, ids, b.dx, d_grid);
+  if (st != NTBC_OK) return st;
   DwArgs d{};
   const uint16_t* xt = reinterpret_cast<const uint16_t*>(ws + l.xt);
   const uint16_t* ht = reinterpret_cast<const uint16_t*>(ws + l.ht);
@@ -2928,12 +2951,236 @@ int fused_backward(Ctx& c, const FusedPlan& f, const float* grid, bool qat, cons
   hipLaunchKernelGGL(k_train_dw, dim3((unsigned)(d.n_tiles * d.splits)), dim3(256), 0, c.strm, d);
   st = check_launch("k_train_dw");
   if (st == NTBC_OK) {
-    hipLaunchKernelGGL(k_train_dw_reduce, dim3(64, (unsigned)d.n_tiles), dim3(256), 0, c.strm, d);
+    hipLaunchKernelGGL(k_train_dw_reduce<128>, dim3(64, (unsigned)d.n_tiles), dim3(256), 0, c.strm, d);
     st = check_launch("k_train_dw_reduce");
   }
-  // the caller's stream waits for the scatter
-  if (side) NTBC_HIP(hipStreamWaitEvent(c.strm, side->join, 0));
-  return st;
+  return beside.join(c, st);
+}
+
+// ------------------------------------------------------------------------------------------ FP32, chained: host
+struct F32Plan {
+  int groups, head_tiles;  // 16-input groups of the first layer, 16-row tiles of the head
+  F32PackArgs pk;
+  F32Chunks fct, bct;
+  int pack_units, n_bias;
+};
+
+// The shapes that k_f32_fwd and k_f32_bwd take; others go through k_gemm layer by layer.
+bool f32_plan(const Shape& s, bool selu, F32Plan* fp) {
+  if ((s.hidden != 64 && s.hidden != 128 && s.hidden != 256) || s.in_dim > 16 * kF32Groups || s.head_dim > 16 * kF32HeadTiles ||
+      (selu && (s.hidden != 64 || s.in_dim > 16)))
+    return false;
+  F32Plan& f = *fp;
+  f = F32Plan{};
+  f.groups = (s.in_dim + 15) / 16;
+  f.head_tiles = (s.head_dim + 15) / 16;
+  F32PackArgs& a = f.pk;
+  a.n_layers = s.n_layers;
+  const int hq = s.hidden / 16;
+  for (int k = 0; k < s.n_layers; ++k) {
+    const bool head = k == s.n_layers - 1;
+    a.in_dim[k] = s.layer_in[k];
+    a.out_dim[k] = s.layer_out[k];
+    a.w_off[k] = s.w_off[k];
+    a.b_off[k] = s.b_off[k];
+    a.f_tiles[k] = a.b_groups[k] = head ? f.head_tiles : hq;
+    a.f_groups[k] = a.b_tiles[k] = k == 0 ? f.groups : hq;
+    a.f_off[k] = f.pack_units;
+    f.pack_units += a.f_tiles[k] * a.f_groups[k] * 64;
+    a.b_off2[k] = f.pack_units;
+    f.pack_units += a.b_tiles[k] * a.b_groups[k] * 64;
+    a.bias_off[k] = f.n_bias;
+    f.n_bias += 16 * a.f_tiles[k];
+  }
+  const int ct = s.hidden == 256 ? 1 : 2;
+  auto add = [&](F32Chunks& c, int src, int tiles, int groups) {
+    for (int t = 0; t < tiles; t += ct) {
+      c.src[c.n] = src + t * groups * 64;
+      c.len[c.n] = std::min(ct, tiles - t) * groups * 64;
+      c.cap = std::max(c.cap, c.len[c.n]);
+      ++c.n;
+    }
+  };
+  for (int k = 0; k < s.n_layers; ++k) add(f.fct, a.f_off[k], a.f_tiles[k], a.f_groups[k]);
+  for (int k = s.n_layers - 1; k >= 0; --k) add(f.bct, a.b_off2[k], a.b_tiles[k], a.b_groups[k]);
+  return true;
+}
+
+static_assert(kF32MaxChunks >= (kFMaxLayers - 1) * 16 + kF32HeadTiles, "chunk table of the deepest network");
+
+struct F32Layout {
+  int64_t pack, bias, x, h[kFMaxLayers - 1], dh[kFMaxLayers - 1], y, dy, dx, part, dbpart, total;  // byte offsets
+  int splits, k_split, n_tiles;
+};
+
+F32Layout f32_layout(const Shape& s, const F32Plan& f, int64_t batch) {
+  F32Layout l{};
+  int64_t o = 1024;  // after the QAT statistics at the start of the workspace
+  auto take = [&](int64_t bytes) {
+    const int64_t r = o;
+    o += (bytes + 255) / 256 * 256;
+    return r;
+  };
+  const int64_t n = std::max<int64_t>(batch, 1);
+  l.pack = take((int64_t)f.pack_units * 16);
+  l.bias = take((int64_t)f.n_bias * 4);
+  l.x = take(n * s.in_dim * 4);
+  for (int k = 0; k < s.n_hidden; ++k) l.h[k] = take(n * s.hidden * 4);
+  for (int k = 0; k < s.n_hidden; ++k) l.dh[k] = take(n * s.hidden * 4);
+  l.y = take(n * s.head_dim * 4);
+  l.dy = take(n * s.head_dim * 4);
+  l.dx = take(n * s.in_dim * 4);
+  for (int k = 0; k < s.n_layers; ++k)
+    l.n_tiles += (int)(ceil_div(s.layer_out[k], kF32DwTile) * ceil_div(s.layer_in[k], kF32DwTile));
+  // about three workgroups a CU, of at least 64 positions each
+  const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(ceil_div(768, l.n_tiles), n / 64));
+  l.k_split = (int)(ceil_div(ceil_div(n, splits), kF32DwK) * kF32DwK);
+  l.splits = (int)ceil_div(n, l.k_split);
+  // (room for the ranges before rounding, so that a larger batch never needs a smaller workspace)
+  l.part = take((int64_t)l.n_tiles * splits * kF32DwTile * kF32DwTile * 4);
+  l.dbpart = take((int64_t)l.n_tiles * splits * kF32DwTile * 4);
+  l.total = o;
+  return l;
+}
+
+typedef void (*F32Fwd)(F32FwdArgs);
+typedef void (*F32Bwd)(F32BwdArgs);
+
+template <int H>
+void f32_kernels_of(int groups, F32Fwd* fk, F32Bwd* bk) {
+  switch (groups) {
+    case 1: *fk = k_f32_fwd<H, 1, false>, *bk = k_f32_bwd<H, 1, false>; break;
+    case 2: *fk = k_f32_fwd<H, 2, false>, *bk = k_f32_bwd<H, 2, false>; break;
+    case 3: *fk = k_f32_fwd<H, 3, false>, *bk = k_f32_bwd<H, 3, false>; break;
+    default: *fk = k_f32_fwd<H, 4, false>, *bk = k_f32_bwd<H, 4, false>; break;
+  }
+}
+
+void f32_kernels(int hid, int groups, bool selu, F32Fwd* fk, F32Bwd* bk) {
+  if (selu) *fk = k_f32_fwd<64, 1, true>, *bk = k_f32_bwd<64, 1, true>;
+  else if (hid == 64) f32_kernels_of<64>(groups, fk, bk);
+  else if (hid == 128) f32_kernels_of<128>(groups, fk, bk);
+  else f32_kernels_of<256>(groups, fk, bk);
+}
+
+// Forward of the batch: features, then heads into y ([n][head_dim]); the layer inputs stay in the workspace
+// for f32_backward.  zero_losses: five floats the pack kernel zeroes on the way.
+int f32_forward(Ctx& c, const F32Plan& f, const float* grid, const float* weights, bool qat, const int32_t* ids, float* y,
+                float* zero_losses = nullptr) {
+  const Shape& s = c.s;
+  const F32Layout l = f32_layout(s, f, c.n);
+  char* ws = reinterpret_cast<char*>(c.ws);
+  int st;
+  if (qat) {
+    st = qat_range(s, grid, c.stats(), c.strm);
+    if (st != NTBC_OK) return st;
+  }
+  F32PackArgs pk = f.pk;
+  pk.w = weights;
+  pk.pack = reinterpret_cast<u32x4*>(ws + l.pack);
+  pk.bias = reinterpret_cast<float*>(ws + l.bias);
+  pk.zero5 = zero_losses;
+  hipLaunchKernelGGL(k_pack_f32t, dim3(16, 2 * s.n_layers), dim3(256), 0, c.strm, pk);
+  const FeatArgs fa = feat_args(s, grid, qat ? c.stats() : nullptr, ids, c.n, reinterpret_cast<float*>(ws + l.x));
+  hipLaunchKernelGGL(k_features, dim3((unsigned)ceil_div(c.n * s.n_levels * s.n_features, kBlock)), dim3(kBlock), 0, c.strm, fa);
+  st = check_launch("k_features");
+  if (st != NTBC_OK) return st;
+  F32FwdArgs a{};
+  a.x = fa.x;
+  a.in_dim = s.in_dim;
+  a.n_layers = s.n_layers;
+  a.head_dim = s.head_dim;
+  a.head_tiles = f.head_tiles;
+  a.n = c.n;
+  a.wpack = pk.pack;
+  a.bias = pk.bias;
+  for (int k = 0; k < s.n_layers; ++k) a.bias_off[k] = pk.bias_off[k];
+  a.n_bias = f.n_bias;
+  for (int k = 0; k < s.n_hidden; ++k) a.h[k] = reinterpret_cast<float*>(ws + l.h[k]);
+  a.y = y;
+  a.ct = f.fct;
+  F32Fwd fk;
+  F32Bwd bk;
+  f32_kernels(s.hidden, f.groups, c.selu, &fk, &bk);
+  const size_t lds = (size_t)2 * f.fct.cap * 16 + (size_t)f.n_bias * 4;
+  NTBC_HIP(hipFuncSetAttribute((const void*)fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(fk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, a);
+  return check_launch("k_f32_fwd");
+}
+
+// Backward of the batch from dZ of the head in c.dy ([n][head_dim]); the forward's workspace contents must be
+// current.  ADDS to d_grid and d_weights, or writes d_weights (assign_dw; then dw_flag, when set, becomes 1
+// if a weight gradient is not finite).
+int f32_backward(Ctx& c, const F32Plan& f, const float* grid, bool qat, const int32_t* ids, float* d_grid, float* d_weights,
+                 bool assign_dw = false, float* dw_flag = nullptr) {
+  const Shape& s = c.s;
+  const F32Layout l = f32_layout(s, f, c.n);
+  char* ws = reinterpret_cast<char*>(c.ws);
+  F32BwdArgs b{};
+  b.dz = c.dy;
+  b.in_dim = s.in_dim;
+  b.n_layers = s.n_layers;
+  b.head_dim = s.head_dim;
+  b.head_tiles = f.head_tiles;
+  b.n = c.n;
+  b.wpack = reinterpret_cast<const u32x4*>(ws + l.pack);
+  for (int k = 0; k < s.n_hidden; ++k) {
+    b.h[k] = reinterpret_cast<const float*>(ws + l.h[k]);
+    b.dh[k] = reinterpret_cast<float*>(ws + l.dh[k]);
+  }
+  b.dx = reinterpret_cast<float*>(ws + l.dx);
+  b.ct = f.bct;
+  F32Fwd fk;
+  F32Bwd bk;
+  f32_kernels(s.hidden, f.groups, c.selu, &fk, &bk);
+  const size_t lds = (size_t)2 * f.bct.cap * 16;
+  NTBC_HIP(hipFuncSetAttribute((const void*)bk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(bk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, b);
+  int st = check_launch("k_f32_bwd");
+  if (st != NTBC_OK) return st;
+  ScatterBeside beside;
+  st = beside.fork(c, grid, qat, ids, b.dx, d_grid);
+  if (st != NTBC_OK) return st;
+  F32DwArgs d{};
+  DwArgs r{};
+  int tile0 = 0;
+  for (int k = 0; k < s.n_layers; ++k) {
+    F32DwJob& J = d.job[k];
+    J.a = k == s.n_layers - 1 ? b.dz : b.dh[k];
+    J.b = k == 0 ? reinterpret_cast<const float*>(ws + l.x) : b.h[k - 1];
+    J.M = r.job[k].M = s.layer_out[k];
+    J.N = r.job[k].N = s.layer_in[k];
+    J.tiles_n = r.job[k].tiles_n = (int)ceil_div(J.N, kF32DwTile);
+    J.tile0 = r.job[k].tile0 = tile0;
+    tile0 += (int)ceil_div(J.M, kF32DwTile) * J.tiles_n;
+    r.job[k].c = d_weights + s.w_off[k];
+    r.job[k].db = d_weights + s.b_off[k];
+  }
+  d.n_jobs = r.n_jobs = s.n_layers;
+  d.n_tiles = r.n_tiles = tile0;
+  d.splits = r.splits = l.splits;
+  d.k_split = l.k_split;
+  d.n = c.n;
+  d.part = r.part = reinterpret_cast<float*>(ws + l.part);
+  d.dbpart = r.dbpart = reinterpret_cast<float*>(ws + l.dbpart);
+  r.assign = assign_dw ? 1 : 0;
+  r.flag = dw_flag;
+  hipLaunchKernelGGL(k_f32_dw, dim3((unsigned)(d.n_tiles * d.splits)), dim3(256), 0, c.strm, d);
+  hipLaunchKernelGGL(k_train_dw_reduce<kF32DwTile>, dim3(kF32DwTile * kF32DwTile / 256, (unsigned)d.n_tiles), dim3(256), 0,
+                     c.strm, r);
+  return beside.join(c, check_launch("k_f32_dw"));
+}
+
+// Where the heads and their gradient of the FP32 path (or the layer-by-layer one) live.
+void place_heads(Ctx& c, const F32Plan* f) {
+  if (f) {
+    const F32Layout l = f32_layout(c.s, *f, c.n);
+    c.y = reinterpret_cast<float*>(reinterpret_cast<char*>(c.ws) + l.y);
+    c.dy = reinterpret_cast<float*>(reinterpret_cast<char*>(c.ws) + l.dy);
+  } else {
+    c.y = c.ws + c.lay.y;
+    c.dy = c.ws + c.lay.dy;
+  }
 }
 
 // dZ = dY * Y (1 - Y) with row strides (ntbc_backward: d_heads [n][head_dim], heads [n][y_ld]).
@@ -2948,11 +3195,13 @@ __global__ void k_dsigmoid_ld(const float* __restrict__ dy, int ld_dy, const flo
 }
 
 
-// Byte offset of the deterministic scatter's region (after the unfused and fused layouts).
+// Byte offset of the deterministic scatter's region (after the layouts of the three paths).
 int64_t det_offset(const Shape& s, int64_t batch) {
   int64_t bytes = train_layout(s, batch).total * (int64_t)sizeof(float);
   FusedPlan f;
   if (fused_plan(s, &f)) bytes = std::max(bytes, fused_layout(s, f, batch).total);
+  F32Plan p;
+  if (f32_plan(s, false, &p)) bytes = std::max(bytes, f32_layout(s, p, batch).total);
   return (bytes + 255) / 256 * 256;
 }
 
@@ -2965,7 +3214,7 @@ int64_t coarse_offset(const Shape& s, int64_t batch) {
 }  // namespace
 
 namespace ntbc {
-// The unfused and fused layouts share the workspace; the deterministic scatter's 64-bit sums and the
+// The layouts of the three paths share the workspace; the deterministic scatter's 64-bit sums and the
 // coarse scatter's per-block sums follow.
 int64_t train_workspace_bytes(const Shape& s, int64_t batch) {
   return coarse_offset(s, batch) + (int64_t)kCoarseBlocks * kCoarseLds;
@@ -2984,6 +3233,8 @@ extern "C" int ntbc_forward(const ntbc_model_desc* d, const float* grid, const f
   c.strm = as_stream(stream);
   FusedPlan f;
   if (c.bf16 && fused_plan(c.s, &f)) return fused_forward(c, f, grid, weights, qat != 0, ids, heads_out, c.s.head_dim);
+  F32Plan p;
+  if (!c.bf16 && f32_plan(c.s, false, &p)) return f32_forward(c, p, grid, weights, qat != 0, ids, heads_out);
   return forward(c, grid, weights, qat != 0, ids, heads_out);
 }
 
@@ -3011,15 +3262,18 @@ extern "C" int ntbc_backward(const ntbc_model_desc* d, const float* grid, const 
     if (st != NTBC_OK) return st;
     return fused_backward(c, f, grid, qat != 0, ids, dz, kFHeadLd, d_grid, d_weights);
   }
-  float* y = c.ws + c.lay.y;
-  st = forward(c, grid, weights, qat != 0, ids, y);
+  F32Plan p;
+  const bool chained = !c.bf16 && f32_plan(c.s, false, &p);
+  place_heads(c, chained ? &p : nullptr);
+  st = chained ? f32_forward(c, p, grid, weights, qat != 0, ids, c.y) : forward(c, grid, weights, qat != 0, ids, c.y);
   if (st != NTBC_OK) return st;
   const int64_t ny = c.n * c.s.head_dim;
-  hipLaunchKernelGGL(k_dsigmoid, dim3((unsigned)std::min<int64_t>(ceil_div(ny, 256), 4096)), dim3(256), 0, c.strm, d_heads, y,
-                     c.ws + c.lay.dy, ny);
+  hipLaunchKernelGGL(k_dsigmoid, dim3((unsigned)std::min<int64_t>(ceil_div(ny, 256), 4096)), dim3(256), 0, c.strm, d_heads, c.y,
+                     c.dy, ny);
   st = check_launch("k_dsigmoid");
   if (st != NTBC_OK) return st;
-  return backward(c, grid, weights, qat != 0, ids, d_grid, d_weights);
+  return chained ? f32_backward(c, p, grid, qat != 0, ids, d_grid, d_weights)
+                 : backward(c, grid, weights, qat != 0, ids, d_grid, d_weights);
 }
 
 extern "C" int ntbc_loss_grad(const ntbc_model_desc* d, const ntbc_targets* t, const float* heads, const int32_t* ids,
@@ -3099,20 +3353,25 @@ extern "C" int ntbc_train_step(const ntbc_model_desc* d, const ntbc_train_state*
                         losses_out + 4);
     if (st != NTBC_OK) return st;
   } else {
-    float* y = c.ws + c.lay.y;
-    st = forward(c, tsd->grid, tsd->weights, qat, batch_ids, y);
+    F32Plan p;
+    const bool chained = !c.bf16 && f32_plan(s, false, &p);
+    place_heads(c, chained ? &p : nullptr);
+    st = chained ? f32_forward(c, p, tsd->grid, tsd->weights, qat, batch_ids, c.y, losses_out)
+                 : forward(c, tsd->grid, tsd->weights, qat, batch_ids, c.y);
     if (st != NTBC_OK) return st;
     // dL/dZ of the head pre-activations straight from the loss kernel (the sigmoid derivative fused)
-    st = s.naive ? naive_loss_grad(s, t, y, batch_ids, c.n, stage, losses_out, c.ws + c.lay.dy, c.strm, true)
-                 : loss_grad(s, t, y, batch_ids, c.n, h->temperature, h->loss_weights, losses_out, c.ws + c.lay.dy,
-                             c.strm, true);
+    st = s.naive ? naive_loss_grad(s, t, c.y, batch_ids, c.n, stage, losses_out, c.dy, c.strm, true, 0, chained)
+                 : loss_grad(s, t, c.y, batch_ids, c.n, h->temperature, h->loss_weights, losses_out, c.dy, c.strm, true, 0,
+                             chained);
     if (st != NTBC_OK) return st;
     st = fill(tsd->d_grid, ng, 0.0f, c.strm);
-    if (st == NTBC_OK) st = fill(tsd->d_weights, s.n_weights, 0.0f, c.strm);
+    if (st == NTBC_OK && !chained) st = fill(tsd->d_weights, s.n_weights, 0.0f, c.strm);
     if (st != NTBC_OK) return st;
-    st = backward(c, tsd->grid, tsd->weights, qat, batch_ids, tsd->d_grid, tsd->d_weights);
+    // (the chained path's weight products write d_weights and flag a non-finite one)
+    st = chained ? f32_backward(c, p, tsd->grid, qat, batch_ids, tsd->d_grid, tsd->d_weights, true, losses_out + 4)
+                 : backward(c, tsd->grid, tsd->weights, qat, batch_ids, tsd->d_grid, tsd->d_weights);
     if (st != NTBC_OK) return st;
-    hipLaunchKernelGGL(k_check_finite, dim3((unsigned)std::min<int64_t>(ceil_div(s.n_weights, 256), 1024)), dim3(256),
+    if (!chained) hipLaunchKernelGGL(k_check_finite, dim3((unsigned)std::min<int64_t>(ceil_div(s.n_weights, 256), 1024)), dim3(256),
                        0, c.strm, tsd->d_weights, s.n_weights, losses_out + 4);
   }
   // learning rates of this step: linear warm-up, then cosine annealing to 0
@@ -3233,7 +3492,28 @@ Ctx faithful_ctx(const Shape& s, int64_t n, char* ws, hipStream_t strm, bool det
   c.det = det;
   c.det_off = det_offset(s, n);
   c.selu = true;
+  F32Plan p;
+  place_heads(c, f32_plan(s, true, &p) ? &p : nullptr);
   return c;
+}
+
+// Forward and backward of one of the two networks: chained where its shape allows (at most 16 inputs), layer
+// by layer otherwise.
+int faithful_forward(Ctx& c, const float* grid, const float* weights, bool qat, const int32_t* ids) {
+  F32Plan p;
+  return f32_plan(c.s, true, &p) ? f32_forward(c, p, grid, weights, qat, ids, c.y) : forward(c, grid, weights, qat, ids, c.y);
+}
+
+int faithful_backward(Ctx& c, const float* grid, const float* weights, bool qat, const int32_t* ids, float* d_grid,
+                      float* d_weights, float* flag) {
+  F32Plan p;
+  if (f32_plan(c.s, true, &p)) return f32_backward(c, p, grid, qat, ids, d_grid, d_weights, true, flag);
+  int st = fill(d_weights, c.s.n_weights, 0.0f, c.strm);
+  if (st == NTBC_OK) st = backward(c, grid, weights, qat, ids, d_grid, d_weights);
+  if (st != NTBC_OK) return st;
+  hipLaunchKernelGGL(k_check_finite, dim3((unsigned)std::min<int64_t>(ceil_div(c.s.n_weights, 256), 1024)), dim3(256), 0, c.strm,
+                     d_weights, c.s.n_weights, flag);
+  return check_launch("k_check_finite");
 }
 
 Ctx faithful_colour_ctx(const Shape& s, int64_t n, char* ws, hipStream_t strm, bool det) {
@@ -3318,34 +3598,27 @@ extern "C" int ntbc_faithful_train_step(const ntbc_faithful_desc* d, const ntbc_
   int32_t* tids = reinterpret_cast<int32_t*>(ws + l.tids);
   float* heads = reinterpret_cast<float*>(ws + l.heads);
   float* dheads = reinterpret_cast<float*>(ws + l.dheads);
-  float* ye = ce.ws + ce.lay.y;
-  float* yc = cc.ws + cc.lay.y;
   const int E = loss.endpoint_dim, C = loss.channels;
   const unsigned hb = (unsigned)std::min<int64_t>(ceil_div((int64_t)batch * loss.head_dim, 256), 4096);
   hipLaunchKernelGGL(k_texel_ids, dim3((unsigned)std::min<int64_t>(ceil_div(16 * (int64_t)batch, 256), 4096)), dim3(256),
                      0, strm, batch_ids, (int64_t)batch, loss.blocks_w, loss.n_positions, tids);
   st = check_launch("k_texel_ids");
-  if (st == NTBC_OK) st = forward(ce, tsd->ep_grid, tsd->ep_weights, qat, batch_ids, ye);
-  if (st == NTBC_OK) st = forward(cc, tsd->col_grid, tsd->col_weights, qat, tids, yc);
+  if (st == NTBC_OK) st = faithful_forward(ce, tsd->ep_grid, tsd->ep_weights, qat, batch_ids);
+  if (st == NTBC_OK) st = faithful_forward(cc, tsd->col_grid, tsd->col_weights, qat, tids);
   if (st != NTBC_OK) return st;
-  hipLaunchKernelGGL(k_fa_heads, dim3(hb), dim3(256), 0, strm, heads, ye, yc, (int64_t)batch, E, C, 0);
+  hipLaunchKernelGGL(k_fa_heads, dim3(hb), dim3(256), 0, strm, heads, ce.y, cc.y, (int64_t)batch, E, C, 0);
   // dL/dZ of the output pre-activations of both networks, in the head layout, then split
   st = loss_grad(loss, t, heads, batch_ids, batch, h->temperature, h->loss_weights, losses_out, dheads, strm, true);
   if (st != NTBC_OK) return st;
-  hipLaunchKernelGGL(k_fa_heads, dim3(hb), dim3(256), 0, strm, dheads, ce.ws + ce.lay.dy, cc.ws + cc.lay.dy,
-                     (int64_t)batch, E, C, 1);
+  hipLaunchKernelGGL(k_fa_heads, dim3(hb), dim3(256), 0, strm, dheads, ce.dy, cc.dy, (int64_t)batch, E, C, 1);
   const int64_t nge = ep.grid_vertices * 2, ngc = col.grid_vertices * 2;
   st = fill(tsd->d_ep_grid, nge, 0.0f, strm);
   if (st == NTBC_OK) st = fill(tsd->d_col_grid, ngc, 0.0f, strm);
-  if (st == NTBC_OK) st = fill(tsd->d_ep_weights, ep.n_weights, 0.0f, strm);
-  if (st == NTBC_OK) st = fill(tsd->d_col_weights, col.n_weights, 0.0f, strm);
-  if (st == NTBC_OK) st = backward(ce, tsd->ep_grid, tsd->ep_weights, qat, batch_ids, tsd->d_ep_grid, tsd->d_ep_weights);
-  if (st == NTBC_OK) st = backward(cc, tsd->col_grid, tsd->col_weights, qat, tids, tsd->d_col_grid, tsd->d_col_weights);
+  if (st == NTBC_OK)
+    st = faithful_backward(ce, tsd->ep_grid, tsd->ep_weights, qat, batch_ids, tsd->d_ep_grid, tsd->d_ep_weights, losses_out + 4);
+  if (st == NTBC_OK)
+    st = faithful_backward(cc, tsd->col_grid, tsd->col_weights, qat, tids, tsd->d_col_grid, tsd->d_col_weights, losses_out + 4);
   if (st != NTBC_OK) return st;
-  hipLaunchKernelGGL(k_check_finite, dim3((unsigned)std::min<int64_t>(ceil_div(ep.n_weights, 256), 1024)), dim3(256), 0,
-                     strm, tsd->d_ep_weights, ep.n_weights, losses_out + 4);
-  hipLaunchKernelGGL(k_check_finite, dim3((unsigned)std::min<int64_t>(ceil_div(col.n_weights, 256), 1024)), dim3(256), 0,
-                     strm, tsd->d_col_weights, col.n_weights, losses_out + 4);
   const double tt = (double)step + 1.0;
   AdamArgs aa{};
   aa.b1 = h->beta1;
