@@ -243,7 +243,7 @@ int ntbc_batch_pack(const void* table, void* workspace, size_t workspace_bytes, 
 /* The kernel instances of a plan (one launch each): n_groups receives their count and, when groups_out
  * is not NULL, groups_out[8 g .. 8 g + 7] = precision, hidden width, first-layer K-steps, unrolled
  * middle layers (-1: a run-time count), BC1 and BC4 textures of the register epilogue (-1: heads staged
- * in LDS), tile waves, items, for g < min(*n_groups, max_groups).  Host only. */
+ * in LDS; -2, 0: any mix), tile waves, items, for g < min(*n_groups, max_groups).  Host only. */
 int ntbc_batch_groups(const void* table, int32_t* groups_out, int32_t max_groups, int32_t* n_groups);
 
 /* Tile shape of one kernel instance of a plan: `waves` (2, 4 or 8) waves of 32 block positions per

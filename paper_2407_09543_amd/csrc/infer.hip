@@ -22,6 +22,7 @@
 // contiguous 16-byte (16-bit formats) or 4-byte (FP32) load; the copy is made by k_pack_lp / k_pack_f32
 // unless the caller says it is current.
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -129,6 +130,8 @@ struct PackArgs {
   int16_t head_src[kHeadRows];   // head_perm: canonical head neuron of packed row r, -1 = zero row
 };
 
+constexpr int kRegSlots = 10;  // textures or colour channels that a register epilogue takes
+
 struct InferArgs {
   dev::GridView grid;
   const void* wpack;            // packed A operands
@@ -149,7 +152,10 @@ struct InferArgs {
   unsigned* amax;               // calibration: per layer, max |layer input| as float bits
   // register-resident BC epilogue: texture k of the slot layout (BC1 textures first, then BC4) is
   // canonical texture reg_tex[k]; reg_ep / reg_ch are its endpoint and colour-channel offsets
-  int reg_tex[NTBC_MAX_TEXTURES], reg_ep[NTBC_MAX_TEXTURES], reg_ch[NTBC_MAX_TEXTURES];
+  int reg_tex[kRegSlots], reg_ep[kRegSlots], reg_ch[NTBC_MAX_TEXTURES];
+  // any-mix epilogue: reg_tex[q] is the texture whose first colour channel is q (-1: none), reg_ep / reg_ep1[q]
+  // the offset of channel q's endpoint 0 / 1
+  int reg_ep1[kRegSlots];
 };
 
 // ------------------------------------------------------------------------------ weight packing
@@ -746,6 +752,84 @@ __device__ __forceinline__ void reg_epilogue(ArgsT a, const f32x16_t (&h)[kHeadT
 #undef NTBC_SLOT
 }
 
+// The same epilogue for any mix of textures with at most kRegChannels colour channels in all: colour channel
+// q (in the texel's order) has slots 9q .. 9q+7 for its eight texels and 9q + 8 for its endpoint g, so that
+// every slot is a compile-time register and only which texture a channel belongs to is a run-time
+// (uniform) question.  9 C slots, as many head tiles as the canonical order.
+constexpr int kRegChannels = kRegSlots;
+static_assert(9 * kRegChannels <= 16 * kHeadTiles, "slots of the any-mix epilogue");
+
+template <typename ArgsT>
+__device__ __forceinline__ void reg_any_epilogue(ArgsT a, f32x16_t (&h)[kHeadTiles], const float* tab, int g, int64_t id,
+                                                 bool valid) {
+#define NTBC_SLOT(x) h[(x) / 16][(x) % 16]
+  const int partner = (((int)threadIdx.x & 63) ^ 32) << 2;
+  auto swap = [partner](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(partner, (int)v); };
+  const int64_t row = id - a.first;
+  const int channels = a.channels;
+#pragma unroll
+  for (int q = 0; q < kRegChannels; ++q) {
+    if (q >= channels) continue;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) NTBC_SLOT(9 * q + i) = sigmoid_fast(NTBC_SLOT(9 * q + i));
+  }
+#pragma unroll
+  for (int q = 0; q < kRegChannels; ++q) {
+    if (q >= channels) continue;
+    const int t = a.reg_tex[q];  // the texture whose first channel is q, -1 = none
+    if (t < 0) continue;
+    if (q + 2 < kRegChannels && a.formats[t] == NTBC_BC1) {
+      constexpr int kLast = kRegChannels - 3;
+      const int qb = q < kLast ? q : kLast;  // (q itself: keeps the slots below the last)
+      const uint32_t w = dev::rgb565(NTBC_SLOT(9 * qb + 8), NTBC_SLOT(9 * qb + 17), NTBC_SLOT(9 * qb + 26)), o = swap(w);
+      const dev::Bc1Pal p = dev::bc1_palette(g ? o : w, g ? w : o, tab);
+      uint32_t codes = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        codes |= dev::bc1_code(p, NTBC_SLOT(9 * qb + i), NTBC_SLOT(9 * qb + 9 + i), NTBC_SLOT(9 * qb + 18 + i)) << (2 * i);
+      const uint32_t hi = swap(codes);
+      if (g == 0 && valid)
+        a.out[(int64_t)t * a.n + row] = (uint64_t)p.c0 | ((uint64_t)p.c1 << 16) | ((uint64_t)(codes | (hi << 16)) << 32);
+    } else {
+      const uint32_t w = (uint32_t)dev::quant_bits(NTBC_SLOT(9 * q + 8), 255.0f), o = swap(w);
+      const dev::Bc4Pal p = dev::bc4_palette((int)(g ? o : w), (int)(g ? w : o), tab);
+      uint32_t codes = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) codes |= dev::bc4_code(p, NTBC_SLOT(9 * q + i)) << (3 * i);
+      const uint32_t hi = swap(codes);
+      if (g == 0 && valid)
+        a.out[(int64_t)t * a.n + row] =
+            (uint64_t)p.e0 | ((uint64_t)p.e1 << 8) | (((uint64_t)codes | ((uint64_t)hi << 24)) << 16);
+    }
+  }
+  if (a.heads && valid) {
+    // the lane's eight texels are one run of 8 C floats, a texel's channels in order: words of four where C
+    // reaches them
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    float* hr = a.heads + row * a.head_dim;
+    float* hc = hr + a.endpoint_dim + 8 * g * channels;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+#pragma unroll
+      for (int q = 0; q < kRegChannels; q += 4) {
+        if (q + 3 < kRegChannels && q + 3 < channels) {
+          *reinterpret_cast<f4*>(hc + i * channels + q) =
+              f4{NTBC_SLOT(9 * q + i), NTBC_SLOT(9 * (q + 1) + i), NTBC_SLOT(9 * (q + (q + 2 < kRegChannels ? 2 : 0)) + i),
+                 NTBC_SLOT(9 * (q + (q + 3 < kRegChannels ? 3 : 0)) + i)};
+        } else {
+#pragma unroll
+          for (int c = q; c < q + 4 && c < kRegChannels; ++c)
+            if (c < channels) hc[i * channels + c] = NTBC_SLOT(9 * c + i);
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kRegChannels; ++q)
+      if (q < channels) hr[g ? a.reg_ep1[q] : a.reg_ep[q]] = NTBC_SLOT(9 * q + 8);
+  }
+#undef NTBC_SLOT
+}
+
 // The head's input: the last hidden layer's operands, which FP8 mode rounds to bfloat16 separately.
 template <bool MIX, typename A, typename B>
 __device__ __forceinline__ const B& pick_head_input(const A& bin, const B& hb) {
@@ -754,6 +838,8 @@ __device__ __forceinline__ const B& pick_head_input(const A& bin, const B& hb) {
   else
     return bin;
 }
+
+constexpr int kAnyMix = -2;  // NB1 of the instances with the any-mix register epilogue
 
 // The fused network of one tile of W * 32 block positions (W waves; tile index `tile` of the range
 // a.first .. a.first + a.n).
@@ -901,6 +987,10 @@ __device__ __forceinline__ void infer_tile(ArgsT a, ChunksT ct, int64_t tile) {
     }
   }
   // sigmoid heads in registers (all lanes; the register epilogue's layout uses the first kUsed slots)
+  if constexpr (NB1 == kAnyMix) {
+    reg_any_epilogue<ArgsT>(a, hacc, tab, g, id, pos0 + j <= last);
+    return;
+  }
   constexpr int used = NB1 >= 0 ? RegLayout<NB1 < 0 ? 0 : NB1, NB4>::kUsed : 16 * kHeadTiles;
 #pragma unroll
   for (int t = 0; t < kHeadTiles; ++t) {
@@ -951,6 +1041,137 @@ k_infer_lds(InferArgs a, ChunkTable ct) {
   infer_tile<L, HID, KS0, NH, NB1, NB4>(a, ct, xcd_tile(blockIdx.x, gridDim.x));
 }
 
+// ------------------------------------------------------------------------------ 16-bit kernel, resident weights
+// Widths 64 and 128 with one or two middle layers (at most 128 KB of packed weights): the whole network is
+// copied into LDS once and the waves then run tile after tile on their own.  Streamed in chunks, these
+// networks' products (512 cycles a chunk at width 128) are shorter than the latency of the next chunk's copy,
+// so every chunk ended in a wait and a barrier.  Eight waves share a copy (one workgroup a CU, two waves a
+// SIMD by registers) and take a contiguous run of tiles; fewer waves while that gives more CUs work.
+// 1024^2, 48-128x3-162, half: 23.4 -> 23.0 us (one tile a wave);
+// 4096^2 of that network and 64 inputs, bfloat16: 446 -> 252; 256^2, 16-64x2-72: 15.1 -> 10.5.
+constexpr int kResWaves = 8;
+
+struct ResArgs {
+  int units, n_bias;      // packed weights (u32x4) and padded biases (floats)
+  int64_t tiles, per_wg;  // tiles of 32 positions, and of a workgroup
+};
+
+// The network on the wave's 32 positions from pos0: x0 = the features' operands; wl, bias_s: the packed weights
+// and biases in LDS.
+template <Lp L, int HID, int KS0, int NH>
+__device__ __forceinline__ void res_network(const InferArgs& a, const typename LpOp<L>::type (&x0)[KS0], const u32x4* wl, const float* bias_s,
+                                            const float* tab, int64_t id, bool valid, int lane) {
+  constexpr int S = HID / 16, T = HID / 32, CT = kChunkTiles;
+  static_assert(NH == 1 || NH == 2, "one or two middle layers");
+  const int g = lane >> 5;
+  u32x4 h0[S], h1[S];
+#pragma unroll
+  for (int tc = 0; tc < T / CT; ++tc) {
+    f32x16_t acc[CT];
+#pragma unroll
+    for (int u = 0; u < CT; ++u) acc[u] = acc_init<L>(bias_s + 32 * (CT * tc + u), g);
+    chunk_mfma<L, KS0, CT, KS0>(wl + CT * tc * KS0 * 64, KS0, x0, lane, CT, acc);
+#pragma unroll
+    for (int u = 0; u < CT; ++u)
+      hidden_epilogue<L>(acc[u], nullptr, g, &h0[2 * (CT * tc + u)], &h0[2 * (CT * tc + u) + 1], 1.0f, 1.0f);
+  }
+  const u32x4* w = wl + T * KS0 * 64;
+  const float* b = bias_s + HID;
+#pragma unroll
+  for (int m = 0; m < NH; ++m) {
+    const u32x4 (&in)[S] = m == 0 ? h0 : h1;
+    u32x4 (&out)[S] = m == 0 ? h1 : h0;
+#pragma unroll
+    for (int tc = 0; tc < T / CT; ++tc) {
+      f32x16_t acc[CT];
+#pragma unroll
+      for (int u = 0; u < CT; ++u) acc[u] = acc_init<L>(b + 32 * (CT * tc + u), g);
+      chunk_mfma<L, S, CT, S>(w + CT * tc * S * 64, S, in, lane, CT, acc);
+#pragma unroll
+      for (int u = 0; u < CT; ++u)
+        hidden_epilogue<L>(acc[u], nullptr, g, &out[2 * (CT * tc + u)], &out[2 * (CT * tc + u) + 1], 1.0f, 1.0f);
+    }
+    w += T * S * 64;
+    b += HID;
+  }
+  const u32x4 (&hin)[S] = NH == 1 ? h1 : h0;
+  const int nht = a.otiles[NH + 1];
+  f32x16_t hacc[kHeadTiles];
+#pragma unroll
+  for (int t = 0; t < kHeadTiles; ++t) hacc[t] = f32x16_t{};
+#pragma unroll
+  for (int tc = 0; tc < kHeadTiles / CT; ++tc) {
+    if (CT * tc >= nht) continue;
+    f32x16_t acc[CT];
+#pragma unroll
+    for (int u = 0; u < CT; ++u) acc[u] = CT * tc + u < nht ? acc_init<L>(b + 32 * (CT * tc + u), g) : f32x16_t{};
+    chunk_mfma<L, S, CT, S>(w + CT * tc * S * 64, S, hin, lane, nht - CT * tc, acc);
+#pragma unroll
+    for (int u = 0; u < CT; ++u) hacc[CT * tc + u] = acc[u];
+  }
+  reg_any_epilogue<const InferArgs&>(a, hacc, tab, g, id, valid);
+}
+
+// A workgroup's run of tiles: [t0, t1) of the range a.first .. a.first + a.n.  The arguments are read through
+// the constant address space, again for every tile (kept in scalar registers across the loop they would
+// not fit).
+typedef const __attribute__((address_space(4))) InferArgs ConstArgs;
+
+template <Lp L, int HID, int KS0, int NH>
+__device__ __forceinline__ void res_run(const ConstArgs* args, int units, int n_bias, int64_t t0, int64_t t1) {
+  const InferArgs& a = *(const InferArgs*)args;
+  extern __shared__ u32x4 smem[];
+  float* tab = reinterpret_cast<float*>(smem + units);
+  float* bias_s = tab + 256;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, waves = nt >> 6;
+  const int j = lane & 31, g = lane >> 5;
+  const u32x4* wp = reinterpret_cast<const u32x4*>(a.wpack);
+  const int wave_base = __builtin_amdgcn_readfirstlane(tid & ~63);
+  for (int r = 0; r < units; r += nt)
+    if (r + tid < units)
+      __builtin_amdgcn_global_load_lds(wp + r + tid, (__attribute__((address_space(3))) void*)(smem + r + wave_base), 16, 0, 0);
+  for (int i = tid; i < 256; i += nt) tab[i] = (float)i / 255.0f;
+  for (int i = tid; i < n_bias; i += nt) bias_s[i] = a.bias[i];
+  const int64_t last = a.first + a.n - 1;
+  bool loaded = false;
+  // every wave makes at least one round (a wave without a tile on the last position, its result dropped), so
+  // that all of them reach the barrier behind the copy
+  for (int64_t t = t0 + wave; t < t1 || !loaded; t += waves) {
+    const int64_t p = a.first + 32 * t + j;
+    const bool valid = t < t1 && p <= last;
+    const int64_t id = p <= last ? p : last;
+    int bx, by;
+    dev::block_of(id, last, a.grid.blocks_w, &bx, &by);
+    // opaque copies: nothing of the gather and no weight is hoisted out of the loop (it would not fit)
+    int gv = g;
+    uint32_t zero = 0;
+    const ConstArgs* args_t = args;
+    asm volatile("" : "+v"(gv), "+v"(zero), "+s"(args_t));
+    const InferArgs& at = *(const InferArgs*)args_t;
+    u32x4 x0[KS0];
+#pragma unroll
+    for (int s = 0; s < KS0; ++s) {
+      float v[8];
+      dev::features<8>(at.grid, 16 * s + 8 * gv, bx, by, v);
+      x0[s] = x8_of<L>(v);
+    }
+    if (!loaded) {
+      wait_dma();
+      __syncthreads();
+      loaded = true;
+    }
+    res_network<L, HID, KS0, NH>(at, x0, smem + zero, bias_s + zero, tab, id, valid, lane);
+  }
+}
+
+template <Lp L, int HID, int KS0, int NH>
+__global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(2))) k_infer_res(InferArgs a, ResArgs r) {
+  const int64_t t0 = xcd_tile(blockIdx.x, gridDim.x) * r.per_wg, t1 = t0 + r.per_wg;
+  // (the first argument starts the kernel-argument segment)
+  res_run<L, HID, KS0, NH>((const ConstArgs*)__builtin_amdgcn_kernarg_segment_ptr(), r.units, r.n_bias, t0,
+                           t1 < r.tiles ? t1 : r.tiles);
+}
+
 // ------------------------------------------------------------------------------ launch over work items
 // Many block ranges (materials, their mip levels) in one launch per kernel instance.  The items live
 // in device memory (their arguments are read through the scalar cache, and
@@ -964,6 +1185,8 @@ struct BatchItem {
   ChunkTable ct;
   int64_t tile_begin, tiles;
   int32_t index;  // position of the item in the caller's list (stamps)
+  // resident weights: packed weights (u32x4), padded biases (floats), tiles of 32 positions a workgroup takes
+  int32_t units, n_bias, per_wg;
 };
 
 template <Lp L, int HID, int KS0, int NH, int NB1, int NB4, int W>
@@ -988,6 +1211,32 @@ k_infer_lds_batch(const BatchItem* __restrict__ items, int n_items, unsigned* __
     if (threadIdx.x == 0) {
       __threadfence();
       if (atomicAdd(&done[it.index], 1u) + 1u == (unsigned)it.tiles) stamps[1 + it.index] = wall_clock64();
+    }
+  }
+}
+
+// The same with resident weights (k_infer_res): a workgroup takes it.per_wg tiles of 32 positions of its item.
+template <Lp L, int HID, int KS0, int NH>
+__global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(2)))
+k_infer_res_batch(const BatchItem* __restrict__ items, int n_items, unsigned* __restrict__ done,
+                  uint64_t* __restrict__ stamps) {
+  typedef const __attribute__((address_space(4))) BatchItem ConstItem;
+  const ConstItem* citems = (const ConstItem*)items;
+  const int64_t b = xcd_tile(blockIdx.x, gridDim.x);
+  int lo = 0, hi = n_items - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (citems[mid].tile_begin <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  const ConstItem* it = citems + lo;
+  const int64_t all = (it->a.n + 31) / 32, t0 = (b - it->tile_begin) * it->per_wg, t1 = t0 + it->per_wg;
+  res_run<L, HID, KS0, NH>((const ConstArgs*)&it->a, it->units, it->n_bias, t0, t1 < all ? t1 : all);
+  if (stamps != nullptr) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __threadfence();
+      if (atomicAdd(&done[it->index], 1u) + 1u == (unsigned)it->tiles) stamps[1 + it->index] = wall_clock64();
     }
   }
 }
@@ -1439,11 +1688,18 @@ bool batch_instance_bf16(int hid, int ks0, int nh, int nb1, int nb4, int waves, 
 bool batch_instance_fp16(int hid, int ks0, int nh, int nb1, int nb4, int waves, const void** fn, BatchLaunch* launch);
 bool batch_instance_fp8(int hid, int ks0, int nh, int nb1, int nb4, int waves, const void** fn, BatchLaunch* launch);
 bool lds_instance_f32(int hid, int kq, const void** fn, LdsLaunch* launch);
+bool res_instance_bf16(int hid, int ks0, int nh, const void** fn, LdsLaunch* launch);
+bool res_instance_fp16(int hid, int ks0, int nh, const void** fn, LdsLaunch* launch);
+bool any_instance_bf16(int ks0, int nh, const void** fn, LdsLaunch* launch);
+bool any_instance_fp16(int ks0, int nh, const void** fn, LdsLaunch* launch);
+bool res_batch_instance_bf16(int hid, int ks0, int nh, const void** fn, BatchLaunch* launch);
+bool res_batch_instance_fp16(int hid, int ks0, int nh, const void** fn, BatchLaunch* launch);
 }  // namespace ntbc
 
 // Single-range instances: every precision at widths 64/128/256 with one to four input K-steps and a
 // run-time layer count, the two-middle-layer shapes (128, 3) and (256, 4) unrolled, with the LDS-staged
-// epilogue and with the register epilogue for two BC1 + three BC4 textures.
+// epilogue and with the register epilogue for two BC1 + three BC4 textures; bfloat16 and half with one or two
+// middle layers and the any-mix register epilogue, weights resident at widths 64 and 128 and streamed at 256.
 #define NTBC_LDS_INSTANCE_L(LP, H, K, NH, NB1, NB4)                                                          \
   if (hid == H && ks0 == K && nh == NH && nb1 == NB1 && (NB1 < 0 || nb4 == NB4)) {                         \
     *fn = (const void*)k_infer_lds<LP, H, K, NH, NB1, NB4>;                                                  \
@@ -1461,11 +1717,12 @@ bool lds_instance_f32(int hid, int kq, const void** fn, LdsLaunch* launch);
   NTBC_LDS_INSTANCE_L(LP, 256, 1, -1, -1, 0) NTBC_LDS_INSTANCE_L(LP, 256, 2, -1, -1, 0)                          \
   NTBC_LDS_INSTANCE_L(LP, 256, 3, -1, -1, 0) NTBC_LDS_INSTANCE_L(LP, 256, 4, -1, -1, 0)                          \
   NTBC_LDS_INSTANCE_L(LP, 128, 3, 2, -1, 0) NTBC_LDS_INSTANCE_L(LP, 256, 4, 2, -1, 0)                            \
-  NTBC_LDS_INSTANCE_L(LP, 128, 3, 2, 2, 3) NTBC_LDS_INSTANCE_L(LP, 256, 4, 2, 2, 3)
+  NTBC_LDS_INSTANCE_L(LP, 256, 4, 2, 2, 3)
 
-// Batched instances: the same shapes with the LDS-staged epilogue in every precision, and BF16 with the
-// register epilogue for two BC1 + one to three BC4 textures at widths 64, 128 (run-time layer count)
-// and 256 (two middle layers unrolled).
+// Batched instances: the same shapes with the LDS-staged epilogue in every precision, BF16 with the register
+// epilogue for two BC1 + one to three BC4 textures at width 256 (two middle layers unrolled), and bfloat16
+// and half with the any-mix epilogue and one or two middle layers: resident weights at width 64, streamed at 128
+// and 256 with three or four input K-steps.
 #define NTBC_BATCH_INSTANCE_L(LP, H, K, NH, NB1, NB4)                                                         \
   if (hid == H && ks0 == K && nh == NH && nb1 == NB1 && (NB1 < 0 || nb4 == NB4) && waves == NTBC_BATCH_W) {   \
     *fn = (const void*)k_infer_lds_batch<LP, H, K, NH, NB1, NB4, NTBC_BATCH_W>;                              \
@@ -1483,6 +1740,11 @@ bool lds_instance_f32(int hid, int kq, const void** fn, LdsLaunch* launch);
   NTBC_BATCH_INSTANCE_L(LP, 256, 1, -1, -1, 0) NTBC_BATCH_INSTANCE_L(LP, 256, 2, -1, -1, 0)                        \
   NTBC_BATCH_INSTANCE_L(LP, 256, 3, -1, -1, 0) NTBC_BATCH_INSTANCE_L(LP, 256, 4, -1, -1, 0)                        \
   NTBC_BATCH_INSTANCE_L(LP, 128, 3, 2, -1, 0) NTBC_BATCH_INSTANCE_L(LP, 256, 4, 2, -1, 0)
+#define NTBC_BATCH_ANY(LP)                                                                                      \
+  NTBC_BATCH_INSTANCE_L(LP, 128, 3, 1, kAnyMix, 0) NTBC_BATCH_INSTANCE_L(LP, 128, 4, 1, kAnyMix, 0)             \
+  NTBC_BATCH_INSTANCE_L(LP, 128, 3, 2, kAnyMix, 0) NTBC_BATCH_INSTANCE_L(LP, 128, 4, 2, kAnyMix, 0)             \
+  NTBC_BATCH_INSTANCE_L(LP, 256, 3, 1, kAnyMix, 0) NTBC_BATCH_INSTANCE_L(LP, 256, 4, 1, kAnyMix, 0)             \
+  NTBC_BATCH_INSTANCE_L(LP, 256, 3, 2, kAnyMix, 0) NTBC_BATCH_INSTANCE_L(LP, 256, 4, 2, kAnyMix, 0)
 #define NTBC_BATCH_REG(H, K, NH)                                                                                \
   NTBC_BATCH_INSTANCE_L(Lp::BF16, H, K, NH, 2, 1) NTBC_BATCH_INSTANCE_L(Lp::BF16, H, K, NH, 2, 2)                 \
   NTBC_BATCH_INSTANCE_L(Lp::BF16, H, K, NH, 2, 3)
@@ -1503,6 +1765,7 @@ bool lds_instance_fp16(int hid, int ks0, int nh, int nb1, int nb4, const void** 
 #if NTBC_PART(3)
 bool lds_instance_fp8(int hid, int ks0, int nh, int nb1, int nb4, const void** fn, LdsLaunch* launch) {
   NTBC_LDS_INSTANCES(Lp::FP8)
+  NTBC_LDS_INSTANCE_L(Lp::FP8, 128, 3, 2, 2, 3)
   return false;
 }
 #endif
@@ -1512,7 +1775,7 @@ bool lds_instance_fp8(int hid, int ks0, int nh, int nb1, int nb4, const void** f
   bool batch_instance_bf16_w##WV(int hid, int ks0, int nh, int nb1, int nb4, int waves, const void** fn,         \
                                  BatchLaunch* launch) {                                                         \
     NTBC_BATCH_INSTANCES(Lp::BF16)                                                                              \
-    NTBC_BATCH_REG(64, 4, -1) NTBC_BATCH_REG(128, 4, -1) NTBC_BATCH_REG(256, 4, 2)                              \
+    NTBC_BATCH_REG(256, 4, 2) NTBC_BATCH_ANY(Lp::BF16)                                                          \
     return false;                                                                                               \
   }
 bool batch_instance_bf16_w2(int, int, int, int, int, int, const void**, BatchLaunch*);
@@ -1542,6 +1805,7 @@ NTBC_BATCH_BF16_W(8)
 #if NTBC_PART(5)
 bool batch_instance_fp16(int hid, int ks0, int nh, int nb1, int nb4, int waves, const void** fn, BatchLaunch* launch) {
   NTBC_BATCH_INSTANCES(Lp::FP16)
+  NTBC_BATCH_ANY(Lp::FP16)
   return false;
 }
 #endif
@@ -1553,6 +1817,86 @@ bool batch_instance_fp8(int hid, int ks0, int nh, int nb1, int nb4, int waves, c
 #endif
 #undef NTBC_BATCH_W
 #undef NTBC_BATCH_BF16_W
+#define NTBC_RES_INSTANCE(LP, H, K, NH)                                                                    \
+  if (hid == H && ks0 == K && nh == NH) {                                                                  \
+    *fn = (const void*)k_infer_res<LP, H, K, NH>;                                                          \
+    *launch = [](dim3 gr, dim3 bl, size_t sh, hipStream_t st, const void* x, const void* y) {             \
+      hipLaunchKernelGGL((k_infer_res<LP, H, K, NH>), gr, bl, sh, st, *static_cast<const InferArgs*>(x),  \
+                         *static_cast<const ResArgs*>(y));                                                 \
+    };                                                                                                     \
+    return true;                                                                                           \
+  }
+#define NTBC_RES_64(X, LP)                                         \
+  X(LP, 64, 1, 1) X(LP, 64, 2, 1) X(LP, 64, 3, 1) X(LP, 64, 4, 1) \
+  X(LP, 64, 1, 2) X(LP, 64, 2, 2) X(LP, 64, 3, 2) X(LP, 64, 4, 2)
+#define NTBC_RES_128(X, LP)                                            \
+  X(LP, 128, 1, 1) X(LP, 128, 2, 1) X(LP, 128, 3, 1) X(LP, 128, 4, 1) \
+  X(LP, 128, 1, 2) X(LP, 128, 2, 2) X(LP, 128, 3, 2) X(LP, 128, 4, 2)
+#define NTBC_RES_BATCH_INSTANCE(LP, H, K, NH)                                                                  \
+  if (hid == H && ks0 == K && nh == NH) {                                                                      \
+    *fn = (const void*)k_infer_res_batch<LP, H, K, NH>;                                                        \
+    *launch = [](dim3 g, dim3 b, size_t sh, hipStream_t st, const void* it, int n, unsigned* d, uint64_t* s) { \
+      hipLaunchKernelGGL((k_infer_res_batch<LP, H, K, NH>), g, b, sh, st, static_cast<const BatchItem*>(it), n, d, s); \
+    };                                                                                                         \
+    return true;                                                                                               \
+  }
+#define NTBC_ANY_INSTANCE(LP, K, NH)                                                                       \
+  if (ks0 == K && nh == NH) {                                                                              \
+    *fn = (const void*)k_infer_lds<LP, 256, K, NH, kAnyMix, 0>;                                            \
+    *launch = [](dim3 gr, dim3 bl, size_t sh, hipStream_t st, const void* x, const void* y) {             \
+      hipLaunchKernelGGL((k_infer_lds<LP, 256, K, NH, kAnyMix, 0>), gr, bl, sh, st,                        \
+                         *static_cast<const InferArgs*>(x), *static_cast<const ChunkTable*>(y));           \
+    };                                                                                                     \
+    return true;                                                                                           \
+  }
+#define NTBC_ANY_INSTANCES(LP)                                                                       \
+  NTBC_ANY_INSTANCE(LP, 1, 1) NTBC_ANY_INSTANCE(LP, 2, 1) NTBC_ANY_INSTANCE(LP, 3, 1)                 \
+  NTBC_ANY_INSTANCE(LP, 4, 1) NTBC_ANY_INSTANCE(LP, 1, 2) NTBC_ANY_INSTANCE(LP, 2, 2)                 \
+  NTBC_ANY_INSTANCE(LP, 3, 2) NTBC_ANY_INSTANCE(LP, 4, 2)
+#if NTBC_PART(12)
+bool res_instance_bf16(int hid, int ks0, int nh, const void** fn, LdsLaunch* launch) {
+  NTBC_RES_64(NTBC_RES_INSTANCE, Lp::BF16)
+  NTBC_RES_128(NTBC_RES_INSTANCE, Lp::BF16)
+  return false;
+}
+#endif
+#if NTBC_PART(13)
+bool res_instance_fp16(int hid, int ks0, int nh, const void** fn, LdsLaunch* launch) {
+  NTBC_RES_64(NTBC_RES_INSTANCE, Lp::FP16)
+  NTBC_RES_128(NTBC_RES_INSTANCE, Lp::FP16)
+  return false;
+}
+#endif
+#if NTBC_PART(14)
+bool any_instance_bf16(int ks0, int nh, const void** fn, LdsLaunch* launch) {
+  NTBC_ANY_INSTANCES(Lp::BF16)
+  return false;
+}
+#endif
+#if NTBC_PART(15)
+bool any_instance_fp16(int ks0, int nh, const void** fn, LdsLaunch* launch) {
+  NTBC_ANY_INSTANCES(Lp::FP16)
+  return false;
+}
+#endif
+#if NTBC_PART(16)
+bool res_batch_instance_bf16(int hid, int ks0, int nh, const void** fn, BatchLaunch* launch) {
+  NTBC_RES_64(NTBC_RES_BATCH_INSTANCE, Lp::BF16)
+  return false;
+}
+#endif
+#if NTBC_PART(17)
+bool res_batch_instance_fp16(int hid, int ks0, int nh, const void** fn, BatchLaunch* launch) {
+  NTBC_RES_64(NTBC_RES_BATCH_INSTANCE, Lp::FP16)
+  return false;
+}
+#endif
+#undef NTBC_RES_INSTANCE
+#undef NTBC_RES_BATCH_INSTANCE
+#undef NTBC_RES_64
+#undef NTBC_RES_128
+#undef NTBC_ANY_INSTANCE
+#undef NTBC_ANY_INSTANCES
 #if NTBC_PART(10)
 // FP32 LDS-staged instances: widths 64/128/256, one to four groups of 16 first-layer inputs.
 #define NTBC_F32_INSTANCE(H, KQ)                                                                        \
@@ -1578,6 +1922,7 @@ bool lds_instance_f32(int hid, int kq, const void** fn, LdsLaunch* launch) {
 #undef NTBC_BATCH_INSTANCE_L
 #undef NTBC_BATCH_INSTANCES
 #undef NTBC_BATCH_REG
+#undef NTBC_BATCH_ANY
 
 // ------------------------------------------------------------------------------ host code (part 0)
 #if NTBC_PART(0)
@@ -1588,12 +1933,47 @@ struct BatchGroup {
   int32_t item_begin, item_end;
   int64_t tiles, lds;
   int32_t waves;       // tile shape: waves (of 32 block positions) per workgroup
-  int32_t pad;
+  int32_t any;         // any-mix epilogue (batch_resident says with which kernel)
   int64_t lds_w[3];    // LDS bytes at 2, 4 and 8 waves
 };
 
 constexpr int kTileWaves[3] = {2, 4, 8};
 int waves_index(int w) { return w == 2 ? 0 : (w == 8 ? 2 : 1); }
+
+// Whether a group runs with resident weights: any mix at width 64, where a CU holds two four-wave workgroups'
+// copies.  (At width 128 a copy fills the CU: eight-wave workgroups of it decoded 16 materials with their mip
+// chains in 2.48 ms against 2.44 streamed in four-wave tiles.)
+bool batch_resident(const BatchGroup& gr) { return gr.any && gr.hid == 64; }
+
+// Numbers the tiles of a group's items for its tile shape.  Resident weights: a workgroup takes the fewest rounds
+// of its waves with which the group's workgroups are all resident at once (256 CUs, eight waves a CU), so
+// that no second, thinly filled generation copies the weights again.
+void batch_tiles(BatchGroup* gr, BatchItem* items) {
+  auto count = [&](int64_t per_wg) {
+    int64_t n = 0;
+    for (int i = gr->item_begin; i < gr->item_end; ++i) n += ceil_div(items[i].a.n, 32 * per_wg);
+    return n;
+  };
+  int64_t per_wg = gr->waves;
+  if (batch_resident(*gr)) {
+    const int64_t slots = std::max<int64_t>(256 * (int64_t)(8 / gr->waves), gr->item_end - gr->item_begin);
+    int64_t lo = 1, hi = 1;  // rounds
+    while (count(gr->waves * hi) > slots) hi *= 2;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (count(gr->waves * mid) > slots) lo = mid + 1;
+      else hi = mid;
+    }
+    per_wg = gr->waves * hi;
+  }
+  gr->tiles = 0;
+  for (int i = gr->item_begin; i < gr->item_end; ++i) {
+    items[i].per_wg = (int32_t)per_wg;
+    items[i].tile_begin = gr->tiles;
+    items[i].tiles = ceil_div(items[i].a.n, 32 * per_wg);
+    gr->tiles += items[i].tiles;
+  }
+}
 
 // Kernel instance of an item: the unrolled two-middle-layer instances where they exist, else the
 // generic one (same selection as ntbc_infer_blocks).
@@ -1607,7 +1987,9 @@ int launch_batch_group(const BatchGroup& gr, const BatchItem* items, unsigned* d
   const void* fn = nullptr;
   BatchLaunch launch = nullptr;
   const bool found =
-      gr.lp == NTBC_FP8_E4M3 ? batch_instance_fp8(gr.hid, gr.ks0, gr.nh, gr.nb1, gr.nb4, gr.waves, &fn, &launch)
+      batch_resident(gr) ? (gr.lp == NTBC_FP16 ? res_batch_instance_fp16(gr.hid, gr.ks0, gr.nh, &fn, &launch)
+                                   : res_batch_instance_bf16(gr.hid, gr.ks0, gr.nh, &fn, &launch))
+      : gr.lp == NTBC_FP8_E4M3 ? batch_instance_fp8(gr.hid, gr.ks0, gr.nh, gr.nb1, gr.nb4, gr.waves, &fn, &launch)
       : gr.lp == NTBC_FP16   ? batch_instance_fp16(gr.hid, gr.ks0, gr.nh, gr.nb1, gr.nb4, gr.waves, &fn, &launch)
                              : batch_instance_bf16(gr.hid, gr.ks0, gr.nh, gr.nb1, gr.nb4, gr.waves, &fn, &launch);
   if (!found) fn = nullptr;
@@ -1623,19 +2005,27 @@ int launch_batch_group(const BatchGroup& gr, const BatchItem* items, unsigned* d
 // an instance for its texture mix and network shape, else nb1 = -1 (heads staged in LDS).
 struct RegPlan {
   int nb1 = -1, nb4 = 0;
+  bool any = false;  // the any-mix slots (reg_any_epilogue)
   int tex[NTBC_MAX_TEXTURES] = {};
 };
 
-// Instances with the register epilogue: single range (any precision) for two BC1 + three BC4 textures
-// at the paper-scale and 1024^2 shapes; batched (BF16) for two BC1 + one to three BC4 textures at
-// widths 64, 128 (four input K-steps, run-time layer count) and 256 (four K-steps, two middle layers).
+// Any-mix instances: bfloat16 and half, one or two middle layers, at most kRegChannels colour channels.
+bool any_mix(const Plan& p) {
+  const int mid = p.s.n_layers - 2;
+  return (p.precision == NTBC_BF16 || p.precision == NTBC_FP16) && !p.s.naive && (mid == 1 || mid == 2) &&
+         p.s.channels <= kRegChannels && p.ksteps[0] <= 4;
+}
+
+// Instances with the register epilogue of one mix: single range (any precision) for two BC1 + three BC4
+// textures at the paper-scale shape (FP8: the 1024^2 one too); batched (BF16) for two BC1 + one to three BC4
+// textures at width 256 (four K-steps, two middle layers).
 bool reg_instance(const Plan& p, int nb1, int nb4, bool batch) {
   if (batch) {
-    const bool shape = (p.hid_inst == 256 && p.ksteps[0] == 4 && batch_nh(p) == 2) ||
-                       ((p.hid_inst == 64 || p.hid_inst == 128) && p.ksteps[0] == 4 && batch_nh(p) == -1);
+    const bool shape = p.hid_inst == 256 && p.ksteps[0] == 4 && batch_nh(p) == 2;
     return p.precision == NTBC_BF16 && shape && nb1 == 2 && nb4 >= 1 && nb4 <= 3;
   }
-  const bool shape = (p.hid_inst == 256 && p.ksteps[0] == 4) || (p.hid_inst == 128 && p.ksteps[0] == 3);
+  const bool shape =
+      (p.hid_inst == 256 && p.ksteps[0] == 4) || (p.hid_inst == 128 && p.ksteps[0] == 3 && p.precision == NTBC_FP8_E4M3);
   return shape && batch_nh(p) == 2 && nb1 == 2 && nb4 == 3;
 }
 
@@ -1650,13 +2040,29 @@ RegPlan reg_plan(const Plan& p, bool batch = false) {
   if (!s.naive && reg_instance(p, nb1, nb4, batch) && 27 * nb1 + 9 * nb4 <= 16 * p.otiles[s.n_layers - 1]) {
     r.nb1 = nb1;
     r.nb4 = nb4;
+  } else if (any_mix(p) && (!batch || p.hid_inst == 64 || p.ksteps[0] >= 3)) {
+    r.nb1 = nb1;
+    r.nb4 = nb4;
+    r.any = true;
   }
   return r;
 }
 
+// Head offset of endpoint g of colour channel q.
+int channel_endpoint(const Shape& s, int q, int g) {
+  int t = 0;
+  while (t + 1 < s.n_textures && s.ch_off[t + 1] <= q) ++t;
+  return s.ep_off[t] + (s.formats[t] == NTBC_BC1 ? 3 * g : g) + q - s.ch_off[t];
+}
+
 // Canonical head neuron of packed head row `row` under the register layout, -1 for a padding row.
 int reg_source(const Shape& s, const RegPlan& r, int row) {
-  const int t = row / 32, q = (row % 32) / 8, g = (row % 8) / 4, slot = 16 * t + 4 * q + row % 4;
+  const int t = row / 32, g = (row % 8) / 4, slot = 16 * t + 4 * ((row % 32) / 8) + row % 4;
+  if (r.any) {
+    const int q = slot / 9, i = slot % 9;
+    if (q >= s.channels) return -1;
+    return i < 8 ? s.endpoint_dim + (8 * g + i) * s.channels + q : channel_endpoint(s, q, g);
+  }
   const int c4 = 24 * r.nb1, e1 = c4 + 8 * r.nb4, e4 = e1 + 3 * r.nb1, used = e4 + r.nb4;
   if (slot < c4)
     return s.endpoint_dim + (8 * g + (slot % 24) / 3) * s.channels + s.ch_off[r.tex[slot / 24]] + slot % 3;
@@ -1673,6 +2079,15 @@ void apply_reg_plan(const Shape& s, const RegPlan& r, PackArgs* pa, InferArgs* a
     for (int row = 0; row < kHeadRows; ++row) pa->head_src[row] = (int16_t)reg_source(s, r, row);
   }
   if (!a) return;
+  if (r.any) {
+    for (int q = 0; q < kRegSlots; ++q) a->reg_tex[q] = -1;
+    for (int t = 0; t < s.n_textures; ++t) a->reg_tex[s.ch_off[t]] = t;
+    for (int q = 0; q < s.channels; ++q) {
+      a->reg_ep[q] = channel_endpoint(s, q, 0);
+      a->reg_ep1[q] = channel_endpoint(s, q, 1);
+    }
+    return;
+  }
   for (int k = 0; k < r.nb1 + r.nb4; ++k) {
     a->reg_tex[k] = r.tex[k];
     a->reg_ep[k] = s.ep_off[r.tex[k]];
@@ -1749,6 +2164,21 @@ extern "C" int ntbc_workspace_size(const ntbc_model_desc* d, int32_t precision, 
 
 namespace {
 
+// Compute units of the current device (asked once per device).
+int cu_count(int* out) {
+  constexpr int kMax = 64;
+  static std::atomic<int> known[kMax];
+  int dev = 0, v = 0;
+  NTBC_HIP(hipGetDevice(&dev));
+  if (dev >= 0 && dev < kMax) v = known[dev].load(std::memory_order_relaxed);
+  if (v == 0) {
+    NTBC_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
+    if (dev >= 0 && dev < kMax) known[dev].store(v, std::memory_order_relaxed);
+  }
+  *out = v > 0 ? v : 1;
+  return NTBC_OK;
+}
+
 // ntbc_infer_blocks with the workspace already chosen (the caller's buffer, or the device's static
 // scratch array for ntbc_infer_blocks_noalloc); `p` is the plan of (d, precision).
 int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm, int32_t precision,
@@ -1819,6 +2249,28 @@ int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm
   a.heads = heads_out;
 
   const int ppw = p.positions_per_wave;
+  if (rp.any && p.hid_inst <= 128) {
+    ResArgs r{};
+    r.units = (int)(p.pack_bytes / sizeof(u32x4));
+    r.n_bias = (int)(p.bias_bytes / 4);
+    r.tiles = ceil_div(n_blocks, 32);
+    const size_t lds = (size_t)p.pack_bytes + (256 + (size_t)r.n_bias) * sizeof(float);
+    int cus = 0;
+    st = cu_count(&cus);
+    if (st != NTBC_OK) return st;
+    // (width 128: at least four waves a copy of up to 128 KB)
+    const int waves = (int)std::max<int64_t>(p.hid_inst == 128 ? 4 : 1, std::min<int64_t>(kResWaves, ceil_div(r.tiles, cus)));
+    const int64_t wgs = std::min<int64_t>(ceil_div(r.tiles, waves), cus);
+    r.per_wg = ceil_div(ceil_div(r.tiles, wgs), waves) * waves;
+    const void* fn = nullptr;
+    LdsLaunch launch = nullptr;
+    NTBC_REQUIRE(precision == NTBC_FP16 ? res_instance_fp16(p.hid_inst, p.ksteps[0], s.n_layers - 2, &fn, &launch)
+                                        : res_instance_bf16(p.hid_inst, p.ksteps[0], s.n_layers - 2, &fn, &launch),
+                 "no resident kernel instance for width %d, %d input K-steps", p.hid_inst, p.ksteps[0]);
+    NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    launch(dim3((unsigned)ceil_div(r.tiles, r.per_wg)), dim3(64 * waves), lds, strm, &a, &r);
+    return check_launch("ntbc_infer_blocks");
+  }
   if ((lp16 || fp8) && lds_shape) {
     ChunkTable ct{};
     size_t lds = 0;
@@ -1828,7 +2280,9 @@ int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm
     const void* fn = nullptr;
     LdsLaunch launch = nullptr;
     const int nh = batch_nh(p);
-    const bool found = fp8 ? lds_instance_fp8(p.hid_inst, p.ksteps[0], nh, rp.nb1, rp.nb4, &fn, &launch)
+    const bool found = rp.any ? (precision == NTBC_FP16 ? any_instance_fp16(p.ksteps[0], s.n_layers - 2, &fn, &launch)
+                                                        : any_instance_bf16(p.ksteps[0], s.n_layers - 2, &fn, &launch))
+                       : fp8 ? lds_instance_fp8(p.hid_inst, p.ksteps[0], nh, rp.nb1, rp.nb4, &fn, &launch)
                        : precision == NTBC_FP16 ? lds_instance_fp16(p.hid_inst, p.ksteps[0], nh, rp.nb1, rp.nb4, &fn, &launch)
                                                 : lds_instance_bf16(p.hid_inst, p.ksteps[0], nh, rp.nb1, rp.nb4, &fn, &launch);
     if (!found) fn = nullptr;
@@ -2090,11 +2544,13 @@ extern "C" int ntbc_batch_plan(const ntbc_batch_item* items, int32_t n_items, in
     }
     model_of[i] = m;
     const RegPlan rp = reg_plan(p, true);
-    const BatchGroup want{precision, p.hid_inst, p.ksteps[0], batch_nh(p), rp.nb1, rp.nb4, 0, 0, 0, 0, kLdsWaves, 0, {0, 0, 0}};
+    const BatchGroup want{precision, p.hid_inst, p.ksteps[0], rp.any ? s.n_layers - 2 : batch_nh(p),
+                          rp.any ? kAnyMix : rp.nb1, rp.any ? 0 : rp.nb4,
+                          0, 0, 0, 0, kLdsWaves, rp.any ? 1 : 0, {0, 0, 0}};
     int gi = -1;
     for (size_t q = 0; q < groups.size(); ++q)
       if (groups[q].hid == want.hid && groups[q].ks0 == want.ks0 && groups[q].nh == want.nh &&
-          groups[q].nb1 == want.nb1 && groups[q].nb4 == want.nb4)
+          groups[q].nb1 == want.nb1 && groups[q].nb4 == want.nb4 && groups[q].any == want.any)
         gi = (int)q;
     if (gi < 0) {
       NTBC_REQUIRE((int)groups.size() < kMaxBatchGroups, "more than %d kernel instances in one batch", kMaxBatchGroups);
@@ -2148,7 +2604,6 @@ extern "C" int ntbc_batch_plan(const ntbc_batch_item* items, int32_t n_items, in
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     BatchGroup& gr = groups[gi];
     gr.item_begin = n_out;
-    int64_t tiles = 0;
     for (int i = 0; i < n_items; ++i) {
       if (key[i] != (int)gi || items[i].n_blocks == 0) continue;
       const Plan& p = plans[i];
@@ -2167,19 +2622,19 @@ extern "C" int ntbc_batch_plan(const ntbc_batch_item* items, int32_t n_items, in
       if (st != NTBC_OK) return st;
       // LDS of every tile shape (the staging area grows with the waves of the staged epilogue)
       for (int w = 0; w < 3; ++w) {
-        const int64_t lw = (int64_t)stage_bytes(p.hid_inst, fp8, bi.a.head_stride, staged, kTileWaves[w]) +
+        const int64_t lw = (batch_resident(gr) ? p.pack_bytes
+                                   : (int64_t)stage_bytes(p.hid_inst, fp8, bi.a.head_stride, staged, kTileWaves[w])) +
                            (256 + (int64_t)bi.ct.n_bias) * (int64_t)sizeof(float);
         gr.lds_w[w] = std::max<int64_t>(gr.lds_w[w], lw);
       }
       gr.lds = gr.lds_w[waves_index(gr.waves)];
-      bi.tile_begin = tiles;
-      bi.tiles = ceil_div(items[i].n_blocks, (int64_t)32 * gr.waves);
+      bi.units = (int32_t)(p.pack_bytes / (int64_t)sizeof(u32x4));
+      bi.n_bias = bi.ct.n_bias;
       bi.index = i;
-      tiles += bi.tiles;
       out[n_out++] = bi;
     }
     gr.item_end = n_out;
-    gr.tiles = tiles;
+    batch_tiles(&gr, out);
   }
   h->n_groups = (int)groups.size();
   for (size_t gi = 0; gi < groups.size(); ++gi) h->groups[gi] = groups[gi];
@@ -2235,16 +2690,11 @@ extern "C" int ntbc_batch_set_waves(void* table, int32_t group, int32_t waves) {
   gr.waves = waves;
   gr.lds = lds;
   BatchItem* items = reinterpret_cast<BatchItem*>(static_cast<char*>(table) + h->items_offset);
-  int64_t tiles = 0;
-  for (int i = gr.item_begin; i < gr.item_end; ++i) {
-    // the staging area (and with it the /255 table and biases behind it) moves with the shape
-    items[i].ct.stage = (int)(stage_bytes(gr.hid, gr.lp == NTBC_FP8_E4M3, items[i].a.head_stride, gr.nb1 < 0, waves) /
+  // the staging area (and with it the /255 table and biases behind it) moves with the shape
+  for (int i = gr.item_begin; i < gr.item_end; ++i)
+    items[i].ct.stage = (int)(stage_bytes(gr.hid, gr.lp == NTBC_FP8_E4M3, items[i].a.head_stride, gr.nb1 == -1, waves) /
                               sizeof(u32x4));
-    items[i].tile_begin = tiles;
-    items[i].tiles = ceil_div(items[i].a.n, (int64_t)32 * waves);
-    tiles += items[i].tiles;
-  }
-  gr.tiles = tiles;
+  batch_tiles(&gr, items);
   return NTBC_OK;
 }
 
