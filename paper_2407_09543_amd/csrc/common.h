@@ -32,6 +32,12 @@ int check_launch(const char* what);
       return ::ntbc::fail(NTBC_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));          \
   } while (0)
 
+// Lets kernel `fn` be launched with `lds` bytes of dynamic LDS (beyond 64 KB only when asked for; below, a launch
+// needs no such call).
+inline hipError_t allow_lds(const void* fn, size_t lds) {
+  return lds <= 64 * 1024 ? hipSuccess : hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
 // Derived sizes of a model description.
 struct Shape {
   int n_levels, base_res, n_features, in_dim, hidden, n_hidden, n_layers;

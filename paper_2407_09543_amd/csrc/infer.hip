@@ -1995,7 +1995,7 @@ int launch_batch_group(const BatchGroup& gr, const BatchItem* items, unsigned* d
   if (!found) fn = nullptr;
   NTBC_REQUIRE(fn != nullptr, "no batch kernel instance for width %d, %d input K-steps, %d-wave tiles", gr.hid, gr.ks0,
                gr.waves);
-  NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gr.lds));
+  NTBC_HIP(allow_lds((const void*)fn, gr.lds));
   launch(dim3((unsigned)gr.tiles), dim3(64 * gr.waves), (size_t)gr.lds, strm, items + gr.item_begin,
          gr.item_end - gr.item_begin, done, stamps);
   return check_launch("ntbc_infer_batch");
@@ -2267,7 +2267,7 @@ int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm
     NTBC_REQUIRE(precision == NTBC_FP16 ? res_instance_fp16(p.hid_inst, p.ksteps[0], s.n_layers - 2, &fn, &launch)
                                         : res_instance_bf16(p.hid_inst, p.ksteps[0], s.n_layers - 2, &fn, &launch),
                  "no resident kernel instance for width %d, %d input K-steps", p.hid_inst, p.ksteps[0]);
-    NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    NTBC_HIP(allow_lds((const void*)fn, lds));
     launch(dim3((unsigned)ceil_div(r.tiles, r.per_wg)), dim3(64 * waves), lds, strm, &a, &r);
     return check_launch("ntbc_infer_blocks");
   }
@@ -2287,7 +2287,7 @@ int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm
                                                 : lds_instance_bf16(p.hid_inst, p.ksteps[0], nh, rp.nb1, rp.nb4, &fn, &launch);
     if (!found) fn = nullptr;
     NTBC_REQUIRE(fn != nullptr, "no LDS kernel instance for width %d, %d input K-steps", p.hid_inst, p.ksteps[0]);
-    NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    NTBC_HIP(allow_lds((const void*)fn, lds));
     launch(dim3((unsigned)nwg), dim3(64 * kLdsWaves), lds, strm, &a, &ct);
     return check_launch("ntbc_infer_blocks");
   }
@@ -2300,7 +2300,7 @@ int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm
     LdsLaunch launch = nullptr;
     if (!lds_instance_f32(p.hid_inst, p.ksteps[0] / 4, &fn, &launch)) fn = nullptr;
     NTBC_REQUIRE(fn != nullptr, "no FP32 kernel instance for width %d, %d input K-steps", p.hid_inst, p.ksteps[0]);
-    NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    NTBC_HIP(allow_lds((const void*)fn, lds));
     launch(dim3((unsigned)ceil_div(n_blocks, (int64_t)16 * kF32Waves)), dim3(64 * kF32Waves), lds, strm, &a, &ct);
     return check_launch("ntbc_infer_blocks");
   }
@@ -2319,7 +2319,7 @@ int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm
                                                                   : (const void*)k_infer_lp<Lp::FP16, 256>))
                          : (p.hid_inst == 64 ? (const void*)k_infer_f32<64, false>
                                              : (p.hid_inst == 128 ? (const void*)k_infer_f32<128, false> : (const void*)k_infer_f32<256, false>));
-    NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    NTBC_HIP(allow_lds((const void*)fn, lds));
   }
   if (precision == NTBC_BF16) {
     if (p.hid_inst == 64) hipLaunchKernelGGL((k_infer_lp<Lp::BF16, 64>), grid, block, lds, strm, a);
@@ -3273,7 +3273,7 @@ extern "C" int ntbc_faithful_infer(const ntbc_faithful_desc* d, const ntbc_faith
   int waves = kFaMaxWaves;
   while (waves > 1 && tiles < 512 * (int64_t)waves) waves /= 2;
   const size_t lds = (size_t)(kFaColUnits + kFaColBias / 4 + kFaLevels) * 16 + (size_t)waves * (3 * s.n1 + 2 * s.n4) * 64 * 16;
-  NTBC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  NTBC_HIP(allow_lds((const void*)fn, lds));
   launch(dim3((unsigned)ceil_div(tiles, waves)), dim3(64 * waves), lds, strm, &a);
   return check_launch("k_faithful");
 }

@@ -2818,7 +2818,7 @@ int fused_forward(Ctx& c, const FusedPlan& f, const float* grid, const float* we
   BwdKernel bk;
   fused_kernels(f.hid, &fk, &bk);
   const size_t lds = (size_t)2 * f.fct.cap * 16 + (size_t)kFW * kPatchBytes + (size_t)f.n_bias * 4;
-  NTBC_HIP(hipFuncSetAttribute((const void*)fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  NTBC_HIP(allow_lds((const void*)fk, lds));
   hipLaunchKernelGGL(fk, dim3((unsigned)(l.bpad / kFPos)), dim3(64 * kFW), lds, c.strm, a);
   return check_launch("k_train_fwd");
 }
@@ -2913,7 +2913,7 @@ int fused_backward(Ctx& c, const FusedPlan& f, const float* grid, bool qat, cons
   BwdKernel bk;
   fused_kernels(f.hid, &fk, &bk);
   const size_t lds = (size_t)2 * f.bct.cap * 16 + (size_t)kFW * kPatchBytes;
-  NTBC_HIP(hipFuncSetAttribute((const void*)bk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  NTBC_HIP(allow_lds((const void*)bk, lds));
   hipLaunchKernelGGL(bk, dim3((unsigned)(l.bpad / kFPos)), dim3(64 * kFW), lds, c.strm, b);
   int st = check_launch("k_train_bwd");
   if (st != NTBC_OK) return st;
@@ -3103,7 +3103,7 @@ int f32_forward(Ctx& c, const F32Plan& f, const float* grid, const float* weight
   F32Bwd bk;
   f32_kernels(s.hidden, f.groups, c.selu, &fk, &bk);
   const size_t lds = (size_t)2 * f.fct.cap * 16 + (size_t)f.n_bias * 4;
-  NTBC_HIP(hipFuncSetAttribute((const void*)fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  NTBC_HIP(allow_lds((const void*)fk, lds));
   hipLaunchKernelGGL(fk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, a);
   return check_launch("k_f32_fwd");
 }
@@ -3134,7 +3134,7 @@ int f32_backward(Ctx& c, const F32Plan& f, const float* grid, bool qat, const in
   F32Bwd bk;
   f32_kernels(s.hidden, f.groups, c.selu, &fk, &bk);
   const size_t lds = (size_t)2 * f.bct.cap * 16;
-  NTBC_HIP(hipFuncSetAttribute((const void*)bk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  NTBC_HIP(allow_lds((const void*)bk, lds));
   hipLaunchKernelGGL(bk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, b);
   int st = check_launch("k_f32_bwd");
   if (st != NTBC_OK) return st;
