@@ -853,8 +853,9 @@ struct LossArgs {
   float inv_ne, inv_nc;  // 1/(n E), 1/(n 16 C)
   float* losses;         // [5]
   int dsigmoid;          // write dL/dZ = dL/dY * Y (1 - Y) (the head's pre-activation) instead of dL/dY
-  int tex_of[2][NTBC_MAX_TEXTURES];  // the BC1 textures, then the BC4 textures, in head order
-  int n_bc1;                         // how many BC1 textures (k_loss_grad_mixed)
+  int tex_of[NTBC_MAX_TEXTURES];  // the BC1 textures, then the BC4 textures, each in head order
+  int n_bc1;                      // how many BC1 textures
+  int g_shift;                    // a block's groups of 16 positions: 1 << g_shift
 };
 
 // Texel row `sub` (4 texels x CH bytes) of block id of texture t: from the block-major copy (the block's
@@ -891,7 +892,8 @@ __device__ __forceinline__ void palette_coef(bool eight, int n, float* a, float*
   *k = (!eight && n == 7) ? 1.0f : 0.0f;
 }
 
-__device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+// -1, 0 or 1: any nonzero v, the smallest subnormal too, is beyond 1 once multiplied by 2^200.
+__device__ __forceinline__ float sign_of(float v) { return __builtin_amdgcn_fmed3f(ldexpf(v, 200), -1.0f, 1.0f); }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
 // Straight-through decoded-colour term for one texel: distances dist[0..N) (d_n = -dist_n), the
@@ -900,26 +902,27 @@ __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcp
 // g = 2 (x - c) / N_cd, xs = sum_n s_n pr_n, computed as dd_n = (e_n / (T tot)) (G_n - sum_m e_m G_m / tot)
 // with e_n = exp(-(dist_n - dist_min) / T), tot = sum e_n and G_n = g . pr_n.  t2 = log2(e) / T.
 template <int CH, int N>
-__device__ __forceinline__ void cd_term(const float* dist, const float (*pr)[3], const float* er0, const float* er1,
-                                        bool eight_ref, const float* c, float inv_ncd, float inv_t, float t2,
-                                        float* loss, float* dd) {
+__device__ __forceinline__ void cd_term(const float* dist, const float (*pr)[3], const float* c, float inv_ncd, float inv_t,
+                                        float t2, float* loss, float* dd) {
 #pragma clang fp contract(fast)
-  // hard choice: the first nearest entry k.  Its colour is rebuilt from k with the same operations
-  // that built pr (an indexed read of pr would force the palette out of registers).
-  int k = 0;
-  float dmin = dist[0];
+  // hard choice: the colour of the first nearest entry
+  float dmin = dist[0], x[CH];
+#pragma unroll
+  for (int ch = 0; ch < CH; ++ch) {
+    x[ch] = pr[0][ch];
+    asm("" : "+v"(x[ch]));  // a value from here on: a choice between loads of pr would put the palette into memory
+  }
 #pragma unroll
   for (int n = 1; n < N; ++n) {
     const bool nearer = dist[n] < dmin;
     dmin = nearer ? dist[n] : dmin;
-    k = nearer ? n : k;
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) x[ch] = nearer ? pr[n][ch] : x[ch];
   }
-  float ak, bk, kk;
-  palette_coef<CH == 3>(eight_ref, k, &ak, &bk, &kk);
   float gx[CH];
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
-    const float d = (ak * er0[ch] + bk * er1[ch] + kk) - c[ch];
+    const float d = x[ch] - c[ch];
     *loss += d * d;
     gx[ch] = 2.0f * d * inv_ncd;
   }
@@ -943,18 +946,42 @@ __device__ __forceinline__ void cd_term(const float* dist, const float (*pr)[3],
 // Losses and head gradients of one texture of one position, for the texel row `sub` (texels
 // 4*sub .. 4*sub+3; four lanes share a position/texture).  Returns the partial endpoint gradients in
 // de0/de1; lane sub == 0 also carries the L_e term.  The caller combines the four lanes and writes the
-// endpoint gradients.  Non-finite heads show up as non-finite gradients, which the caller checks.  A
+// endpoint gradients.  row_c is the position's row of the block's tile: the lane's colour gradients take the place
+// of the colours.  Non-finite heads show up as non-finite gradients, which the caller checks.  A
 // distance ||v|| and its unit vector come from one reciprocal square root (CH = 3), or from |v| and
 // sign(v) (CH = 1: no transcendental).
+struct LossIn {
+  uint64_t w;      // the reference block
+  uint32_t rw[3];  // the lane's texel row: 4 texels x CH bytes
+  float eh[6];     // the predicted endpoints
+};
+
 template <int CH>
-__device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t, int id, int sub, float* le, float* lc,
-                                             float* lcde, float* lcdc, bool* bad, float de0[3], float de1[3]) {
+__device__ __forceinline__ void loss_load(const LossArgs& a, int64_t p, int t, int id, int sub, LossIn* in) {
+  in->w = a.ref[(int64_t)t * a.n_positions + id];
+#pragma unroll
+  for (int k = 0; k < 2 * CH; ++k) in->eh[k] = a.y[p * a.ld + a.ep_off[t] + k];
+  const uint8_t* row = texel_row<CH>(a, t, id, sub);
+  // dword loads when the texture is 4-byte aligned (the row offset always is), byte loads otherwise
+  if ((reinterpret_cast<uintptr_t>(row) & 3) == 0) {
+#pragma unroll
+    for (int k = 0; k < CH; ++k) in->rw[k] = reinterpret_cast<const uint32_t*>(row)[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < CH; ++k)
+      in->rw[k] = (uint32_t)row[4 * k] | ((uint32_t)row[4 * k + 1] << 8) | ((uint32_t)row[4 * k + 2] << 16) |
+                  ((uint32_t)row[4 * k + 3] << 24);
+  }
+}
+
+template <int CH>
+__device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in, float* row_c, int t, int sub, float* le,
+                                             float* lc, float* lcde, float* lcdc, bool* bad, float de0[3], float de1[3]) {
 #pragma clang fp contract(fast)
   constexpr bool bc1 = CH == 3;
   constexpr int N = bc1 ? 4 : 8;
-  const float* yp = a.y + p * a.ld;
-  float* dyp = a.dy + p * a.ld;
-  const uint64_t w = a.ref[(int64_t)t * a.n_positions + id];
+  const uint64_t w = in.w;
+  const uint32_t rw0 = in.rw[0], rw1 = CH > 1 ? in.rw[1] : 0, rw2 = CH > 2 ? in.rw[2] : 0;
   float er0[3] = {0, 0, 0}, er1[3] = {0, 0, 0};
   bool eight_ref = true;
   constexpr float k255 = 1.0f / 255.0f;
@@ -973,19 +1000,12 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t
     eight_ref = b0 > b1;
   }
   float pr[N][3], ph[N][3], ca[N], cb[N];
-  const int e = a.ep_off[t];
   float eh0[3], eh1[3];
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
-    eh0[ch] = yp[e + ch];
-    eh1[ch] = yp[e + CH + ch];
+    eh0[ch] = in.eh[ch];
+    eh1[ch] = in.eh[CH + ch];
   }
-  // the predicted colours of the lane's four texels, loaded before the palettes are built
-  float chat4[4][CH];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int ch = 0; ch < CH; ++ch) chat4[x][ch] = yp[a.E + (4 * sub + x) * a.C + a.ch_off[t] + ch];
   const bool eight_hat = bc1 ? true : eh0[0] > eh1[0];
 #pragma unroll
   for (int n = 0; n < N; ++n) {
@@ -1012,30 +1032,17 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t
       de1[ch] = a.w_e * 2.0f * d1 * a.inv_ne;
     }
   }
-  const uint8_t* row = texel_row<CH>(a, t, id, sub);
-  // the lane's texel row (4 texels x CH bytes) in CH words: dword loads when the texture is 4-byte
-  // aligned (the row offset always is), byte loads otherwise
-  uint32_t rw[CH];
-  if ((reinterpret_cast<uintptr_t>(row) & 3) == 0) {
-#pragma unroll
-    for (int k = 0; k < CH; ++k) rw[k] = reinterpret_cast<const uint32_t*>(row)[k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < CH; ++k)
-      rw[k] = (uint32_t)row[4 * k] | ((uint32_t)row[4 * k + 1] << 8) | ((uint32_t)row[4 * k + 2] << 16) |
-              ((uint32_t)row[4 * k + 3] << 24);
-  }
 #pragma unroll 1
   for (int x = 0; x < 4; ++x) {
     const int i = 4 * sub + x;
     float c[CH], chat[CH], dchat[CH];
-    const int ci = a.E + i * a.C + a.ch_off[t];
+    const int ci = i * a.C + a.ch_off[t];
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
       const int b = x * CH + ch;  // byte of the row (run-time x: words chosen by selects, no indexing)
-      const uint32_t word = CH == 1 ? rw[0] : (b < 4 ? rw[0] : (b < 8 ? rw[CH > 1 ? 1 : 0] : rw[CH > 2 ? 2 : 0]));
+      const uint32_t word = CH == 1 ? rw0 : (b < 4 ? rw0 : (b < 8 ? rw1 : rw2));
       c[ch] = (float)((word >> (8 * (b & 3))) & 255u) * k255;
-      chat[ch] = x == 0 ? chat4[0][ch] : (x == 1 ? chat4[1][ch] : (x == 2 ? chat4[2][ch] : chat4[3][ch]));
+      chat[ch] = row_c[ci + ch];
       const float d = chat[ch] - c[ch];
       *lc += d * d;
       dchat[ch] = a.w_c * 2.0f * d * a.inv_nc;
@@ -1047,7 +1054,7 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t
       if (CH == 1) {
         const float v = c[0] - ph[n][0];
         dist[n] = fabsf(v);
-        unit[n] = v > 0.0f ? 1.0f : (v < 0.0f ? -1.0f : 0.0f);
+        unit[n] = sign_of(v);
       } else {
         float acc = 0.0f;
 #pragma unroll
@@ -1055,12 +1062,12 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t
           const float d = c[ch] - ph[n][ch];
           acc += d * d;
         }
-        const float rs = acc > 0.0f ? __builtin_amdgcn_rsqf(acc) : 0.0f;
+        const float rs = __builtin_amdgcn_rsqf(fmaxf(acc, 0x1p-126f));  // v = 0: distance and gradient 0
         dist[n] = acc * rs;
         unit[n] = rs;
       }
     }
-    cd_term<CH, N>(dist, pr, er0, er1, eight_ref, c, a.inv_nc, a.inv_t, a.t2, lcde, dd);
+    cd_term<CH, N>(dist, pr, c, a.inv_nc, a.inv_t, a.t2, lcde, dd);
 #pragma unroll
     for (int n = 0; n < N; ++n) {
       const float q = a.w_cde * dd[n] * unit[n];
@@ -1083,7 +1090,7 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t
       if (CH == 1) {
         const float v = chat[0] - pr[n][0];
         dist[n] = fabsf(v);
-        unit[n] = v > 0.0f ? 1.0f : (v < 0.0f ? -1.0f : 0.0f);
+        unit[n] = sign_of(v);
       } else {
         float acc = 0.0f;
 #pragma unroll
@@ -1091,12 +1098,12 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t
           const float d = chat[ch] - pr[n][ch];
           acc += d * d;
         }
-        const float rs = acc > 0.0f ? __builtin_amdgcn_rsqf(acc) : 0.0f;
+        const float rs = __builtin_amdgcn_rsqf(fmaxf(acc, 0x1p-126f));  // v = 0: distance and gradient 0
         dist[n] = acc * rs;
         unit[n] = rs;
       }
     }
-    cd_term<CH, N>(dist, pr, er0, er1, eight_ref, c, a.inv_nc, a.inv_t, a.t2, lcdc, dd);
+    cd_term<CH, N>(dist, pr, c, a.inv_nc, a.inv_t, a.t2, lcdc, dd);
 #pragma unroll
     for (int n = 0; n < N; ++n) {
       const float q = a.w_cdc * dd[n] * unit[n];
@@ -1109,20 +1116,25 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, int64_t p, int t
     }
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
-      dyp[ci + ch] = head_grad(a, dchat[ch], chat[ch]);
+      row_c[ci + ch] = head_grad(a, dchat[ch], chat[ch]);
       *bad |= !isfinite(dchat[ch]);
     }
   }
 }
 
-// Four lanes per (texture, position).  A block has one wave per texture (so a wave works on one
-// format) and covers 16 positions at a time: the waves of a block read the same rows of the heads and
-// write the same rows of their gradient at about the same time, so those rows pass through L2 once
-// instead of once per texture.  A grid-stride loop over groups of 16 positions keeps the shuffles
-// uniform; the loss sums are reduced per block and added with one atomic per block and loss
-// (same-address atomics from every wave serialise in L2).
-// Blocks of the loss launches: every block resident at once (a CU holds 16 of their waves at four waves
-// per SIMD; a block has one wave per texture), so the grid-stride loop has no second, thinly filled round.
+// Four lanes per (texture, position).  A wave works on one texture of 16 positions at a time; a block of four
+// waves covers 1 << g_shift groups of 16 positions, and its waves take the (texture, group) pairs in turn,
+// texture by texture.  Four waves, because a block's waves go to the CU's SIMDs in turn: with one wave per texture
+// (five) the first SIMD got two of each block, two blocks filled it, and it had 40% of the CU's work.  The colours
+// of the positions come into LDS by direct copies, each lane replaces a value by its gradient there, and the
+// rows are stored in whole lines; in place, a lane's values 4 C bytes apart were a request of their own each
+// (6.7 M write requests for 42 MB), and four groups of four waves then thrash L1 (163 us).  Bound by instruction issue
+// (palette distances, softmax and straight-through gradients: some 1,500 VALU instructions per texture of 16
+// positions, 64 exponentials among them).  65,536 positions of five textures: 113 us with a wave per texture
+// and values in place, 83 so, 77 with the sign and the hard choice below.  The loss sums are reduced per block
+// and added with one atomic per block and loss (same-address atomics from every wave serialise in L2).
+// Blocks that are resident at once with waves_per_block waves each, as a CU holds 16 of their waves at four waves
+// per SIMD, and no more than the positions fill.
 int loss_blocks(int64_t n, int waves_per_block) {
   static int cus = 0;
   if (cus == 0) {
@@ -1136,42 +1148,38 @@ int loss_blocks(int64_t n, int waves_per_block) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 16), resident));
 }
 
-// The wave's groups of 16 positions for texture t of format CH (CH = 3: BC1, CH = 1: BC4); the loss sums
-// accumulate in le .. lcdc, non-finite gradients in bad.
+// Floats between a tile's rows: odd, so that a wave's 16 rows start in different banks.
+__host__ __device__ inline int loss_row(int channels) { return (16 * channels) | 1; }
+inline size_t loss_lds(int g_shift, int channels) { return (size_t)(16 << g_shift) * loss_row(channels) * sizeof(float); }
+
+__device__ __forceinline__ void dma_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The sum over an aligned group of four lanes, in every one of them.
+__device__ __forceinline__ float quad_sum(float x) {
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));  // lane ^ 1
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, true));  // lane ^ 2
+}
+
+// Texture t of format CH (CH = 3: BC1, CH = 1: BC4) of position p's row `tile` of colours, all lanes of a position
+// alike in `active`; the loss sums accumulate in le .. lcdc, non-finite gradients in bad.
 template <int CH>
-__device__ __forceinline__ void loss_groups(const LossArgs& a, int t, int lane, float& le, float& lc, float& lcde,
-                                            float& lcdc, bool& bad) {
-  const int64_t groups = (a.n + 15) / 16;
-  for (int64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    float de0[3] = {0, 0, 0}, de1[3] = {0, 0, 0};
-    const int64_t p = grp * 16 + (lane >> 2);
-    const int sub = lane & 3;
-    const bool active = p < a.n;
-    if (active) {
-      const int id = clamp_id(a.ids[p], a.n_positions);
-      texture_loss<CH>(a, p, t, id, sub, &le, &lc, &lcde, &lcdc, &bad, de0, de1);
-    }
-    // combine the endpoint gradients of the four lanes of a position (an aligned group of the wave)
+__device__ __forceinline__ void loss_group(const LossArgs& a, const LossIn& in, float* tile, int64_t p, bool active, int t,
+                                           int sub, float& le, float& lc, float& lcde, float& lcdc, bool& bad) {
+  float de0[3] = {0, 0, 0}, de1[3] = {0, 0, 0};
+  if (active) texture_loss<CH>(a, in, tile, t, sub, &le, &lc, &lcde, &lcdc, &bad, de0, de1);
+  // combine the endpoint gradients of the four lanes of a position (an aligned group of the wave)
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
+  for (int ch = 0; ch < CH; ++ch) {
+    de0[ch] = quad_sum(de0[ch]);
+    de1[ch] = quad_sum(de1[ch]);
+  }
+  if (active && sub == 0) {
+    float* dyp = a.dy + p * a.ld + a.ep_off[t];
 #pragma unroll
-      for (int off = 1; off < 4; off <<= 1) {
-        de0[ch] += __shfl_xor(de0[ch], off);
-        de1[ch] += __shfl_xor(de1[ch], off);
-      }
-    }
-    if (active && sub == 0) {
-      constexpr int ch_n = CH;
-      float* dyp = a.dy + p * a.ld + a.ep_off[t];
-      const float* yp = a.y + p * a.ld + a.ep_off[t];
-#pragma unroll
-      for (int ch = 0; ch < 3; ++ch) {
-        if (ch < ch_n) {
-          dyp[ch] = head_grad(a, de0[ch], yp[ch]);
-          dyp[ch_n + ch] = head_grad(a, de1[ch], yp[ch_n + ch]);
-          bad |= !isfinite(de0[ch]) || !isfinite(de1[ch]);
-        }
-      }
+    for (int ch = 0; ch < CH; ++ch) {
+      dyp[ch] = head_grad(a, de0[ch], in.eh[ch]);
+      dyp[CH + ch] = head_grad(a, de1[ch], in.eh[CH + ch]);
+      bad |= !isfinite(de0[ch]) || !isfinite(de1[ch]);
     }
   }
 }
@@ -1210,28 +1218,52 @@ __device__ __forceinline__ void loss_finish(const LossArgs& a, float le, float l
   }
 }
 
-// Materials of one format: the block has one wave per texture (wave w works on texture
-// a.tex_of[CH == 3 ? 0 : 1][w]).
-template <int CH>
-__global__ void __launch_bounds__(64 * NTBC_MAX_TEXTURES) k_loss_grad(LossArgs a) {
-  __shared__ float part[NTBC_MAX_TEXTURES][4];
-  __shared__ int part_bad[NTBC_MAX_TEXTURES];
-  float le = 0.0f, lc = 0.0f, lcde = 0.0f, lcdc = 0.0f;
-  bool bad = false;
-  loss_groups<CH>(a, a.tex_of[CH == 3 ? 0 : 1][threadIdx.x >> 6], threadIdx.x & 63, le, lc, lcde, lcdc, bad);
-  loss_finish(a, le, lc, lcde, lcdc, bad, part, part_bad);
-}
+// FMT = 3 or 1: materials of BC1 or of BC4 textures only; 0: of both (a wave-uniform branch).
+constexpr int kLossThreads = 256;
 
-// Materials of both formats: waves 0 .. n_bc1-1 take the BC1 textures, the others the BC4 textures (a
-// wave-uniform branch), so the waves of a block read each row of the heads together.
-__global__ void __launch_bounds__(64 * NTBC_MAX_TEXTURES) k_loss_grad_mixed(LossArgs a) {
-  __shared__ float part[NTBC_MAX_TEXTURES][4];
-  __shared__ int part_bad[NTBC_MAX_TEXTURES];
+template <int FMT>
+__global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(4))) k_loss_grad(LossArgs a) {
+  __shared__ float part[kLossThreads / 64][4];
+  __shared__ int part_bad[kLossThreads / 64];
   float le = 0.0f, lc = 0.0f, lcde = 0.0f, lcdc = 0.0f;
   bool bad = false;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (wave < a.n_bc1) loss_groups<3>(a, a.tex_of[0][wave], lane, le, lc, lcde, lcdc, bad);
-  else loss_groups<1>(a, a.tex_of[1][wave - a.n_bc1], lane, le, lc, lcde, lcdc, bad);
+  extern __shared__ float tile[];
+  const int S = loss_row(a.C), cols = 16 * a.C, per = 16 << a.g_shift;
+  const bool own = a.g_shift == 2;  // a wave's rows are its own: nothing to wait for
+  const int r0 = own ? 16 * wave : wave, dr = own ? 1 : kLossThreads / 64;
+  for (int64_t p0 = (int64_t)blockIdx.x * per; p0 < a.n; p0 += (int64_t)gridDim.x * per) {
+    const int rows = a.n - p0 < per ? (int)(a.n - p0) : per, r1 = own ? min(rows, r0 + 16) : rows;
+    for (int r = r0; r < r1; r += dr)
+      for (int c = 0; c < cols; c += 64)
+        if (c + lane < cols)
+          __builtin_amdgcn_global_load_lds(a.y + (p0 + r) * a.ld + a.E + c + lane,
+                                           (__attribute__((address_space(3))) void*)(tile + r * S + c), 4, 0, 0);
+    const int items = a.n_textures << a.g_shift, sub = lane & 3, q = lane >> 2;
+    LossIn in{};
+    const auto load = [&](int i, LossIn* to) {
+      const int64_t p = p0 + 16 * (i & ((1 << a.g_shift) - 1)) + q;
+      if (i >= items || p >= a.n) return;
+      const int k = i >> a.g_shift, id = clamp_id(a.ids[p], a.n_positions);
+      if (FMT == 3 || (FMT == 0 && k < a.n_bc1)) loss_load<3>(a, p, a.tex_of[k], id, sub, to);
+      else loss_load<1>(a, p, a.tex_of[k], id, sub, to);
+    };
+    load(wave, &in);
+    dma_arrived();
+    if (!own) __syncthreads();
+    for (int i = wave; i < items; i += kLossThreads / 64) {
+      const int row = 16 * (i & ((1 << a.g_shift) - 1)) + q, k = i >> a.g_shift;
+      if (FMT == 3 || (FMT == 0 && k < a.n_bc1))
+        loss_group<3>(a, in, tile + row * S, p0 + row, row < rows, a.tex_of[k], sub, le, lc, lcde, lcdc, bad);
+      else
+        loss_group<1>(a, in, tile + row * S, p0 + row, row < rows, a.tex_of[k], sub, le, lc, lcde, lcdc, bad);
+      load(i + kLossThreads / 64, &in);
+    }
+    if (!own) __syncthreads();
+    for (int r = r0; r < r1; r += dr)
+      for (int c = lane; c < cols; c += 64) a.dy[(p0 + r) * a.ld + a.E + c] = tile[r * S + c];
+    if (!own) __syncthreads();
+  }
   loss_finish(a, le, lc, lcde, lcdc, bad, part, part_bad);
 }
 
@@ -2585,16 +2617,25 @@ int loss_grad(const Shape& s, const ntbc_targets* t, const float* heads, const i
   a.inv_ne = (float)(1.0 / ((double)n * s.endpoint_dim));
   a.inv_nc = (float)(1.0 / ((double)n * 16.0 * s.channels));
   a.losses = losses;
-  int nf[2] = {0, 0};
-  for (int i = 0; i < s.n_textures; ++i) {
-    const int k = s.formats[i] == NTBC_BC1 ? 0 : 1;
-    a.tex_of[k][nf[k]++] = i;
-  }
-  a.n_bc1 = nf[0];
-  const dim3 grid((unsigned)loss_blocks(n, nf[0] + nf[1]));
-  if (nf[0] > 0 && nf[1] > 0) hipLaunchKernelGGL(k_loss_grad_mixed, grid, dim3(64 * (nf[0] + nf[1])), 0, strm, a);
-  else if (nf[0] > 0) hipLaunchKernelGGL(k_loss_grad<3>, grid, dim3(64 * nf[0]), 0, strm, a);
-  else hipLaunchKernelGGL(k_loss_grad<1>, grid, dim3(64 * nf[1]), 0, strm, a);
+  int n_tex = 0;
+  for (int i = 0; i < s.n_textures; ++i)
+    if (s.formats[i] == NTBC_BC1) a.tex_of[n_tex++] = i;
+  a.n_bc1 = n_tex;
+  for (int i = 0; i < s.n_textures; ++i)
+    if (s.formats[i] != NTBC_BC1) a.tex_of[n_tex++] = i;
+  // One group a block while every block is resident: the textures of a position side by side is the shortest way
+  // (16,384 positions of five textures 30 us, with four groups a block 38).  Beyond that, the groups that give the
+  // waves equal shares, as far as four blocks of a CU have LDS for them (65,536 positions: five textures 90 us with
+  // one group, 78 with two, 77 with four; six textures 95, 86, 91).
+  const int64_t groups = ceil_div(n, 16), resident = loss_blocks((int64_t)1 << 40, kLossThreads / 64);
+  if (groups > resident)
+    while ((s.n_textures << a.g_shift) % (kLossThreads / 64) != 0 && loss_lds(a.g_shift + 1, s.channels) <= 40 * 1024) ++a.g_shift;
+  const size_t lds = loss_lds(a.g_shift, s.channels);
+  const dim3 block(kLossThreads);
+  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(groups, (int64_t)1 << a.g_shift), 8 * resident)));
+  if (a.n_bc1 == 0) hipLaunchKernelGGL(k_loss_grad<1>, grid, block, lds, strm, a);
+  else if (a.n_bc1 == n_tex) hipLaunchKernelGGL(k_loss_grad<3>, grid, block, lds, strm, a);
+  else hipLaunchKernelGGL(k_loss_grad<0>, grid, block, lds, strm, a);
   return check_launch("k_loss_grad");
 }
 
