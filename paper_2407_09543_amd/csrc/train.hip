@@ -3001,6 +3001,7 @@ int fused_backward(Ctx& c, const FusedPlan& f, const float* grid, bool qat, cons
 // ------------------------------------------------------------------------------------------ FP32, chained: host
 struct F32Plan {
   int groups, head_tiles;  // 16-input groups of the first layer, 16-row tiles of the head
+  bool narrow;             // backward and weight products in one (k_f32_bwd_dw)
   F32PackArgs pk;
   F32Chunks fct, bct;
   int pack_units, n_bias;
@@ -3009,10 +3010,11 @@ struct F32Plan {
 // The shapes that k_f32_fwd and k_f32_bwd take; others go through k_gemm layer by layer.
 bool f32_plan(const Shape& s, bool selu, F32Plan* fp) {
   if ((s.hidden != 64 && s.hidden != 128 && s.hidden != 256) || s.in_dim > 16 * kF32Groups || s.head_dim > 16 * kF32HeadTiles ||
-      (selu && (s.hidden != 64 || s.in_dim > 16)))
+      (selu && (s.hidden != 64 || s.n_hidden != kF32NarrowHidden || s.in_dim > 16 || s.head_dim > 16 * kF32NarrowHeadTiles)))
     return false;
   F32Plan& f = *fp;
   f = F32Plan{};
+  f.narrow = selu;
   f.groups = (s.in_dim + 15) / 16;
   f.head_tiles = (s.head_dim + 15) / 16;
   F32PackArgs& a = f.pk;
@@ -3067,16 +3069,18 @@ F32Layout f32_layout(const Shape& s, const F32Plan& f, int64_t batch) {
   l.bias = take((int64_t)f.n_bias * 4);
   l.x = take(n * s.in_dim * 4);
   for (int k = 0; k < s.n_hidden; ++k) l.h[k] = take(n * s.hidden * 4);
-  for (int k = 0; k < s.n_hidden; ++k) l.dh[k] = take(n * s.hidden * 4);
+  if (!f.narrow)
+    for (int k = 0; k < s.n_hidden; ++k) l.dh[k] = take(n * s.hidden * 4);
   l.y = take(n * s.head_dim * 4);
   l.dy = take(n * s.head_dim * 4);
   l.dx = take(n * s.in_dim * 4);
   for (int k = 0; k < s.n_layers; ++k)
     l.n_tiles += (int)(ceil_div(s.layer_out[k], kF32DwTile) * ceil_div(s.layer_in[k], kF32DwTile));
-  // about three workgroups a CU, of at least 64 positions each
-  const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(ceil_div(768, l.n_tiles), n / 64));
+  // about three workgroups a CU, of at least 64 positions each (narrow: the workgroups of the one kernel; never more
+  // bytes than with dZ, which the workspace has room for)
+  const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(f.narrow ? kF32NarrowBlocks : ceil_div(768, l.n_tiles), n / 64));
   l.k_split = (int)(ceil_div(ceil_div(n, splits), kF32DwK) * kF32DwK);
-  l.splits = (int)ceil_div(n, l.k_split);
+  l.splits = f.narrow ? (int)splits : (int)ceil_div(n, l.k_split);
   // (room for the ranges before rounding, so that a larger batch never needs a smaller workspace)
   l.part = take((int64_t)l.n_tiles * splits * kF32DwTile * kF32DwTile * 4);
   l.dbpart = take((int64_t)l.n_tiles * splits * kF32DwTile * 4);
@@ -3090,15 +3094,15 @@ typedef void (*F32Bwd)(F32BwdArgs);
 template <int H>
 void f32_kernels_of(int groups, F32Fwd* fk, F32Bwd* bk) {
   switch (groups) {
-    case 1: *fk = k_f32_fwd<H, 1, false>, *bk = k_f32_bwd<H, 1, false>; break;
-    case 2: *fk = k_f32_fwd<H, 2, false>, *bk = k_f32_bwd<H, 2, false>; break;
-    case 3: *fk = k_f32_fwd<H, 3, false>, *bk = k_f32_bwd<H, 3, false>; break;
-    default: *fk = k_f32_fwd<H, 4, false>, *bk = k_f32_bwd<H, 4, false>; break;
+    case 1: *fk = k_f32_fwd<H, 1, false>, *bk = k_f32_bwd<H, 1>; break;
+    case 2: *fk = k_f32_fwd<H, 2, false>, *bk = k_f32_bwd<H, 2>; break;
+    case 3: *fk = k_f32_fwd<H, 3, false>, *bk = k_f32_bwd<H, 3>; break;
+    default: *fk = k_f32_fwd<H, 4, false>, *bk = k_f32_bwd<H, 4>; break;
   }
 }
 
 void f32_kernels(int hid, int groups, bool selu, F32Fwd* fk, F32Bwd* bk) {
-  if (selu) *fk = k_f32_fwd<64, 1, true>, *bk = k_f32_bwd<64, 1, true>;
+  if (selu) *fk = k_f32_fwd<64, 1, true>, *bk = nullptr;  // k_f32_bwd_dw
   else if (hid == 64) f32_kernels_of<64>(groups, fk, bk);
   else if (hid == 128) f32_kernels_of<128>(groups, fk, bk);
   else f32_kernels_of<256>(groups, fk, bk);
@@ -3157,57 +3161,95 @@ int f32_backward(Ctx& c, const F32Plan& f, const float* grid, bool qat, const in
   const Shape& s = c.s;
   const F32Layout l = f32_layout(s, f, c.n);
   char* ws = reinterpret_cast<char*>(c.ws);
-  F32BwdArgs b{};
-  b.dz = c.dy;
-  b.in_dim = s.in_dim;
-  b.n_layers = s.n_layers;
-  b.head_dim = s.head_dim;
-  b.head_tiles = f.head_tiles;
-  b.n = c.n;
-  b.wpack = reinterpret_cast<const u32x4*>(ws + l.pack);
-  for (int k = 0; k < s.n_hidden; ++k) {
-    b.h[k] = reinterpret_cast<const float*>(ws + l.h[k]);
-    b.dh[k] = reinterpret_cast<float*>(ws + l.dh[k]);
-  }
-  b.dx = reinterpret_cast<float*>(ws + l.dx);
-  b.ct = f.bct;
-  F32Fwd fk;
-  F32Bwd bk;
-  f32_kernels(s.hidden, f.groups, c.selu, &fk, &bk);
-  const size_t lds = (size_t)2 * f.bct.cap * 16;
-  NTBC_HIP(allow_lds((const void*)bk, lds));
-  hipLaunchKernelGGL(bk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, b);
-  int st = check_launch("k_f32_bwd");
-  if (st != NTBC_OK) return st;
-  ScatterBeside beside;
-  st = beside.fork(c, grid, qat, ids, b.dx, d_grid);
-  if (st != NTBC_OK) return st;
-  F32DwArgs d{};
+  const float* x = reinterpret_cast<const float*>(ws + l.x);
+  float* dx = reinterpret_cast<float*>(ws + l.dx);
+  const u32x4* wpack = reinterpret_cast<const u32x4*>(ws + l.pack);
+  float *part = reinterpret_cast<float*>(ws + l.part), *dbpart = reinterpret_cast<float*>(ws + l.dbpart);
   DwArgs r{};
   int tile0 = 0;
   for (int k = 0; k < s.n_layers; ++k) {
-    F32DwJob& J = d.job[k];
-    J.a = k == s.n_layers - 1 ? b.dz : b.dh[k];
-    J.b = k == 0 ? reinterpret_cast<const float*>(ws + l.x) : b.h[k - 1];
-    J.M = r.job[k].M = s.layer_out[k];
-    J.N = r.job[k].N = s.layer_in[k];
-    J.tiles_n = r.job[k].tiles_n = (int)ceil_div(J.N, kF32DwTile);
-    J.tile0 = r.job[k].tile0 = tile0;
-    tile0 += (int)ceil_div(J.M, kF32DwTile) * J.tiles_n;
+    r.job[k].M = s.layer_out[k];
+    r.job[k].N = s.layer_in[k];
+    r.job[k].tiles_n = (int)ceil_div(s.layer_in[k], kF32DwTile);
+    r.job[k].tile0 = tile0;
+    tile0 += (int)ceil_div(s.layer_out[k], kF32DwTile) * r.job[k].tiles_n;
     r.job[k].c = d_weights + s.w_off[k];
     r.job[k].db = d_weights + s.b_off[k];
   }
-  d.n_jobs = r.n_jobs = s.n_layers;
-  d.n_tiles = r.n_tiles = tile0;
-  d.splits = r.splits = l.splits;
-  d.k_split = l.k_split;
-  d.n = c.n;
-  d.part = r.part = reinterpret_cast<float*>(ws + l.part);
-  d.dbpart = r.dbpart = reinterpret_cast<float*>(ws + l.dbpart);
+  r.n_jobs = s.n_layers;
+  r.n_tiles = tile0;
+  r.splits = l.splits;
+  r.part = part;
+  r.dbpart = dbpart;
   r.assign = assign_dw ? 1 : 0;
   r.flag = dw_flag;
-  hipLaunchKernelGGL(k_f32_dw, dim3((unsigned)(d.n_tiles * d.splits)), dim3(256), 0, c.strm, d);
-  hipLaunchKernelGGL(k_train_dw_reduce<kF32DwTile>, dim3(kF32DwTile * kF32DwTile / 256, (unsigned)d.n_tiles), dim3(256), 0,
+  int st;
+  ScatterBeside beside;
+  if (f.narrow) {
+    F32NarrowArgs b{};
+    b.dz = c.dy;
+    b.x = x;
+    b.dx = dx;
+    b.in_dim = s.in_dim;
+    b.head_dim = s.head_dim;
+    b.n = c.n;
+    b.wpack = wpack;
+    b.part = part;
+    b.dbpart = dbpart;
+    for (int k = 0; k < s.n_layers; ++k) b.src[k] = f.pk.b_off2[k];
+    for (int k = 0; k < s.n_hidden; ++k) b.h[k] = reinterpret_cast<const float*>(ws + l.h[k]);
+    void (*const nk[])(F32NarrowArgs) = {k_f32_bwd_dw<1>, k_f32_bwd_dw<2>, k_f32_bwd_dw<3>};
+    const auto kern = nk[f.head_tiles - 1];
+    const size_t lds = f32_narrow_lds(f.head_tiles);
+    NTBC_HIP(allow_lds((const void*)kern, lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)l.splits), dim3(kF32Threads), lds, c.strm, b);
+    st = check_launch("k_f32_bwd_dw");
+    if (st == NTBC_OK) st = beside.fork(c, grid, qat, ids, dx, d_grid);
+    if (st != NTBC_OK) return st;
+  } else {
+    F32BwdArgs b{};
+    b.dz = c.dy;
+    b.in_dim = s.in_dim;
+    b.n_layers = s.n_layers;
+    b.head_dim = s.head_dim;
+    b.head_tiles = f.head_tiles;
+    b.n = c.n;
+    b.wpack = wpack;
+    for (int k = 0; k < s.n_hidden; ++k) {
+      b.h[k] = reinterpret_cast<const float*>(ws + l.h[k]);
+      b.dh[k] = reinterpret_cast<float*>(ws + l.dh[k]);
+    }
+    b.dx = dx;
+    b.ct = f.bct;
+    F32Fwd fk;
+    F32Bwd bk;
+    f32_kernels(s.hidden, f.groups, false, &fk, &bk);
+    const size_t lds = (size_t)2 * f.bct.cap * 16;
+    NTBC_HIP(allow_lds((const void*)bk, lds));
+    hipLaunchKernelGGL(bk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, b);
+    st = check_launch("k_f32_bwd");
+    if (st == NTBC_OK) st = beside.fork(c, grid, qat, ids, dx, d_grid);
+    if (st != NTBC_OK) return st;
+    F32DwArgs d{};
+    for (int k = 0; k < s.n_layers; ++k) {
+      F32DwJob& J = d.job[k];
+      J.a = k == s.n_layers - 1 ? b.dz : b.dh[k];
+      J.b = k == 0 ? x : b.h[k - 1];
+      J.M = r.job[k].M;
+      J.N = r.job[k].N;
+      J.tiles_n = r.job[k].tiles_n;
+      J.tile0 = r.job[k].tile0;
+    }
+    d.n_jobs = s.n_layers;
+    d.n_tiles = tile0;
+    d.splits = l.splits;
+    d.k_split = l.k_split;
+    d.n = c.n;
+    d.part = part;
+    d.dbpart = dbpart;
+    hipLaunchKernelGGL(k_f32_dw, dim3((unsigned)(d.n_tiles * d.splits)), dim3(256), 0, c.strm, d);
+  }
+  hipLaunchKernelGGL(k_train_dw_reduce<kF32DwTile>, dim3(kF32DwTile * kF32DwTile / 256, (unsigned)r.n_tiles), dim3(256), 0,
                      c.strm, r);
   return beside.join(c, check_launch("k_f32_dw"));
 }

@@ -21,6 +21,10 @@
 // quarter-wave register swaps for four registers).  The backward has no choices to keep: its operands stay
 // where they are, and its weights are packed with the columns in that order.
 //
+//   k_f32_bwd_dw    for the narrow networks of the two-network layout (width 64, three SELU layers, at most 16
+//                   inputs and 48 outputs) the last two as one: neither dZ nor a second read of the layer inputs
+//                   passes through memory
+//
 // What it replaces: a product a launch for every layer and direction, 64 x 64 tiles with one 16-deep slice
 // in flight, activations read back between the layers, and weight products adding to one matrix with
 // float atomics.  16,384 positions, 48-128x3-162: 380 -> 125 us of products; the matrix cores need
@@ -253,7 +257,7 @@ k_f32_fwd(F32FwdArgs a) {
 
 // dZ of a hidden layer: the products of Wᵀ with the layer above's dZ (the first `groups` groups of `in`),
 // times the activation's derivative, taken from the layer's outputs h.
-template <int H, int QI, bool SELU>
+template <int H, int QI>
 __device__ __forceinline__ void f32_bwd_layer(const F32BwdArgs& a, const f32x4_t (&in)[QI], int groups, f32x4_t (&out)[H / 16],
                                               const float* h, float* store, bool valid, u32x4* smem, int& c, int tid, int lane) {
   constexpr int CT = f32_chunk_tiles<H>();
@@ -272,7 +276,7 @@ __device__ __forceinline__ void f32_bwd_layer(const F32BwdArgs& a, const f32x4_t
       f32x4_t r;
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        r[v] = SELU ? acc[u][v] * selu_grad_of_out(hv[u][v]) : (hv[u][v] > 0.0f ? acc[u][v] : 0.0f);
+        r[v] = hv[u][v] > 0.0f ? acc[u][v] : 0.0f;
       if (valid) *reinterpret_cast<f32x4_t*>(store + 16 * t + 4 * g) = r;
       out[t] = r;
     }
@@ -282,7 +286,7 @@ __device__ __forceinline__ void f32_bwd_layer(const F32BwdArgs& a, const f32x4_t
   }
 }
 
-template <int H, int KQ, bool SELU>
+template <int H, int KQ>
 __global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(H == 256 ? 2 : (H == 128 ? 3 : 4))))
 k_f32_bwd(F32BwdArgs a) {
   constexpr int CT = f32_chunk_tiles<H>(), Q = H / 16;
@@ -301,14 +305,14 @@ k_f32_bwd(F32BwdArgs a) {
       head[q] = q < a.head_tiles ? f32_row4(a.dz + pc * a.head_dim, 16 * q + 4 * g, a.head_dim) : f32x4_t{};
     fwait_dma();
     __syncthreads();
-    f32_bwd_layer<H, kF32HeadTiles, SELU>(a, head, a.head_tiles, out, a.h[layer] + pc * H, a.dh[layer] + pc * H, valid, smem, c,
+    f32_bwd_layer<H, kF32HeadTiles>(a, head, a.head_tiles, out, a.h[layer] + pc * H, a.dh[layer] + pc * H, valid, smem, c,
                                           tid, lane);
   }
   for (--layer; layer >= 0; --layer) {
     f32x4_t in[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) in[q] = out[q];
-    f32_bwd_layer<H, Q, SELU>(a, in, Q, out, a.h[layer] + pc * H, a.dh[layer] + pc * H, valid, smem, c, tid, lane);
+    f32_bwd_layer<H, Q>(a, in, Q, out, a.h[layer] + pc * H, a.dh[layer] + pc * H, valid, smem, c, tid, lane);
   }
 #pragma unroll
   for (int t0 = 0; t0 < KQ; t0 += CT) {
@@ -413,5 +417,263 @@ __global__ void __launch_bounds__(256) k_f32_dw(F32DwArgs a) {
       for (int r = 0; r < kF32DwK; ++r) t += As[0][r][tid];
       a.dbpart[((int64_t)tile * a.splits + split) * kF32DwTile + tid] = t;
     }
+  }
+}
+
+// ------------------------------------------------------------------------------------------ width 64: backward and dW
+// dZ of the head -> dX and dW, db of every layer, for the networks of the two-network layout.  Their layers are
+// so narrow that the two kernels above are bound by memory (65,536 * 16 texels: 0.8 GB of dZ written, read back
+// beside the layer inputs' second 0.8 GB; 0.40 + 0.59 ms, where the matrix cores need 0.28 for both).  Here all
+// weights stay in LDS and a wave keeps the weight products of its positions in accumulators: 10 to 13 tiles of
+// 16 x 16 a layer column, 176 registers with 32 outputs, so one wave a SIMD with all 512
+// (a step of 65,536 blocks: 0.98 ms -> 0.51, the matrix cores busy for 0.29).  A workgroup a CU takes
+// groups of 16 positions in turn; the next group's rows are loaded under this one's products.  dZ and the layer
+// inputs pass through a patch of LDS per wave, from a position's row a lane to a neuron a lane.  Nothing in the
+// loop waits for another wave.  At the end the four waves' sums are added in order and each workgroup
+// writes one partial, which k_train_dw_reduce adds in workgroup order.
+constexpr int kF32NarrowBlocks = 256;  // a CU each
+constexpr int kF32NarrowLd = 72;       // floats between the rows of a patch: rows and columns both over the banks
+constexpr int kF32NarrowHidden = 3, kF32NarrowHeadTiles = 3;  // eight BC1 textures: 48 endpoint values
+
+struct F32NarrowArgs {
+  const float *dz, *x;  // [n][head_dim], [n][in_dim]
+  const float* h[kF32NarrowHidden];
+  float* dx;
+  int in_dim, head_dim;
+  int64_t n;
+  const u32x4* wpack;
+  int src[kF32NarrowHidden + 1];  // u32x4 offsets of the layers' transposed weights
+  float *part, *dbpart;           // [layer][gridDim.x][64 * 64], [layer][gridDim.x][64]
+};
+
+constexpr int f32_narrow_units(int ht) { return (4 * ht + 2 * 16 + 4) * 64; }
+constexpr size_t f32_narrow_lds(int ht) {
+  return (size_t)f32_narrow_units(ht) * 16 + (size_t)kF32Waves * 2 * 16 * kF32NarrowLd * 4;
+}
+
+template <int HT>
+struct F32Rows {  // of one group: a lane's four of every sixteen elements
+  f32x4_t dz[HT], x, h[kF32NarrowHidden][4];
+};
+
+template <int HT>
+__device__ __forceinline__ void f32_narrow_load(const F32NarrowArgs& a, int64_t grp, int lane, F32Rows<HT>* r) {
+  const int j = lane & 15, g = lane >> 4;
+  const int64_t p = grp * 16 + j, pc = p < a.n ? p : a.n - 1;
+#pragma unroll
+  for (int q = 0; q < HT; ++q) {
+    r->dz[q] = f32_row4(a.dz + pc * a.head_dim, 16 * q + 4 * g, a.head_dim);
+    if (p >= a.n) r->dz[q] = f32x4_t{};  // and with it every dZ of the lane's position
+  }
+  r->x = f32_row4(a.x + pc * a.in_dim, 4 * g, a.in_dim);
+#pragma unroll
+  for (int k = 0; k < kF32NarrowHidden; ++k)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) r->h[k][t] = *reinterpret_cast<const f32x4_t*>(a.h[k] + pc * 64 + 16 * t + 4 * g);
+}
+
+template <int T>
+__device__ __forceinline__ void f32_patch_put(float* patch, const f32x4_t (&v)[T], int lane) {
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+    *reinterpret_cast<f32x4_t*>(patch + (lane & 15) * kF32NarrowLd + 16 * t + 4 * (lane >> 4)) = v[t];
+}
+
+// The patches are one wave's: its LDS accesses complete in order, so only the compiler has to keep them so.
+__device__ __forceinline__ void f32_patch_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Both operands of the weight products over a patch's 16 positions, K-step s = positions 4s .. 4s+3.
+template <int MT, int NT>
+struct F32Frags {
+  float a[4][MT], b[4][NT];
+};
+
+template <int MT, int NT>
+__device__ __forceinline__ void f32_patch_get(const float* z, const float* h, int lane, F32Frags<MT, NT>* f) {
+  const int li = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) f->a[s][i] = z[(4 * s + g) * kF32NarrowLd + 16 * i + li];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) f->b[s][k] = h[(4 * s + g) * kF32NarrowLd + 16 * k + li];
+  }
+}
+
+// acc[i][k] += dZ^T H, bs the lane's share of the row sums of dZ^T.
+template <int MT, int NT>
+__device__ __forceinline__ void f32_patch_dw(const F32Frags<MT, NT>& f, f32x4_t (&acc)[MT][NT], float (&bs)[MT]) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      bs[i] += f.a[s][i];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[s][i], f.b[s][k], acc[i][k], 0, 0, 0);
+    }
+}
+
+// T tiles over Q groups of 16 K values, as f32_products, the next group's weights read under this one's products.
+template <int T, int Q>
+__device__ __forceinline__ void f32_narrow_products(const u32x4* wb, const f32x4_t (&b)[Q], int lane, f32x4_t (&acc)[T]) {
+  f32x4_t w[2][T];
+#pragma unroll
+  for (int u = 0; u < T; ++u) {
+    acc[u] = f32x4_t{};
+    w[0][u] = __builtin_bit_cast(f32x4_t, wb[u * Q * 64 + lane]);
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (q + 1 < Q)
+#pragma unroll
+      for (int u = 0; u < T; ++u) w[(q + 1) & 1][u] = __builtin_bit_cast(f32x4_t, wb[(u * Q + q + 1) * 64 + lane]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int u = 0; u < T; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q & 1][u][v], b[q][v], acc[u], 0, 0, 0);
+    if (q + 1 < Q) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// dZ of a hidden layer from the layer above's, with all four tiles of its weights at w.
+template <int Q>
+__device__ __forceinline__ void f32_narrow_layer(const u32x4* w, const f32x4_t (&in)[Q], const f32x4_t (&h)[4], int lane,
+                                                 f32x4_t (&out)[4]) {
+  f32x4_t acc[4];
+  f32_narrow_products<4, Q>(w, in, lane, acc);
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) out[t][v] = acc[t][v] * selu_grad_of_out(h[t][v]);
+}
+
+// The sums of a layer over the workgroup, wave 0's first, in wave 0's registers; buf holds a wave's sums.
+template <int MT, int NT>
+__device__ __forceinline__ void f32_wave_put(f32x4_t* buf, int& o, int lane, const f32x4_t (&acc)[MT][NT], const float (&bs)[MT]) {
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) buf[(o++) * 64 + lane] = acc[i][k];
+    buf[(o++) * 64 + lane] = f32x4_t{bs[i], 0.0f, 0.0f, 0.0f};
+  }
+}
+
+template <int MT, int NT>
+__device__ __forceinline__ void f32_wave_add(const f32x4_t* buf, int& o, int lane, f32x4_t (&acc)[MT][NT], float (&bs)[MT]) {
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) acc[i][k] += buf[(o++) * 64 + lane];
+    bs[i] += buf[(o++) * 64 + lane][0];
+  }
+}
+
+template <int MT, int NT>
+__device__ __forceinline__ void f32_narrow_part(const F32NarrowArgs& a, int layer, int lane, const f32x4_t (&acc)[MT][NT],
+                                                const float (&bs)[MT]) {
+  const int li = lane & 15, g = lane >> 4;
+  const int64_t slot = (int64_t)layer * gridDim.x + blockIdx.x;
+  float* part = a.part + slot * 4096;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part[(16 * i + 4 * g + v) * 64 + 16 * k + li] = acc[i][k][v];
+    float b = bs[i];
+    b += __shfl_xor(b, 16);
+    b += __shfl_xor(b, 32);
+    if (g == 0) a.dbpart[slot * 64 + 16 * i + li] = b;
+  }
+}
+
+template <int HT>
+__global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(1, 1))) k_f32_bwd_dw(F32NarrowArgs a) {
+  extern __shared__ u32x4 smem[];
+  constexpr int kW2 = 4 * HT * 64, kW1 = kW2 + 16 * 64, kW0 = kW1 + 16 * 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int u = wave; u < f32_narrow_units(HT) / 64; u += kF32Waves) {
+    const int at = 64 * u;
+    const u32x4* from = a.wpack + (at < kW2 ? a.src[3] + at : at < kW1 ? a.src[2] + at - kW2 : at < kW0 ? a.src[1] + at - kW1 : a.src[0] + at - kW0);
+    __builtin_amdgcn_global_load_lds(from + lane, (__attribute__((address_space(3))) void*)(smem + at), 16, 0, 0);
+  }
+  float* zp = reinterpret_cast<float*>(smem + f32_narrow_units(HT)) + wave * 2 * 16 * kF32NarrowLd;
+  float* hp = zp + 16 * kF32NarrowLd;
+  f32x4_t w3[HT][4] = {}, w2[4][4] = {}, w1[4][4] = {}, w0[4][1] = {};
+  float b3[HT] = {}, b2[4] = {}, b1[4] = {}, b0[4] = {};
+  const int64_t groups = (a.n + 15) / 16, step = (int64_t)gridDim.x * kF32Waves;
+  int64_t grp = (int64_t)blockIdx.x * kF32Waves + wave;
+  F32Rows<HT> next{};
+  if (grp < groups) f32_narrow_load(a, grp, lane, &next);
+  fwait_dma();
+  __syncthreads();
+  for (; grp < groups; grp += step) {
+    const F32Rows<HT> r = next;
+    f32_narrow_load(a, grp + step < groups ? grp + step : grp, lane, &next);
+    f32x4_t d2[4], d1[4], d0[4], dx[1];
+    const f32x4_t x[1] = {r.x};
+    f32_patch_put(zp, r.dz, lane);
+    f32_patch_put(hp, r.h[2], lane);
+    f32_patch_order();
+    F32Frags<HT, 4> f3;
+    f32_patch_get(zp, hp, lane, &f3);
+    f32_narrow_layer(smem, r.dz, r.h[2], lane, d2);
+    f32_patch_dw(f3, w3, b3);
+    f32_patch_order();
+    f32_patch_put(zp, d2, lane);
+    f32_patch_put(hp, r.h[1], lane);
+    f32_patch_order();
+    F32Frags<4, 4> f2;
+    f32_patch_get(zp, hp, lane, &f2);
+    f32_narrow_layer(smem + kW2, d2, r.h[1], lane, d1);
+    f32_patch_dw(f2, w2, b2);
+    f32_patch_order();
+    f32_patch_put(zp, d1, lane);
+    f32_patch_put(hp, r.h[0], lane);
+    f32_patch_order();
+    F32Frags<4, 4> f1;
+    f32_patch_get(zp, hp, lane, &f1);
+    f32_narrow_layer(smem + kW1, d1, r.h[0], lane, d0);
+    f32_patch_dw(f1, w1, b1);
+    f32_patch_order();
+    f32_patch_put(zp, d0, lane);
+    f32_patch_put(hp, x, lane);
+    f32_patch_order();
+    F32Frags<4, 1> f0;
+    f32_patch_get(zp, hp, lane, &f0);
+    f32_narrow_products<1, 4>(smem + kW0, d0, lane, dx);
+    f32_patch_dw(f0, w0, b0);
+    f32_patch_order();
+    const int64_t p = grp * 16 + (lane & 15);
+    if (p < a.n) f32_put4(a.dx + p * a.in_dim, 4 * (lane >> 4), a.in_dim, dx[0]);
+  }
+  f32x4_t* buf = reinterpret_cast<f32x4_t*>(smem);
+  static_assert((size_t)(HT * 5 + 20 + 20 + 8) * 64 * 16 <= f32_narrow_lds(HT), "a wave's sums");
+  for (int w = 1; w < kF32Waves; ++w) {
+    __syncthreads();
+    int o = 0;
+    if (wave == w) {
+      f32_wave_put(buf, o, lane, w3, b3);
+      f32_wave_put(buf, o, lane, w2, b2);
+      f32_wave_put(buf, o, lane, w1, b1);
+      f32_wave_put(buf, o, lane, w0, b0);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      f32_wave_add(buf, o, lane, w3, b3);
+      f32_wave_add(buf, o, lane, w2, b2);
+      f32_wave_add(buf, o, lane, w1, b1);
+      f32_wave_add(buf, o, lane, w0, b0);
+    }
+  }
+  if (wave == 0) {
+    f32_narrow_part(a, 3, lane, w3, b3);
+    f32_narrow_part(a, 2, lane, w2, b2);
+    f32_narrow_part(a, 1, lane, w1, b1);
+    f32_narrow_part(a, 0, lane, w0, b0);
   }
 }
