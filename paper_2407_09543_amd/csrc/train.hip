@@ -2239,41 +2239,55 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   }
 }
 
-// dW (and db) += the sum of the partial TS x TS tiles over the K ranges, in K-range order (= with a.assign);
-// one thread per element of a tile.
+// dW (and db) += the sum of the partial TS x TS tiles over the K ranges (= with a.assign), in an order that the
+// number of ranges fixes: 256 / dw_reduce_el threads an element, each a run of the ranges in order, their sums then
+// in order.  One thread an element left the reads to a chain each and the chip mostly idle: 64 x 64 tiles in 256
+// ranges 20 us -> 6.5 (beside the grid scatter 103), in 86 ranges 9.8 -> 5.4; 128 x 128 tiles in a few dozen
+// ranges 11.2 -> 8.6 (with runs as short as the smaller tiles' 14.7).
+template <int TS>
+constexpr int dw_reduce_el() {
+  return TS == 64 ? 32 : 128;
+}
+
+template <int TS>
+dim3 dw_reduce_grid(int tiles) {
+  return dim3((unsigned)((TS * TS + TS + dw_reduce_el<TS>() - 1) / dw_reduce_el<TS>()), (unsigned)tiles);
+}
+
 template <int TS>
 __global__ void __launch_bounds__(256) k_train_dw_reduce(DwArgs a) {
+  constexpr int kEl = dw_reduce_el<TS>(), kRuns = 256 / kEl;
+  __shared__ float run[kRuns][kEl];
   const int tile = blockIdx.y;
   int jb = 0;
   while (jb + 1 < a.n_jobs && tile >= a.job[jb + 1].tile0) ++jb;
   const DwJob& J = a.job[jb];
-  const int lt = tile - J.tile0;
-  const int tm = lt / J.tiles_n, tn = lt % J.tiles_n;
-  const float* part = a.part + (int64_t)tile * a.splits * (TS * TS);
-  const int e = blockIdx.x * 256 + threadIdx.x;  // gridDim.x = TS * TS / 256
-  const int r = e / TS, col = e % TS;
-  const int m = tm * TS + r, nn = tn * TS + col;
-  bool bad = false;
-  if (m < J.M && nn < J.N) {
-    float s = 0.0f;
-    // unrolled so that eight loads are in flight; the additions stay in split order
+  const int lt = tile - J.tile0, tm = lt / J.tiles_n, tn = lt % J.tiles_n;
+  // elements of the tile, then (first tile of a row) its TS row sums
+  const int el = threadIdx.x % kEl, e = blockIdx.x * kEl + el;
+  const bool bias = e >= TS * TS;
+  const int m = tm * TS + (bias ? e - TS * TS : e / TS), nn = bias ? 0 : tn * TS + e % TS;
+  const bool in = m < J.M && (bias ? tn == 0 : nn < J.N);
+  const int g = threadIdx.x / kEl, per = (a.splits + kRuns - 1) / kRuns;
+  const int k0 = g * per, k1 = k0 + per < a.splits ? k0 + per : a.splits;
+  const int64_t stride = bias ? TS : TS * TS;
+  const float* part = (bias ? a.dbpart + (e - TS * TS) : a.part + e) + (int64_t)tile * a.splits * stride;
+  float s = 0.0f;
+  if (in) {
+    // unrolled so that eight loads are in flight; the additions stay in order
 #pragma unroll 8
-    for (int k = 0; k < a.splits; ++k) s += part[(int64_t)k * (TS * TS) + e];
-    float* dst = J.c + (int64_t)m * J.N + nn;
+    for (int k = k0; k < k1; ++k) s += part[k * stride];
+  }
+  run[g][el] = s;
+  __syncthreads();
+  bool bad = false;
+  if (g == 0 && in) {
+#pragma unroll
+    for (int k = 1; k < kRuns; ++k) s += run[k][el];
+    float* dst = bias ? J.db + m : J.c + (int64_t)m * J.N + nn;
     const float v = a.assign ? s : *dst + s;
     *dst = v;
     bad = !isfinite(v);
-  }
-  if (tn == 0 && blockIdx.x == 0 && threadIdx.x < TS) {
-    const int mr = tm * TS + threadIdx.x;
-    if (mr < J.M) {
-      float s = 0.0f;
-#pragma unroll 8
-      for (int k = 0; k < a.splits; ++k) s += a.dbpart[((int64_t)tile * a.splits + k) * TS + threadIdx.x];
-      const float v = a.assign ? s : J.db[mr] + s;
-      J.db[mr] = v;
-      bad |= !isfinite(v);
-    }
   }
   if (a.flag != nullptr && __ballot(bad) != 0ull && (threadIdx.x & 63) == 0) atomicExch(a.flag, 1.0f);
 }
@@ -2992,7 +3006,7 @@ int fused_backward(Ctx& c, const FusedPlan& f, const float* grid, bool qat, cons
   hipLaunchKernelGGL(k_train_dw, dim3((unsigned)(d.n_tiles * d.splits)), dim3(256), 0, c.strm, d);
   st = check_launch("k_train_dw");
   if (st == NTBC_OK) {
-    hipLaunchKernelGGL(k_train_dw_reduce<128>, dim3(64, (unsigned)d.n_tiles), dim3(256), 0, c.strm, d);
+    hipLaunchKernelGGL(k_train_dw_reduce<128>, dw_reduce_grid<128>(d.n_tiles), dim3(256), 0, c.strm, d);
     st = check_launch("k_train_dw_reduce");
   }
   return beside.join(c, st);
@@ -3249,8 +3263,7 @@ int f32_backward(Ctx& c, const F32Plan& f, const float* grid, bool qat, const in
     d.dbpart = dbpart;
     hipLaunchKernelGGL(k_f32_dw, dim3((unsigned)(d.n_tiles * d.splits)), dim3(256), 0, c.strm, d);
   }
-  hipLaunchKernelGGL(k_train_dw_reduce<kF32DwTile>, dim3(kF32DwTile * kF32DwTile / 256, (unsigned)r.n_tiles), dim3(256), 0,
-                     c.strm, r);
+  hipLaunchKernelGGL(k_train_dw_reduce<kF32DwTile>, dw_reduce_grid<kF32DwTile>(r.n_tiles), dim3(256), 0, c.strm, r);
   return beside.join(c, check_launch("k_f32_dw"));
 }
 
