@@ -1122,9 +1122,9 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in
   }
 }
 
-// Four lanes per (texture, position).  A wave works on one texture of 16 positions at a time; a block of four
+// Four lanes per (texture, position).  A wave works on one texture of 16 positions at a time; a team of four
 // waves covers 1 << g_shift groups of 16 positions, and its waves take the (texture, group) pairs in turn,
-// texture by texture.  Four waves, because a block's waves go to the CU's SIMDs in turn: with one wave per texture
+// texture by texture.  A block is one, two or four teams.  Four waves, because a block's waves go to the CU's SIMDs in turn: with one wave per texture
 // (five) the first SIMD got two of each block, two blocks filled it, and it had 40% of the CU's work.  The colours
 // of the positions come into LDS by direct copies, each lane replaces a value by its gradient there, and the
 // rows are stored in whole lines; in place, a lane's values 4 C bytes apart were a request of their own each
@@ -1132,7 +1132,10 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in
 // (palette distances, softmax and straight-through gradients: some 1,500 VALU instructions per texture of 16
 // positions, 64 exponentials among them).  65,536 positions of five textures: 113 us with a wave per texture
 // and values in place, 83 so, 77 with the sign and the hard choice below.  The loss sums are reduced per block
-// and added with one atomic per block and loss (same-address atomics from every wave serialise in L2).
+// and added with one atomic per block and loss (same-address atomics from every wave serialise in L2, and each
+// addition rounds the sum).
+constexpr int kLossWaves = 4, kLossTeams = 4;
+
 // Blocks that are resident at once with waves_per_block waves each, as a CU holds 16 of their waves at four waves
 // per SIMD, and no more than the positions fill.
 int loss_blocks(int64_t n, int waves_per_block) {
@@ -1219,31 +1222,33 @@ __device__ __forceinline__ void loss_finish(const LossArgs& a, float le, float l
 }
 
 // FMT = 3 or 1: materials of BC1 or of BC4 textures only; 0: of both (a wave-uniform branch).
-constexpr int kLossThreads = 256;
-
 template <int FMT>
-__global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(4))) k_loss_grad(LossArgs a) {
-  __shared__ float part[kLossThreads / 64][4];
-  __shared__ int part_bad[kLossThreads / 64];
+__global__ void __launch_bounds__(kLossWaves * 64 * kLossTeams) __attribute__((amdgpu_waves_per_eu(4))) k_loss_grad(LossArgs a) {
+  __shared__ float part[kLossWaves * kLossTeams][4];
+  __shared__ int part_bad[kLossWaves * kLossTeams];
   float le = 0.0f, lc = 0.0f, lcde = 0.0f, lcdc = 0.0f;
   bool bad = false;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  extern __shared__ float tile[];
-  const int S = loss_row(a.C), cols = 16 * a.C, per = 16 << a.g_shift;
+  extern __shared__ float tiles[];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), team = w / kLossWaves, wave = w % kLossWaves;
+  const int lane = threadIdx.x & 63, sub = lane & 3, q = lane >> 2;
+  const int S = loss_row(a.C), cols = 16 * a.C, per = 16 << a.g_shift, items = a.n_textures << a.g_shift;
+  const int64_t block = (int64_t)per * (blockDim.x / (64 * kLossWaves));
+  float* tile = tiles + team * per * S;
   const bool own = a.g_shift == 2;  // a wave's rows are its own: nothing to wait for
-  const int r0 = own ? 16 * wave : wave, dr = own ? 1 : kLossThreads / 64;
-  for (int64_t p0 = (int64_t)blockIdx.x * per; p0 < a.n; p0 += (int64_t)gridDim.x * per) {
-    const int rows = a.n - p0 < per ? (int)(a.n - p0) : per, r1 = own ? min(rows, r0 + 16) : rows;
+  const int r0 = own ? 16 * wave : wave, dr = own ? 1 : kLossWaves;
+  for (int64_t b0 = blockIdx.x * block; b0 < a.n; b0 += gridDim.x * block) {
+    const int64_t p0 = b0 + team * per;
+    const int rows = a.n - p0 < per ? (int)(a.n > p0 ? a.n - p0 : 0) : per, r1 = own ? min(rows, r0 + 16) : rows;
     for (int r = r0; r < r1; r += dr)
       for (int c = 0; c < cols; c += 64)
         if (c + lane < cols)
           __builtin_amdgcn_global_load_lds(a.y + (p0 + r) * a.ld + a.E + c + lane,
                                            (__attribute__((address_space(3))) void*)(tile + r * S + c), 4, 0, 0);
-    const int items = a.n_textures << a.g_shift, sub = lane & 3, q = lane >> 2;
     LossIn in{};
     const auto load = [&](int i, LossIn* to) {
-      const int64_t p = p0 + 16 * (i & ((1 << a.g_shift) - 1)) + q;
-      if (i >= items || p >= a.n) return;
+      const int row = 16 * (i & ((1 << a.g_shift) - 1)) + q;
+      if (i >= items || row >= rows) return;
+      const int64_t p = p0 + row;
       const int k = i >> a.g_shift, id = clamp_id(a.ids[p], a.n_positions);
       if (FMT == 3 || (FMT == 0 && k < a.n_bc1)) loss_load<3>(a, p, a.tex_of[k], id, sub, to);
       else loss_load<1>(a, p, a.tex_of[k], id, sub, to);
@@ -1251,13 +1256,13 @@ __global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_
     load(wave, &in);
     dma_arrived();
     if (!own) __syncthreads();
-    for (int i = wave; i < items; i += kLossThreads / 64) {
+    for (int i = wave; i < items; i += kLossWaves) {
       const int row = 16 * (i & ((1 << a.g_shift) - 1)) + q, k = i >> a.g_shift;
       if (FMT == 3 || (FMT == 0 && k < a.n_bc1))
         loss_group<3>(a, in, tile + row * S, p0 + row, row < rows, a.tex_of[k], sub, le, lc, lcde, lcdc, bad);
       else
         loss_group<1>(a, in, tile + row * S, p0 + row, row < rows, a.tex_of[k], sub, le, lc, lcde, lcdc, bad);
-      load(i + kLossThreads / 64, &in);
+      load(i + kLossWaves, &in);
     }
     if (!own) __syncthreads();
     for (int r = r0; r < r1; r += dr)
@@ -2637,19 +2642,25 @@ int loss_grad(const Shape& s, const ntbc_targets* t, const float* heads, const i
   a.n_bc1 = n_tex;
   for (int i = 0; i < s.n_textures; ++i)
     if (s.formats[i] != NTBC_BC1) a.tex_of[n_tex++] = i;
-  // One group a block while every block is resident: the textures of a position side by side is the shortest way
-  // (16,384 positions of five textures 30 us, with four groups a block 38).  Beyond that, the groups that give the
-  // waves equal shares, as far as four blocks of a CU have LDS for them (65,536 positions: five textures 90 us with
+  // One group a team while the teams are resident: the textures of a position side by side is the shortest way
+  // (16,384 positions of five textures 28 us, with four groups a team 38).  Beyond that, the groups that give the
+  // waves equal shares, as far as four teams of a CU have LDS for them (65,536 positions: five textures 90 us with
   // one group, 78 with two, 77 with four; six textures 95, 86, 91).
-  const int64_t groups = ceil_div(n, 16), resident = loss_blocks((int64_t)1 << 40, kLossThreads / 64);
-  if (groups > resident)
-    while ((s.n_textures << a.g_shift) % (kLossThreads / 64) != 0 && loss_lds(a.g_shift + 1, s.channels) <= 40 * 1024) ++a.g_shift;
-  const size_t lds = loss_lds(a.g_shift, s.channels);
-  const dim3 block(kLossThreads);
-  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(groups, (int64_t)1 << a.g_shift), 8 * resident)));
-  if (a.n_bc1 == 0) hipLaunchKernelGGL(k_loss_grad<1>, grid, block, lds, strm, a);
-  else if (a.n_bc1 == n_tex) hipLaunchKernelGGL(k_loss_grad<3>, grid, block, lds, strm, a);
-  else hipLaunchKernelGGL(k_loss_grad<0>, grid, block, lds, strm, a);
+  const int64_t groups = ceil_div(n, 16), cus = loss_blocks((int64_t)1 << 40, 16);
+  if (groups > 4 * cus)
+    while ((s.n_textures << a.g_shift) % kLossWaves != 0 && loss_lds(a.g_shift + 1, s.channels) <= 39 * 1024) ++a.g_shift;
+  // Teams share a block where there are more than 512, for fewer additions to the loss sums (one team a block left
+  // the sum of 2,048 off by 1.1e-6; 512 and 256 blocks by 3e-7, as the one wave per texture did).  Four only where
+  // each has several groups or more than one turn: they wait for each other (16,384 positions of five textures 33 us,
+  // with two a block 28).
+  const int64_t need = ceil_div(groups, (int64_t)1 << a.g_shift);
+  const int teams = groups > 4 * cus && need >= 4 * cus ? kLossTeams : (need > 2 * cus ? 2 : 1);
+  const size_t lds = teams * loss_lds(a.g_shift, s.channels);
+  const dim3 block(64 * kLossWaves * teams);
+  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(need, teams), teams == kLossTeams ? cus : 2 * cus)));
+  void (*const kern)(LossArgs) = a.n_bc1 == 0 ? k_loss_grad<1> : a.n_bc1 == n_tex ? k_loss_grad<3> : k_loss_grad<0>;
+  NTBC_HIP(allow_lds((const void*)kern, lds));
+  hipLaunchKernelGGL(kern, grid, block, lds, strm, a);
   return check_launch("k_loss_grad");
 }
 
