@@ -3119,16 +3119,15 @@ typedef void (*F32Bwd)(F32BwdArgs);
 template <int H>
 void f32_kernels_of(int groups, F32Fwd* fk, F32Bwd* bk) {
   switch (groups) {
-    case 1: *fk = k_f32_fwd<H, 1, false>, *bk = k_f32_bwd<H, 1>; break;
-    case 2: *fk = k_f32_fwd<H, 2, false>, *bk = k_f32_bwd<H, 2>; break;
-    case 3: *fk = k_f32_fwd<H, 3, false>, *bk = k_f32_bwd<H, 3>; break;
-    default: *fk = k_f32_fwd<H, 4, false>, *bk = k_f32_bwd<H, 4>; break;
+    case 1: *fk = k_f32_fwd<H, 1>, *bk = k_f32_bwd<H, 1>; break;
+    case 2: *fk = k_f32_fwd<H, 2>, *bk = k_f32_bwd<H, 2>; break;
+    case 3: *fk = k_f32_fwd<H, 3>, *bk = k_f32_bwd<H, 3>; break;
+    default: *fk = k_f32_fwd<H, 4>, *bk = k_f32_bwd<H, 4>; break;
   }
 }
 
-void f32_kernels(int hid, int groups, bool selu, F32Fwd* fk, F32Bwd* bk) {
-  if (selu) *fk = k_f32_fwd<64, 1, true>, *bk = nullptr;  // k_f32_bwd_dw
-  else if (hid == 64) f32_kernels_of<64>(groups, fk, bk);
+void f32_kernels(int hid, int groups, F32Fwd* fk, F32Bwd* bk) {
+  if (hid == 64) f32_kernels_of<64>(groups, fk, bk);
   else if (hid == 128) f32_kernels_of<128>(groups, fk, bk);
   else f32_kernels_of<256>(groups, fk, bk);
 }
@@ -3152,6 +3151,24 @@ int f32_forward(Ctx& c, const F32Plan& f, const float* grid, const float* weight
   pk.zero5 = zero_losses;
   hipLaunchKernelGGL(k_pack_f32t, dim3(16, 2 * s.n_layers), dim3(256), 0, c.strm, pk);
   const FeatArgs fa = feat_args(s, grid, qat ? c.stats() : nullptr, ids, c.n, reinterpret_cast<float*>(ws + l.x));
+  if (f.narrow) {
+    F32NarrowFwdArgs a{};
+    a.f = fa;
+    a.in_dim = s.in_dim;
+    a.head_dim = s.head_dim;
+    a.head_tiles = f.head_tiles;
+    a.n_bias = f.n_bias;
+    a.wpack = pk.pack;
+    a.bias = pk.bias;
+    for (int k = 0; k < s.n_layers; ++k) a.src[k] = pk.f_off[k], a.bias_off[k] = pk.bias_off[k];
+    for (int k = 0; k < s.n_hidden; ++k) a.h[k] = reinterpret_cast<float*>(ws + l.h[k]);
+    a.y = y;
+    const size_t lds = (size_t)f32_narrow_fwd_units(f.head_tiles) * 16 + (size_t)f.n_bias * 4;
+    NTBC_HIP(allow_lds((const void*)k_f32_fwd_narrow, lds));
+    const int64_t blocks = std::min<int64_t>(2 * kF32NarrowBlocks, ceil_div(ceil_div(c.n, 16), kF32NarrowWaves));
+    hipLaunchKernelGGL(k_f32_fwd_narrow, dim3((unsigned)blocks), dim3(64 * kF32NarrowWaves), lds, c.strm, a);
+    return check_launch("k_f32_fwd_narrow");
+  }
   hipLaunchKernelGGL(k_features, dim3((unsigned)ceil_div(c.n * s.n_levels * s.n_features, kBlock)), dim3(kBlock), 0, c.strm, fa);
   st = check_launch("k_features");
   if (st != NTBC_OK) return st;
@@ -3171,7 +3188,7 @@ int f32_forward(Ctx& c, const F32Plan& f, const float* grid, const float* weight
   a.ct = f.fct;
   F32Fwd fk;
   F32Bwd bk;
-  f32_kernels(s.hidden, f.groups, c.selu, &fk, &bk);
+  f32_kernels(s.hidden, f.groups, &fk, &bk);
   const size_t lds = (size_t)2 * f.fct.cap * 16 + (size_t)f.n_bias * 4;
   NTBC_HIP(allow_lds((const void*)fk, lds));
   hipLaunchKernelGGL(fk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, a);
@@ -3248,7 +3265,7 @@ int f32_backward(Ctx& c, const F32Plan& f, const float* grid, bool qat, const in
     b.ct = f.bct;
     F32Fwd fk;
     F32Bwd bk;
-    f32_kernels(s.hidden, f.groups, false, &fk, &bk);
+    f32_kernels(s.hidden, f.groups, &fk, &bk);
     const size_t lds = (size_t)2 * f.bct.cap * 16;
     NTBC_HIP(allow_lds((const void*)bk, lds));
     hipLaunchKernelGGL(bk, dim3((unsigned)ceil_div(c.n, kF32Pos)), dim3(kF32Threads), lds, c.strm, b);

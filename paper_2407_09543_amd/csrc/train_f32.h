@@ -21,9 +21,10 @@
 // quarter-wave register swaps for four registers).  The backward has no choices to keep: its operands stay
 // where they are, and its weights are packed with the columns in that order.
 //
-//   k_f32_bwd_dw    for the narrow networks of the two-network layout (width 64, three SELU layers, at most 16
-//                   inputs and 48 outputs) the last two as one: neither dZ nor a second read of the layer inputs
-//                   passes through memory
+//   k_f32_fwd_narrow, k_f32_bwd_dw
+//                   for the narrow networks of the two-network layout (width 64, three SELU layers, at most 16
+//                   inputs and 48 outputs) the features and the forward as one, and the last two as one: neither dZ nor
+//                   a second read of the layer inputs passes through memory
 //
 // What it replaces: a product a launch for every layer and direction, 64 x 64 tiles with one 16-deep slice
 // in flight, activations read back between the layers, and weight products adding to one matrix with
@@ -180,7 +181,7 @@ __device__ __forceinline__ void f32_products(const u32x4* wb, const f32x4_t (&b)
 
 // One hidden layer: products, bias, activation; the outputs go to `store` (row-major, the lane's row) and,
 // in natural order, into `out`.
-template <int H, int Q, bool SELU>
+template <int H, int Q>
 __device__ __forceinline__ void f32_fwd_layer(const F32FwdArgs& a, const f32x4_t (&in)[Q], f32x4_t (&out)[H / 16], const float* bl,
                                               float* store, bool valid, u32x4* smem, int& c, int tid, int lane) {
   constexpr int CT = f32_chunk_tiles<H>();
@@ -199,7 +200,7 @@ __device__ __forceinline__ void f32_fwd_layer(const F32FwdArgs& a, const f32x4_t
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float z = acc[u][v] + bv[v];
-        r[v] = SELU ? selu_f(z) : (z < 0.0f ? 0.0f : z);  // ReLU that keeps NaN
+        r[v] = z < 0.0f ? 0.0f : z;  // ReLU that keeps NaN
       }
       if (valid) *reinterpret_cast<f32x4_t*>(store + 16 * t + 4 * g) = r;
       out[t] = f32_natural(r);
@@ -210,7 +211,7 @@ __device__ __forceinline__ void f32_fwd_layer(const F32FwdArgs& a, const f32x4_t
   }
 }
 
-template <int H, int KQ, bool SELU>
+template <int H, int KQ>
 __global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(H == 256 ? 2 : (H == 128 ? 3 : 4))))
 k_f32_fwd(F32FwdArgs a) {
   constexpr int CT = f32_chunk_tiles<H>(), Q = H / 16;
@@ -229,9 +230,9 @@ k_f32_fwd(F32FwdArgs a) {
   __syncthreads();
   int c = 0;
   f32x4_t in[Q], out[Q];
-  f32_fwd_layer<H, KQ, SELU>(a, x0, in, bias_s + a.bias_off[0], a.h[0] + pc * H, valid, smem, c, tid, lane);
+  f32_fwd_layer<H, KQ>(a, x0, in, bias_s + a.bias_off[0], a.h[0] + pc * H, valid, smem, c, tid, lane);
   for (int layer = 1; layer < a.n_layers - 1; ++layer) {
-    f32_fwd_layer<H, Q, SELU>(a, in, out, bias_s + a.bias_off[layer], a.h[layer] + pc * H, valid, smem, c, tid, lane);
+    f32_fwd_layer<H, Q>(a, in, out, bias_s + a.bias_off[layer], a.h[layer] + pc * H, valid, smem, c, tid, lane);
 #pragma unroll
     for (int q = 0; q < Q; ++q) in[q] = out[q];
   }
@@ -449,6 +450,134 @@ struct F32NarrowArgs {
 constexpr int f32_narrow_units(int ht) { return (4 * ht + 2 * 16 + 4) * 64; }
 constexpr size_t f32_narrow_lds(int ht) {
   return (size_t)f32_narrow_units(ht) * 16 + (size_t)kF32Waves * 2 * 16 * kF32NarrowLd * 4;
+}
+
+// The forward of the same networks: features (as k_features), layers and heads of 16 positions a wave, all weights in
+// LDS, sixteen waves a CU that wait for nobody.  A lane gathers the four features it takes as an operand; what is
+// written is what the backward reads (features, hidden outputs) and the heads.  Features and streamed
+// weights as two launches: 0.12 + 0.35 ms for both networks of 65,536 blocks, now 0.38.  Bound by issue: 1,800 VALU
+// instructions a group, over half of them the exponentials of SELU, beside 160 products of 32 cycles.
+constexpr int kF32NarrowWaves = 8;
+
+struct F32NarrowFwdArgs {
+  FeatArgs f;
+  int in_dim, head_dim, head_tiles, n_bias;
+  const u32x4* wpack;
+  const float* bias;
+  int src[kF32NarrowHidden + 1], bias_off[kF32NarrowHidden + 1];
+  float* h[kF32NarrowHidden];
+  float* y;
+};
+
+constexpr int f32_narrow_fwd_units(int ht) { return (4 + 2 * 16 + 4 * ht) * 64; }
+
+// FE consecutive features of a level, as k_features: the corners' values with QAT's rounding.
+template <int FE>
+__device__ __forceinline__ void f32_feature(const FeatArgs& a, const Tap& t, int l, int f, float* v) {
+  float c[4][FE];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) dev::load_f32<FE>(a.grid + t.vtx[k] * a.F + f, c[k]);
+  if (a.stats) {
+    const float s = reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l];
+    const int z = a.stats[3 * NTBC_MAX_LEVELS + l];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int m = 0; m < FE; ++m) {
+        bool inside;
+        c[k][m] = fake_quant(c[k][m], s, z, &inside);
+      }
+  }
+#pragma unroll
+  for (int m = 0; m < FE; ++m) v[m] = fmaf(t.w[0], c[0][m], fmaf(t.w[1], c[1][m], fmaf(t.w[2], c[2][m], t.w[3] * c[3][m])));
+}
+
+// Features c0 .. c0+3 of a position, zero past in_dim.
+__device__ __forceinline__ f32x4_t f32_features(const FeatArgs& a, int id, int c0, int in_dim) {
+  f32x4_t r{};
+  if (a.F == 2) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      if (c0 + 2 * k < in_dim) {
+        float v[2];
+        const int l = c0 / 2 + k;
+        f32_feature<2>(a, grid_tap_id(a, id, l), l, 0, v);
+        r[2 * k] = v[0];
+        r[2 * k + 1] = v[1];
+      }
+    return r;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (c0 + k < in_dim) {
+      const int l = (c0 + k) >> a.f_shift;
+      float v;
+      f32_feature<1>(a, grid_tap_id(a, id, l), l, (c0 + k) & (a.F - 1), &v);
+      r[k] = v;
+    }
+  return r;
+}
+
+template <int Q>
+__device__ __forceinline__ void f32_narrow_fwd_layer(const u32x4* w, const float* bias, const f32x4_t (&in)[Q], f32x4_t (&out)[4],
+                                                     float* store, bool valid, int lane) {
+  const int g = lane >> 4;
+#pragma unroll
+  for (int t0 = 0; t0 < 4; t0 += 2) {
+    f32x4_t acc[2];
+    f32_products<2, Q>(w + t0 * Q * 64, in, Q, 2, lane, acc);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int t = t0 + u;
+      const f32x4_t b = *reinterpret_cast<const f32x4_t*>(bias + 16 * t + 4 * g);
+      f32x4_t r;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) r[v] = selu_f(acc[u][v] + b[v]);
+      if (valid) *reinterpret_cast<f32x4_t*>(store + 16 * t + 4 * g) = r;
+      out[t] = f32_natural(r);
+    }
+  }
+}
+
+__global__ void __launch_bounds__(64 * kF32NarrowWaves) __attribute__((amdgpu_waves_per_eu(4))) k_f32_fwd_narrow(F32NarrowFwdArgs a) {
+  extern __shared__ u32x4 smem[];
+  constexpr int kW1 = 4 * 64, kW2 = kW1 + 16 * 64, kW3 = kW2 + 16 * 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int units = f32_narrow_fwd_units(a.head_tiles);
+  for (int at = 64 * wave; at < units; at += 64 * kF32NarrowWaves) {
+    const u32x4* from = a.wpack + (at < kW1 ? a.src[0] + at : at < kW2 ? a.src[1] + at - kW1 : at < kW3 ? a.src[2] + at - kW2 : a.src[3] + at - kW3);
+    __builtin_amdgcn_global_load_lds(from + lane, (__attribute__((address_space(3))) void*)(smem + at), 16, 0, 0);
+  }
+  float* bias = reinterpret_cast<float*>(smem + units);
+  for (int i = tid; i < a.n_bias; i += 64 * kF32NarrowWaves) bias[i] = a.bias[i];
+  fwait_dma();
+  __syncthreads();
+  const int64_t n = a.f.n, groups = (n + 15) / 16, npos = (int64_t)a.f.blocks_w * a.f.blocks_h;
+  for (int64_t grp = (int64_t)blockIdx.x * kF32NarrowWaves + wave; grp < groups; grp += (int64_t)gridDim.x * kF32NarrowWaves) {
+    int zero = 0;  // opaque: the weights are to be read in each turn, not kept in registers over the loop
+    asm volatile("" : "+v"(zero));
+    const int g = (lane >> 4) + zero, j = (lane & 15) + zero;
+    const int64_t p = grp * 16 + j;
+    const bool valid = p < n;
+    const int64_t pc = valid ? p : n - 1;
+    const u32x4* w = smem + zero;
+    const float* bl = bias + zero;
+    const f32x4_t x = f32_features(a.f, clamp_id(a.f.ids[pc], npos), 4 * g, a.in_dim);
+    if (valid) f32_put4(a.f.x + p * a.in_dim, 4 * g, a.in_dim, x);
+    const f32x4_t x0[1] = {f32_natural(x)};
+    f32x4_t u[4], v[4];
+    f32_narrow_fwd_layer(w, bl + a.bias_off[0], x0, u, a.h[0] + pc * 64, valid, lane + zero);
+    f32_narrow_fwd_layer(w + kW1, bl + a.bias_off[1], u, v, a.h[1] + pc * 64, valid, lane + zero);
+    f32_narrow_fwd_layer(w + kW2, bl + a.bias_off[2], v, u, a.h[2] + pc * 64, valid, lane + zero);
+    for (int t = 0; t < a.head_tiles; ++t) {
+      f32x4_t acc[1], r;
+      f32_products<1, 4>(w + kW3 + t * 256, u, 4, 1, lane, acc);
+      const int n0 = 16 * t + 4 * g;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) r[k] = 1.0f / (1.0f + expf(-(acc[0][k] + bl[a.bias_off[3] + n0 + k])));
+      if (valid) f32_put4(a.y + p * a.head_dim, n0, a.head_dim, r);
+    }
+  }
 }
 
 template <int HT>
