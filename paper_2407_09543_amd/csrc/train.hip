@@ -469,8 +469,7 @@ __global__ void k_zero_u64(unsigned long long* __restrict__ p, int64_t count) {
 }
 
 // ------------------------------------------------------------------------------------------ GEMM
-enum Epi { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_SIGMOID = 2, EPI_MASK = 3, EPI_ATOMIC = 4, EPI_BIAS_SELU = 5,
-           EPI_SELU_MASK = 6 };
+enum Epi { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_SIGMOID = 2, EPI_MASK = 3, EPI_ATOMIC = 4 };
 
 // SELU (the paper's own layout, Sec. 3.4) with the constants of Klambauer et al. (2017).  Its
 // derivative from the layer output h = selu(z): lambda where h > 0 (z > 0), otherwise
@@ -579,10 +578,6 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
           *out = z < 0.0f ? 0.0f : z;  // ReLU that keeps NaN (so a non-finite parameter is detected)
         } else if (EPI == EPI_BIAS_SIGMOID) {
           *out = 1.0f / (1.0f + expf(-(val + g.bias[n])));
-        } else if (EPI == EPI_BIAS_SELU) {
-          *out = selu_f(val + g.bias[n]);
-        } else if (EPI == EPI_SELU_MASK) {
-          *out = val * selu_grad_of_out(g.mask[(int64_t)m * g.ldm + n]);
         } else if (EPI == EPI_MASK) {
           *out = g.mask[(int64_t)m * g.ldm + n] > 0.0f ? val : 0.0f;
         } else if (EPI == EPI_ATOMIC) {
@@ -766,10 +761,10 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
     const int n = n0 + wn * 64 + 32 * j + li;
     if (n >= g.N) continue;
     // the lane's column: its bias read once, rows addressed from one base with 32-bit row offsets
-    const float bn = (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_SIGMOID || EPI == EPI_BIAS_SELU) ? g.bias[n] : 0.0f;
+    const float bn = (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_SIGMOID) ? g.bias[n] : 0.0f;
     const int mb = m0 + wm * 64 + 4 * lg;
     float* __restrict__ cb = g.c + (int64_t)mb * g.ldc + n;
-    const float* __restrict__ kb = EPI == EPI_MASK || EPI == EPI_SELU_MASK ? g.mask + (int64_t)mb * g.ldm + n : nullptr;
+    const float* __restrict__ kb = EPI == EPI_MASK ? g.mask + (int64_t)mb * g.ldm + n : nullptr;
     const int ldc = (int)g.ldc, ldm = (int)g.ldm;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -784,10 +779,6 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
           *out = z < 0.0f ? 0.0f : z;  // ReLU that keeps NaN (so a non-finite parameter is detected)
         } else if (EPI == EPI_BIAS_SIGMOID) {
           *out = 1.0f / (1.0f + expf(-(val + bn)));
-        } else if (EPI == EPI_BIAS_SELU) {
-          *out = selu_f(val + bn);
-        } else if (EPI == EPI_SELU_MASK) {
-          *out = val * selu_grad_of_out(kb[dm * ldm]);
         } else if (EPI == EPI_MASK) {
           *out = kb[dm * ldm] > 0.0f ? val : 0.0f;
         } else if (EPI == EPI_ATOMIC) {
@@ -2380,7 +2371,6 @@ struct Ctx {
   hipStream_t strm;
   bool bf16;  // bfloat16 matrix-core operands (FP32 accumulation, FP32 master parameters)
   bool det = false;     // deterministic reductions (grid scatter in fixed point, unsplit weight products)
-  bool selu = false;    // SELU hidden layers (the paper's own layout) instead of ReLU
   bool texel_blocks = false;  // the positions are the 16 texels of each block in turn (texel-grid ids)
   int64_t det_off = 0;  // byte offset of the deterministic scatter's sums in the workspace
   float* y = nullptr;   // heads and their gradient (unfused and chained FP32 paths)
@@ -2439,9 +2429,7 @@ int forward(Ctx& c, const float* grid, const float* weights, bool qat, const int
     g.K = s.layer_in[k];
     g.k_split = g.K;
     g.bias = weights + s.b_off[k];
-    st = last     ? gemm<EPI_BIAS_SIGMOID>(g, 1, c.strm, c.bf16)
-         : c.selu ? gemm<EPI_BIAS_SELU>(g, 1, c.strm, c.bf16)
-                  : gemm<EPI_BIAS_RELU>(g, 1, c.strm, c.bf16);
+    st = last ? gemm<EPI_BIAS_SIGMOID>(g, 1, c.strm, c.bf16) : gemm<EPI_BIAS_RELU>(g, 1, c.strm, c.bf16);
     if (st != NTBC_OK) return st;
   }
   return NTBC_OK;
@@ -2587,7 +2575,7 @@ int backward(Ctx& c, const float* grid, const float* weights, bool qat, const in
     if (k > 0) {
       gd.mask = c.act_in(k);
       gd.ldm = in;
-      st = c.selu ? gemm<EPI_SELU_MASK>(gd, 1, c.strm, c.bf16) : gemm<EPI_MASK>(gd, 1, c.strm, c.bf16);
+      st = gemm<EPI_MASK>(gd, 1, c.strm, c.bf16);
     } else {
       st = gemm<EPI_STORE>(gd, 1, c.strm, c.bf16);
     }
@@ -3035,7 +3023,8 @@ struct F32Plan {
 // The shapes that k_f32_fwd and k_f32_bwd take; others go through k_gemm layer by layer.
 bool f32_plan(const Shape& s, bool selu, F32Plan* fp) {
   if ((s.hidden != 64 && s.hidden != 128 && s.hidden != 256) || s.in_dim > 16 * kF32Groups || s.head_dim > 16 * kF32HeadTiles ||
-      (selu && (s.hidden != 64 || s.n_hidden != kF32NarrowHidden || s.in_dim > 16 || s.head_dim > 16 * kF32NarrowHeadTiles)))
+      (selu && (s.hidden != 64 || s.n_hidden != kF32NarrowHidden || s.n_features != 2 || s.in_dim > 16 ||
+                s.head_dim > 16 * kF32NarrowHeadTiles)))
     return false;
   F32Plan& f = *fp;
   f = F32Plan{};
@@ -3615,29 +3604,23 @@ Ctx faithful_ctx(const Shape& s, int64_t n, char* ws, hipStream_t strm, bool det
   c.bf16 = false;
   c.det = det;
   c.det_off = det_offset(s, n);
-  c.selu = true;
   F32Plan p;
   place_heads(c, f32_plan(s, true, &p) ? &p : nullptr);
   return c;
 }
 
-// Forward and backward of one of the two networks: chained where its shape allows (at most 16 inputs), layer
-// by layer otherwise.
+// Forward and backward of one of the two networks, whose shapes (at most eight levels of two features, three
+// hidden layers of 64, at most eight textures) the narrow kernels all take.
 int faithful_forward(Ctx& c, const float* grid, const float* weights, bool qat, const int32_t* ids) {
   F32Plan p;
-  return f32_plan(c.s, true, &p) ? f32_forward(c, p, grid, weights, qat, ids, c.y) : forward(c, grid, weights, qat, ids, c.y);
+  NTBC_REQUIRE(f32_plan(c.s, true, &p), "not a network of the two-network layout");
+  return f32_forward(c, p, grid, weights, qat, ids, c.y);
 }
 
-int faithful_backward(Ctx& c, const float* grid, const float* weights, bool qat, const int32_t* ids, float* d_grid,
-                      float* d_weights, float* flag) {
+int faithful_backward(Ctx& c, const float* grid, bool qat, const int32_t* ids, float* d_grid, float* d_weights, float* flag) {
   F32Plan p;
-  if (f32_plan(c.s, true, &p)) return f32_backward(c, p, grid, qat, ids, d_grid, d_weights, true, flag);
-  int st = fill(d_weights, c.s.n_weights, 0.0f, c.strm);
-  if (st == NTBC_OK) st = backward(c, grid, weights, qat, ids, d_grid, d_weights);
-  if (st != NTBC_OK) return st;
-  hipLaunchKernelGGL(k_check_finite, dim3((unsigned)std::min<int64_t>(ceil_div(c.s.n_weights, 256), 1024)), dim3(256), 0, c.strm,
-                     d_weights, c.s.n_weights, flag);
-  return check_launch("k_check_finite");
+  NTBC_REQUIRE(f32_plan(c.s, true, &p), "not a network of the two-network layout");
+  return f32_backward(c, p, grid, qat, ids, d_grid, d_weights, true, flag);
 }
 
 Ctx faithful_colour_ctx(const Shape& s, int64_t n, char* ws, hipStream_t strm, bool det) {
@@ -3739,9 +3722,9 @@ extern "C" int ntbc_faithful_train_step(const ntbc_faithful_desc* d, const ntbc_
   st = fill(tsd->d_ep_grid, nge, 0.0f, strm);
   if (st == NTBC_OK) st = fill(tsd->d_col_grid, ngc, 0.0f, strm);
   if (st == NTBC_OK)
-    st = faithful_backward(ce, tsd->ep_grid, tsd->ep_weights, qat, batch_ids, tsd->d_ep_grid, tsd->d_ep_weights, losses_out + 4);
+    st = faithful_backward(ce, tsd->ep_grid, qat, batch_ids, tsd->d_ep_grid, tsd->d_ep_weights, losses_out + 4);
   if (st == NTBC_OK)
-    st = faithful_backward(cc, tsd->col_grid, tsd->col_weights, qat, tids, tsd->d_col_grid, tsd->d_col_weights, losses_out + 4);
+    st = faithful_backward(cc, tsd->col_grid, qat, tids, tsd->d_col_grid, tsd->d_col_weights, losses_out + 4);
   if (st != NTBC_OK) return st;
   const double tt = (double)step + 1.0;
   AdamArgs aa{};

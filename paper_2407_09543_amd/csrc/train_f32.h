@@ -471,50 +471,33 @@ struct F32NarrowFwdArgs {
 
 constexpr int f32_narrow_fwd_units(int ht) { return (4 + 2 * 16 + 4 * ht) * 64; }
 
-// FE consecutive features of a level, as k_features: the corners' values with QAT's rounding.
-template <int FE>
-__device__ __forceinline__ void f32_feature(const FeatArgs& a, const Tap& t, int l, int f, float* v) {
-  float c[4][FE];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) dev::load_f32<FE>(a.grid + t.vtx[k] * a.F + f, c[k]);
-  if (a.stats) {
-    const float s = reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l];
-    const int z = a.stats[3 * NTBC_MAX_LEVELS + l];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int m = 0; m < FE; ++m) {
-        bool inside;
-        c[k][m] = fake_quant(c[k][m], s, z, &inside);
-      }
-  }
-#pragma unroll
-  for (int m = 0; m < FE; ++m) v[m] = fmaf(t.w[0], c[0][m], fmaf(t.w[1], c[1][m], fmaf(t.w[2], c[2][m], t.w[3] * c[3][m])));
-}
-
-// Features c0 .. c0+3 of a position, zero past in_dim.
+// Features c0 .. c0+3 of a position (two levels of two), zero past in_dim; the corners' values with QAT's rounding
+// and the sum as in k_features.
 __device__ __forceinline__ f32x4_t f32_features(const FeatArgs& a, int id, int c0, int in_dim) {
   f32x4_t r{};
-  if (a.F == 2) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
-      if (c0 + 2 * k < in_dim) {
-        float v[2];
-        const int l = c0 / 2 + k;
-        f32_feature<2>(a, grid_tap_id(a, id, l), l, 0, v);
-        r[2 * k] = v[0];
-        r[2 * k + 1] = v[1];
-      }
-    return r;
-  }
+  for (int h = 0; h < 2; ++h) {
+    if (c0 + 2 * h >= in_dim) continue;
+    const int l = c0 / 2 + h;
+    const Tap t = grid_tap_id(a, id, l);
+    float c[4][2];
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (c0 + k < in_dim) {
-      const int l = (c0 + k) >> a.f_shift;
-      float v;
-      f32_feature<1>(a, grid_tap_id(a, id, l), l, (c0 + k) & (a.F - 1), &v);
-      r[k] = v;
+    for (int k = 0; k < 4; ++k) dev::load_f32<2>(a.grid + t.vtx[k] * 2, c[k]);
+    if (a.stats) {
+      const float s = reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l];
+      const int z = a.stats[3 * NTBC_MAX_LEVELS + l];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          bool inside;
+          c[k][m] = fake_quant(c[k][m], s, z, &inside);
+        }
     }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      r[2 * h + m] = fmaf(t.w[0], c[0][m], fmaf(t.w[1], c[1][m], fmaf(t.w[2], c[2][m], t.w[3] * c[3][m])));
+  }
   return r;
 }
 
