@@ -347,14 +347,14 @@ typedef struct {
                                bfloat16 operands on the matrix cores with FP32 accumulation; master
                                parameters, losses, grid scatter and Adam stay FP32                   */
   float loss_weights[4];    /* weights of L_e, L_c, L_cd(endpoint), L_cd(colour) in the gradient; 1 = paper */
-  int32_t deterministic;    /* 0: the grid scatter (and, for shapes outside the fused bfloat16 path, the
-                               split weight products) add with FP32 atomics, so the gradients depend on
+  int32_t deterministic;    /* 0: the grid scatter (and, for shapes outside the chained paths, the split
+                               weight products) add with FP32 atomics, so the gradients depend on
                                their order in the last bits.  1: bitwise repeatable parameters: the grid
                                gradient is summed as 64-bit fixed-point integers at a per-step power-of-two
                                scale 2^(61 - ceil(log2(batch * max|dX|))) (order-independent; each term
                                rounded to that scale, which is far finer than FP32's resolution of the
-                               sums) and every weight product runs unsplit.  The reported losses are
-                               FP32 atomic sums in both modes. */
+                               sums) and every weight product runs unsplit or adds its ranges in a fixed
+                               order.  The reported losses are FP32 atomic sums in both modes. */
   int32_t stage2_from;      /* NTBC_NAIVE only (Sec. 3.1): steps >= stage2_from are the second stage, which
                                decodes with the quantised weights w_n (the gradient reaches the endpoints
                                only) and updates only the endpoint head's rows of the last layer's weights

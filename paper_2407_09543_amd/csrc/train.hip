@@ -2,14 +2,20 @@
 // App. A straight-through estimator).  One step for a batch of block positions:
 //
 //   k_level_minmax / k_qat_params   per-level min/max of the FP32 master grid -> (s_l, z_l) (QAT on)
-//   k_features                      bilinear features of the (fake-quantised) grid -> X [B][in]
-//   k_gemm (bias+ReLU / sigmoid)    MLP forward, every layer's input kept for the batch
+//   the MLP forward, one of
+//     k_train_fwd                   bfloat16 products, features and layers chained in registers
+//     k_features, k_f32_fwd         FP32 products, layers chained in registers (train_f32.h)
+//     k_f32_fwd_narrow              the same for the two-network layout, features included (train_f32.h)
+//     k_features, k_gemm(_bf16)     other shapes, layer by layer (bias + ReLU / sigmoid epilogues)
 //   k_loss_grad                     L_e, L_c and both decoded-colour terms, dL/dY with the STE
 //   k_dsigmoid                      dZ_out = dY * Y (1 - Y) (in the training step: inside k_loss_grad)
-//   k_gemm (mask / split-K atomic)  dH_k = dZ_k W_k masked by ReLU, dW_k = dZ_k^T H_k, db by k_colsum
-//                                   (bfloat16 products: db fused into the dW product)
-//   k_scatter                       dX through the bilinear weights into d_grid (atomic), QAT
-//                                   pass-through mask
+//   the backward, one of
+//     k_train_bwd, k_train_dw       dZ chained down to dX, then dW and db; k_train_dw_reduce adds the ranges
+//     k_f32_bwd, k_f32_dw           the same in FP32 (train_f32.h)
+//     k_f32_bwd_dw                  both in one for the two-network layout (train_f32.h)
+//     k_gemm (mask / split-K atomic)  other shapes: dH_k = dZ_k W_k masked by ReLU, dW_k = dZ_k^T H_k, db
+//   k_scatter_coarse, k_scatter     dX through the bilinear weights into d_grid (coarse levels in LDS, fine ones
+//                                   with atomics), QAT pass-through mask
 //   k_adam                          dense bias-corrected Adam, learning rate from the host schedule
 //
 // The autograd entry points (ntbc_forward / ntbc_backward) keep nothing between calls: the backward
