@@ -295,23 +295,15 @@ __global__ void __launch_bounds__(kBlock) k_scatter(FeatArgs a, const float* __r
   scatter_one<Acc>(a, dx, p, first_level + l, f, dgrid, det_scale ? *det_scale : 1.0f);
 }
 
-// Levels [first_level, n_levels) when the positions are the texels of whole blocks (16 consecutive
-// positions: texels (4bx + x, 4by + y), i = 4y + x, of a texel grid of blocks_w x blocks_h cells) and
-// no level is finer than the texel grid: one thread per (block, level, feature).  Adjacent texels'
+// Level l, feature f of texel block b, when the positions are the texels of whole blocks (16 consecutive
+// positions: texels (4bx + x, 4by + y), i = 4y + x, of a texel grid of blocks_w x blocks_h cells) and the
+// level is not finer than the texel grid.  Adjacent texels'
 // corners then differ by at most one vertex, so a block's 16 texels touch at most 5 x 5 vertices of a
 // level; their 64 weighted terms are summed in registers first (the bilinear weights are separable:
 // sum over y of wy(y, b) * sum over x of wx(x, a) d(x, y)), and the block adds each touched vertex once.
 template <typename Acc>
-__global__ void __launch_bounds__(kBlock) k_scatter_texels(FeatArgs a, const float* __restrict__ dx,
-                                                           Acc* __restrict__ dgrid, int first_level,
-                                                           const float* __restrict__ det_scale) {
-  const int nl = a.n_levels - first_level;
-  const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (gid >= (a.n / 16) * nl * a.F) return;
-  const int f = (int)gid & (a.F - 1);
-  int l;
-  const int64_t b = div_mod(gid >> a.f_shift, nl, a.n * nl <= 0x7fffffff, &l);
-  l += first_level;
+__device__ __forceinline__ void scatter_block(const FeatArgs& a, const float* __restrict__ dx, int64_t b, int l, int f,
+                                              Acc* __restrict__ dgrid, float scale) {
   const int t0 = clamp_id(a.ids[16 * b], (int64_t)a.blocks_w * a.blocks_h);
   const int tx0 = t0 % a.blocks_w, ty0 = t0 / a.blocks_w;
   const int res = a.base_res << l;
@@ -340,7 +332,6 @@ __global__ void __launch_bounds__(kBlock) k_scatter_texels(FeatArgs a, const flo
   }
   const float s = a.stats ? reinterpret_cast<const float*>(a.stats)[2 * NTBC_MAX_LEVELS + l] : 1.0f;
   const int z = a.stats ? a.stats[3 * NTBC_MAX_LEVELS + l] : 0;
-  const float scale = det_scale ? *det_scale : 1.0f;
 #pragma unroll
   for (int r = 0; r < 5; ++r) {
     float acc[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
@@ -368,6 +359,19 @@ __global__ void __launch_bounds__(kBlock) k_scatter_texels(FeatArgs a, const flo
         atomicAdd(&dgrid[v * a.F + f], acc[c]);
     }
   }
+}
+
+// Levels [first_level, n_levels) of texel blocks: one thread per (block, level, feature).
+template <typename Acc>
+__global__ void __launch_bounds__(kBlock) k_scatter_texels(FeatArgs a, const float* __restrict__ dx,
+                                                           Acc* __restrict__ dgrid, int first_level,
+                                                           const float* __restrict__ det_scale) {
+  const int nl = a.n_levels - first_level;
+  const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (gid >= (a.n / 16) * nl * a.F) return;
+  int l;
+  const int64_t b = div_mod(gid >> a.f_shift, nl, a.n * nl <= 0x7fffffff, &l);
+  scatter_block<Acc>(a, dx, b, l + first_level, (int)gid & (a.F - 1), dgrid, det_scale ? *det_scale : 1.0f);
 }
 
 // Levels [0, n_coarse) (their gradient fits in LDS): every block accumulates a contiguous share of the
@@ -408,6 +412,33 @@ __global__ void __launch_bounds__(kCoarseThreads) k_scatter_coarse(FeatArgs a, c
 #pragma unroll
     for (int u = 0; u < kU; ++u)
       scatter_tap<Acc>(a, df[u], clamp_id(id[u], npos), lf[u] >> a.f_shift, lf[u] & (a.F - 1), acc, scale);
+  }
+  __syncthreads();
+  Acc* row = part + (int64_t)blockIdx.x * nv;
+  for (int64_t i = threadIdx.x; i < nv; i += kCoarseThreads) row[i] = acc[i];
+}
+
+// The same levels of texel blocks, a (block, level, feature) a thread: the 16 texels of a block meet the same few
+// vertices of a coarse level, so a texel at a time their LDS atomics wait for each other (65,536 blocks, three
+// levels of two features: 130 us; their sums added once 26).
+template <typename Acc>
+__global__ void __launch_bounds__(kCoarseThreads) k_scatter_coarse_texels(FeatArgs a, const float* __restrict__ dx,
+                                                                          Acc* __restrict__ part, int n_coarse,
+                                                                          const float* __restrict__ det_scale) {
+  extern __shared__ __align__(8) unsigned char acc_raw[];
+  Acc* acc = reinterpret_cast<Acc*>(acc_raw);
+  const float scale = det_scale ? *det_scale : 1.0f;
+  const int64_t nv = a.level_offset[n_coarse] * a.F;
+  for (int64_t i = threadIdx.x; i < nv; i += kCoarseThreads) acc[i] = (Acc)0;
+  __syncthreads();
+  const int64_t total = a.n / 16 * n_coarse * a.F;
+  const bool small = total <= 0x7fffffff;
+  const int64_t share = (total + gridDim.x - 1) / gridDim.x;
+  const int64_t e0 = (int64_t)blockIdx.x * share, e1 = e0 + share < total ? e0 + share : total;
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += kCoarseThreads) {
+    int lf;
+    const int64_t b = div_mod(e, n_coarse * a.F, small, &lf);
+    scatter_block<Acc>(a, dx, b, lf >> a.f_shift, lf & (a.F - 1), acc, scale);
   }
   __syncthreads();
   Acc* row = part + (int64_t)blockIdx.x * nv;
@@ -2472,35 +2503,38 @@ int scatter_grid(Ctx& c, const float* grid, bool qat, const int32_t* ids, const 
                        c.strm, dx, nx, amax);
     hipLaunchKernelGGL(k_det_scale, dim3(1), dim3(1), 0, c.strm, amax, c.n, scale);
   }
+  // texel blocks whose terms of a level are summed first: no level finer than the texel grid
+  const auto block_sums = [&](int levels_to) {
+    const int64_t finest = (int64_t)s.base_res << (levels_to - 1);
+    return c.texel_blocks && c.n % 16 == 0 && finest <= s.blocks_w && finest <= s.blocks_h;
+  };
   // coarse levels whose gradient fits in kCoarseLds of LDS are pre-aggregated per block
   const int n_coarse = coarse_levels(s, vbytes);
   if (n_coarse > 0 && levels != 2) {
     // two terms a thread, at least sixteen blocks: each block writes a row of up to 48 KB for the reduction to
     // read, so 512 of them for 512 positions' 8,192 terms cost 10.9 + 8.0 us against 5.4 + 3.6 with sixteen
-    const int64_t terms = c.n * n_coarse * s.n_features;
+    const bool texels = block_sums(n_coarse);
+    const int64_t terms = (texels ? c.n / 16 : c.n) * n_coarse * s.n_features;
     const unsigned rows = (unsigned)std::min<int64_t>(
         kCoarseBlocks, std::max(ceil_div(terms, 2 * kCoarseThreads), std::min<int64_t>(16, ceil_div(terms, 64))));
     const int64_t nv = s.level_offset[n_coarse] * s.n_features;
     const size_t lds = (size_t)nv * vbytes;
     char* part = reinterpret_cast<char*>(c.ws) + coarse_offset(s, c.n);
     if (c.det) {
-      hipLaunchKernelGGL(k_scatter_coarse<unsigned long long>, dim3(rows), dim3(kCoarseThreads), lds, c.strm, fa, dx,
+      hipLaunchKernelGGL(texels ? k_scatter_coarse_texels<unsigned long long> : k_scatter_coarse<unsigned long long>, dim3(rows), dim3(kCoarseThreads), lds, c.strm, fa, dx,
                          reinterpret_cast<unsigned long long*>(part), n_coarse, (const float*)scale);
       hipLaunchKernelGGL(k_scatter_reduce<unsigned long long>, dim3((unsigned)ceil_div(nv, 64)), dim3(256), 0, c.strm,
                          reinterpret_cast<const unsigned long long*>(part), (int)rows, nv, acc);
     } else {
-      hipLaunchKernelGGL(k_scatter_coarse<float>, dim3(rows), dim3(kCoarseThreads), lds, c.strm, fa, dx,
+      hipLaunchKernelGGL(texels ? k_scatter_coarse_texels<float> : k_scatter_coarse<float>, dim3(rows), dim3(kCoarseThreads), lds, c.strm, fa, dx,
                          reinterpret_cast<float*>(part), n_coarse, (const float*)nullptr);
       hipLaunchKernelGGL(k_scatter_reduce<float>, dim3((unsigned)ceil_div(nv, 64)), dim3(256), 0, c.strm,
                          reinterpret_cast<const float*>(part), (int)rows, nv, d_grid);
     }
   }
-  // texel blocks: per-block sums when no fine level is finer than the texel grid
-  const int64_t finest = (int64_t)s.base_res << (s.n_levels - 1);
   if (levels == 1) {
     // the fine levels are left to a second call
-  } else if (n_coarse < s.n_levels && c.texel_blocks && c.n % 16 == 0 && finest <= s.blocks_w &&
-             finest <= s.blocks_h) {
+  } else if (n_coarse < s.n_levels && block_sums(s.n_levels)) {
     const dim3 grid_dim((unsigned)ceil_div(c.n / 16 * (s.n_levels - n_coarse) * s.n_features, kBlock));
     if (c.det)
       hipLaunchKernelGGL(k_scatter_texels<unsigned long long>, grid_dim, dim3(kBlock), 0, c.strm, fa, dx, acc, n_coarse,
