@@ -1090,7 +1090,8 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in
           const float d = c[ch] - ph[n][ch];
           acc += d * d;
         }
-        const float rs = __builtin_amdgcn_rsqf(fmaxf(acc, 0x1p-126f));  // v = 0: distance and gradient 0
+        // v = 0: distance and gradient 0, whatever dd is (1/T times a tie of equal entries may exceed 2^65)
+        const float rs = acc > 0.0f ? __builtin_amdgcn_rsqf(acc) : 0.0f;
         dist[n] = acc * rs;
         unit[n] = rs;
       }
@@ -1126,7 +1127,7 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in
           const float d = chat[ch] - pr[n][ch];
           acc += d * d;
         }
-        const float rs = __builtin_amdgcn_rsqf(fmaxf(acc, 0x1p-126f));  // v = 0: distance and gradient 0
+        const float rs = acc > 0.0f ? __builtin_amdgcn_rsqf(acc) : 0.0f;  // v = 0: as above
         dist[n] = acc * rs;
         unit[n] = rs;
       }
