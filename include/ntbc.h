@@ -450,7 +450,8 @@ int ntbc_faithful_train_size(const ntbc_faithful_desc* d, int32_t batch, size_t*
  * grids); h->precision NTBC_FP32, else NTBC_EUNSUPPORTED; h->deterministic as for ntbc_train_step;
  * t: the targets of the model's textures, in their order.  losses_out (device float[5]) as for
  * ntbc_train_step: a non-finite value skips the update and sets losses_out[4] = 1.  A conservative
- * material trains its two models with one call each.  Errors: NTBC_EINVAL, NTBC_ENOWORKSPACE,
+ * material trains its two models with one call each.  Either grid may have up to NTBC_MAX_LEVELS levels here
+ * (beyond eight, ntbc_faithful_infer does not decode it).  Errors: NTBC_EINVAL, NTBC_ENOWORKSPACE,
  * NTBC_EUNSUPPORTED. */
 int ntbc_faithful_train_step(const ntbc_faithful_desc* d, const ntbc_faithful_train_state* st,
                              const ntbc_targets* t, const int32_t* batch_ids, int32_t batch, int64_t step,

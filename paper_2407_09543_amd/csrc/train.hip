@@ -506,7 +506,8 @@ __global__ void k_zero_u64(unsigned long long* __restrict__ p, int64_t count) {
 }
 
 // ------------------------------------------------------------------------------------------ GEMM
-enum Epi { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_SIGMOID = 2, EPI_MASK = 3, EPI_ATOMIC = 4 };
+enum Epi { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_SIGMOID = 2, EPI_MASK = 3, EPI_ATOMIC = 4, EPI_BIAS_SELU = 5,
+           EPI_SELU_MASK = 6 };
 
 // SELU (the paper's own layout, Sec. 3.4) with the constants of Klambauer et al. (2017).  Its
 // derivative from the layer output h = selu(z): lambda where h > 0 (z > 0), otherwise
@@ -615,6 +616,10 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
           *out = z < 0.0f ? 0.0f : z;  // ReLU that keeps NaN (so a non-finite parameter is detected)
         } else if (EPI == EPI_BIAS_SIGMOID) {
           *out = 1.0f / (1.0f + expf(-(val + g.bias[n])));
+        } else if (EPI == EPI_BIAS_SELU) {
+          *out = selu_f(val + g.bias[n]);
+        } else if (EPI == EPI_SELU_MASK) {
+          *out = val * selu_grad_of_out(g.mask[(int64_t)m * g.ldm + n]);
         } else if (EPI == EPI_MASK) {
           *out = g.mask[(int64_t)m * g.ldm + n] > 0.0f ? val : 0.0f;
         } else if (EPI == EPI_ATOMIC) {
@@ -829,16 +834,19 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
 }
 
 // Launches the product on the FP32 (bf16 = false) or bfloat16 matrix cores; `splits` K ranges of
-// g.k_split each (a multiple of 16 for FP32, of kBTK for bfloat16 unless there is one range).
+// g.k_split each (a multiple of 16 for FP32, of kBTK for bfloat16 unless there is one range).  The SELU
+// epilogues are the two-network layout's, which trains with FP32 products only.
 template <int EPI>
 int gemm(const GemmArgs& g, int splits, hipStream_t s, bool bf16 = false) {
-  if (bf16) {
-    const dim3 grid((unsigned)ceil_div(g.N, kBT), (unsigned)ceil_div(g.M, kBT), (unsigned)splits);
-    hipLaunchKernelGGL(k_gemm_bf16<EPI>, grid, dim3(256), 0, s, g);
-  } else {
-    const dim3 grid((unsigned)ceil_div(g.N, 64), (unsigned)ceil_div(g.M, 64), (unsigned)splits);
-    hipLaunchKernelGGL(k_gemm<EPI>, grid, dim3(256), 0, s, g);
+  if constexpr (EPI != EPI_BIAS_SELU && EPI != EPI_SELU_MASK) {
+    if (bf16) {
+      const dim3 grid((unsigned)ceil_div(g.N, kBT), (unsigned)ceil_div(g.M, kBT), (unsigned)splits);
+      hipLaunchKernelGGL(k_gemm_bf16<EPI>, grid, dim3(256), 0, s, g);
+      return check_launch("k_gemm_bf16");
+    }
   }
+  const dim3 grid((unsigned)ceil_div(g.N, 64), (unsigned)ceil_div(g.M, 64), (unsigned)splits);
+  hipLaunchKernelGGL(k_gemm<EPI>, grid, dim3(256), 0, s, g);
   return check_launch("k_gemm");
 }
 
@@ -2409,6 +2417,7 @@ struct Ctx {
   hipStream_t strm;
   bool bf16;  // bfloat16 matrix-core operands (FP32 accumulation, FP32 master parameters)
   bool det = false;     // deterministic reductions (grid scatter in fixed point, unsplit weight products)
+  bool selu = false;    // SELU hidden layers (the paper's own layout) instead of ReLU
   bool texel_blocks = false;  // the positions are the 16 texels of each block in turn (texel-grid ids)
   int64_t det_off = 0;  // byte offset of the deterministic scatter's sums in the workspace
   float* y = nullptr;   // heads and their gradient (unfused and chained FP32 paths)
@@ -2467,7 +2476,9 @@ int forward(Ctx& c, const float* grid, const float* weights, bool qat, const int
     g.K = s.layer_in[k];
     g.k_split = g.K;
     g.bias = weights + s.b_off[k];
-    st = last ? gemm<EPI_BIAS_SIGMOID>(g, 1, c.strm, c.bf16) : gemm<EPI_BIAS_RELU>(g, 1, c.strm, c.bf16);
+    st = last     ? gemm<EPI_BIAS_SIGMOID>(g, 1, c.strm, c.bf16)
+         : c.selu ? gemm<EPI_BIAS_SELU>(g, 1, c.strm, c.bf16)
+                  : gemm<EPI_BIAS_RELU>(g, 1, c.strm, c.bf16);
     if (st != NTBC_OK) return st;
   }
   return NTBC_OK;
@@ -2616,7 +2627,7 @@ int backward(Ctx& c, const float* grid, const float* weights, bool qat, const in
     if (k > 0) {
       gd.mask = c.act_in(k);
       gd.ldm = in;
-      st = gemm<EPI_MASK>(gd, 1, c.strm, c.bf16);
+      st = c.selu ? gemm<EPI_SELU_MASK>(gd, 1, c.strm, c.bf16) : gemm<EPI_MASK>(gd, 1, c.strm, c.bf16);
     } else {
       st = gemm<EPI_STORE>(gd, 1, c.strm, c.bf16);
     }
@@ -3645,23 +3656,29 @@ Ctx faithful_ctx(const Shape& s, int64_t n, char* ws, hipStream_t strm, bool det
   c.bf16 = false;
   c.det = det;
   c.det_off = det_offset(s, n);
+  c.selu = true;
   F32Plan p;
   place_heads(c, f32_plan(s, true, &p) ? &p : nullptr);
   return c;
 }
 
-// Forward and backward of one of the two networks, whose shapes (at most eight levels of two features, three
-// hidden layers of 64, at most eight textures) the narrow kernels all take.
+// Forward and backward of one of the two networks: the narrow kernels for grids of at most eight levels (all that
+// ntbc_faithful_infer decodes), layer by layer for the nine to NTBC_MAX_LEVELS levels that training takes beyond.
 int faithful_forward(Ctx& c, const float* grid, const float* weights, bool qat, const int32_t* ids) {
   F32Plan p;
-  NTBC_REQUIRE(f32_plan(c.s, true, &p), "not a network of the two-network layout");
-  return f32_forward(c, p, grid, weights, qat, ids, c.y);
+  return f32_plan(c.s, true, &p) ? f32_forward(c, p, grid, weights, qat, ids, c.y) : forward(c, grid, weights, qat, ids, c.y);
 }
 
-int faithful_backward(Ctx& c, const float* grid, bool qat, const int32_t* ids, float* d_grid, float* d_weights, float* flag) {
+int faithful_backward(Ctx& c, const float* grid, const float* weights, bool qat, const int32_t* ids, float* d_grid,
+                      float* d_weights, float* flag) {
   F32Plan p;
-  NTBC_REQUIRE(f32_plan(c.s, true, &p), "not a network of the two-network layout");
-  return f32_backward(c, p, grid, qat, ids, d_grid, d_weights, true, flag);
+  if (f32_plan(c.s, true, &p)) return f32_backward(c, p, grid, qat, ids, d_grid, d_weights, true, flag);
+  int st = fill(d_weights, c.s.n_weights, 0.0f, c.strm);
+  if (st == NTBC_OK) st = backward(c, grid, weights, qat, ids, d_grid, d_weights);
+  if (st != NTBC_OK) return st;
+  hipLaunchKernelGGL(k_check_finite, dim3((unsigned)std::min<int64_t>(ceil_div(c.s.n_weights, 256), 1024)), dim3(256), 0, c.strm,
+                     d_weights, c.s.n_weights, flag);
+  return check_launch("k_check_finite");
 }
 
 Ctx faithful_colour_ctx(const Shape& s, int64_t n, char* ws, hipStream_t strm, bool det) {
@@ -3763,9 +3780,9 @@ extern "C" int ntbc_faithful_train_step(const ntbc_faithful_desc* d, const ntbc_
   st = fill(tsd->d_ep_grid, nge, 0.0f, strm);
   if (st == NTBC_OK) st = fill(tsd->d_col_grid, ngc, 0.0f, strm);
   if (st == NTBC_OK)
-    st = faithful_backward(ce, tsd->ep_grid, qat, batch_ids, tsd->d_ep_grid, tsd->d_ep_weights, losses_out + 4);
+    st = faithful_backward(ce, tsd->ep_grid, tsd->ep_weights, qat, batch_ids, tsd->d_ep_grid, tsd->d_ep_weights, losses_out + 4);
   if (st == NTBC_OK)
-    st = faithful_backward(cc, tsd->col_grid, qat, tids, tsd->d_col_grid, tsd->d_col_weights, losses_out + 4);
+    st = faithful_backward(cc, tsd->col_grid, tsd->col_weights, qat, tids, tsd->d_col_grid, tsd->d_col_weights, losses_out + 4);
   if (st != NTBC_OK) return st;
   const double tt = (double)step + 1.0;
   AdamArgs aa{};
