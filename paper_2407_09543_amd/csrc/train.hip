@@ -2929,65 +2929,141 @@ int fused_forward(Ctx& c, const FusedPlan& f, const float* grid, const float* we
   return check_launch("k_train_fwd");
 }
 
-// A second stream of the current device (default priority) with a fork and a join event, created on
-// first use and kept until the process ends: the grid scatter runs on it beside the weight-gradient
-// products.  `lock` is held from the fork to the join, so that calls from several host threads do not
-// interleave their uses of the two events.
+// Side streams of a device (default priority), each with a fork and a join event: the grid scatter runs on one
+// beside the weight-gradient products.  A call takes one from its fork to its join and gives it back, so calls from
+// several host threads never use the same events at a time; they are made as callers on different streams
+// need them, at most kMax a device, and kept until the process ends.  Two rules:
+//   - a stream that a capture has drawn in belongs to that capture until it ends (work put on it would become part
+//     of the graph), so only calls of the same capture take it;
+//   - a caller gets the one it had before where it can: on another caller's its scatter would wait for that one's.
+// A call that finds none to take runs on its own stream alone.
 struct SideStream {
   hipStream_t s;
   hipEvent_t fork, join;
-  std::mutex lock;
+  hipStream_t caller;          // whom it served last
+  unsigned long long capture;  // the capture it was last taken in (0: none)
+  uint64_t turn;               // when it was last taken
+  bool held;
 };
 
-int side_stream(SideStream** out) {
+// The id of the capture that `s` is part of, 0 if it is not capturing (the null stream cannot).
+unsigned long long capture_of(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (s == nullptr) return 0;
+  if (hipStreamGetCaptureInfo(s, &status, &id) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return status == hipStreamCaptureStatusNone ? 0 : (id != 0 ? id : ~0ull);
+}
+
+class SideStreams {
+ public:
+  SideStream* take(hipStream_t caller) {
+    const unsigned long long capture = capture_of(caller);
+    std::lock_guard<std::mutex> g(mu_);
+    // the caller's own, else the one idle longest
+    SideStream* best = nullptr;
+    for (int k = 0; k < made_; ++k) {
+      SideStream& x = table_[k];
+      if (x.held || (capture_of(x.s) != 0 && (capture == 0 || x.capture != capture))) continue;
+      if (best == nullptr || (x.caller == caller) > (best->caller == caller) ||
+          ((x.caller == caller) == (best->caller == caller) && x.turn < best->turn))
+        best = &x;
+    }
+    // (captured work waits for nothing outside its graph, so a capture takes any idle one rather than make another)
+    if (best == nullptr || (best->caller != caller && capture == 0))
+      if (SideStream* x = make()) best = x;
+    if (best == nullptr) return nullptr;
+    best->caller = caller;
+    best->capture = capture;
+    best->turn = ++turn_;
+    best->held = true;
+    return best;
+  }
+  void give(SideStream* x) {
+    std::lock_guard<std::mutex> g(mu_);
+    x->held = false;
+  }
+
+ private:
+  static constexpr int kMax = 8;
+  SideStream* make() {
+    if (made_ == kMax) return nullptr;
+    SideStream x{};
+    if (hipStreamCreateWithFlags(&x.s, hipStreamNonBlocking) == hipSuccess) {
+      if (hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess) {
+        if (hipEventCreateWithFlags(&x.join, hipEventDisableTiming) == hipSuccess) {
+          table_[made_] = x;
+          return &table_[made_++];
+        }
+        (void)hipEventDestroy(x.fork);
+      }
+      (void)hipStreamDestroy(x.s);
+    }
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  std::mutex mu_;
+  SideStream table_[kMax];
+  int made_ = 0;
+  uint64_t turn_ = 0;
+};
+
+// Those of the current device.
+int side_streams(SideStreams** out) {
   constexpr int kMaxDevices = 64;
-  static std::mutex mu;
-  static SideStream table[kMaxDevices];
-  static bool made[kMaxDevices];
+  static SideStreams table[kMaxDevices];
   int dev = 0;
   NTBC_HIP(hipGetDevice(&dev));
   NTBC_REQUIRE(dev >= 0 && dev < kMaxDevices, "device %d beyond %d", dev, kMaxDevices);
-  std::lock_guard<std::mutex> g(mu);
-  if (!made[dev]) {
-    NTBC_HIP(hipStreamCreateWithFlags(&table[dev].s, hipStreamNonBlocking));
-    NTBC_HIP(hipEventCreateWithFlags(&table[dev].fork, hipEventDisableTiming));
-    NTBC_HIP(hipEventCreateWithFlags(&table[dev].join, hipEventDisableTiming));
-    made[dev] = true;
-  }
   *out = &table[dev];
   return NTBC_OK;
 }
 
 // The grid scatter around the weight products, which do not depend on each other: in atomic mode fork()
-// runs the coarse levels on the caller's stream and the fine levels' atomics on the side stream, and join()
-// makes the caller's stream wait for them; in deterministic mode, and for batches whose fine levels take
-// less time than the two events (below 8,192 positions), fork() runs everything on the caller's stream.
-// The side stream's lock is held from one to the other.
+// runs the coarse levels on the caller's stream and the fine levels' atomics on a side stream, and join()
+// makes the caller's stream wait for them (so does the destructor where a step between them failed); in
+// deterministic mode, and for batches whose fine levels take less time than the two events (below 8,192
+// positions), fork() runs everything on the caller's stream.
 class ScatterBeside {
  public:
+  ~ScatterBeside() {
+    (void)join(NTBC_OK);
+    if (side_) pool_->give(side_);
+  }
   int fork(Ctx& c, const float* grid, bool qat, const int32_t* ids, const float* dx, float* d_grid) {
-    if (c.det || c.n < 8192) return scatter_grid(c, grid, qat, ids, dx, d_grid);
-    int st = side_stream(&side_);
+    if (!c.det && c.n >= 8192) {
+      const int st = side_streams(&pool_);
+      if (st != NTBC_OK) return st;
+      side_ = pool_->take(c.strm);
+    }
+    if (!side_) return scatter_grid(c, grid, qat, ids, dx, d_grid);
+    int st = scatter_grid(c, grid, qat, ids, dx, d_grid, 1);
     if (st != NTBC_OK) return st;
-    hold_ = std::unique_lock<std::mutex>(side_->lock);
-    st = scatter_grid(c, grid, qat, ids, dx, d_grid, 1);
+    caller_ = c.strm;
     NTBC_HIP(hipEventRecord(side_->fork, c.strm));
     NTBC_HIP(hipStreamWaitEvent(side_->s, side_->fork, 0));
+    forked_ = true;
     Ctx cs = c;
     cs.strm = side_->s;
-    if (st == NTBC_OK) st = scatter_grid(cs, grid, qat, ids, dx, d_grid, 2);
+    st = scatter_grid(cs, grid, qat, ids, dx, d_grid, 2);
     NTBC_HIP(hipEventRecord(side_->join, side_->s));
-    if (st != NTBC_OK) NTBC_HIP(hipStreamWaitEvent(c.strm, side_->join, 0));
     return st;
   }
-  int join(Ctx& c, int st) {
-    if (side_) NTBC_HIP(hipStreamWaitEvent(c.strm, side_->join, 0));
+  int join(int st) {
+    if (!forked_) return st;
+    forked_ = false;
+    NTBC_HIP(hipStreamWaitEvent(caller_, side_->join, 0));
     return st;
   }
 
  private:
+  SideStreams* pool_ = nullptr;
   SideStream* side_ = nullptr;
-  std::unique_lock<std::mutex> hold_;
+  hipStream_t caller_ = nullptr;
+  bool forked_ = false;
 };
 
 // Backward of the batch from dZ of the head ([n][dz_ld]); the forward's workspace contents must be
@@ -3060,7 +3136,7 @@ int fused_backward(Ctx& c, const FusedPlan& f, const float* grid, bool qat, cons
     hipLaunchKernelGGL(k_train_dw_reduce<128>, dw_reduce_grid<128>(d.n_tiles), dim3(256), 0, c.strm, d);
     st = check_launch("k_train_dw_reduce");
   }
-  return beside.join(c, st);
+  return beside.join(st);
 }
 
 // ------------------------------------------------------------------------------------------ FP32, chained: host
@@ -3333,7 +3409,7 @@ int f32_backward(Ctx& c, const F32Plan& f, const float* grid, bool qat, const in
     hipLaunchKernelGGL(k_f32_dw, dim3((unsigned)(d.n_tiles * d.splits)), dim3(256), 0, c.strm, d);
   }
   hipLaunchKernelGGL(k_train_dw_reduce<kF32DwTile>, dw_reduce_grid<kF32DwTile>(r.n_tiles), dim3(256), 0, c.strm, r);
-  return beside.join(c, check_launch("k_f32_dw"));
+  return beside.join(check_launch("k_f32_dw"));
 }
 
 // Where the heads and their gradient of the FP32 path (or the layer-by-layer one) live.
