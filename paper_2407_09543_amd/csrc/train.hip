@@ -21,6 +21,7 @@
 // The autograd entry points (ntbc_forward / ntbc_backward) keep nothing between calls: the backward
 // pass recomputes the forward activations of its batch.
 #include <algorithm>
+#include <type_traits>
 #include <cmath>
 #include <mutex>
 
@@ -891,7 +892,8 @@ struct LossArgs {
   int dsigmoid;          // write dL/dZ = dL/dY * Y (1 - Y) (the head's pre-activation) instead of dL/dY
   int tex_of[NTBC_MAX_TEXTURES];  // the BC1 textures, then the BC4 textures, each in head order
   int n_bc1;                      // how many BC1 textures
-  int g_shift;                    // a block's groups of 16 positions: 1 << g_shift
+  int g_shift;                    // a team's groups of 16 positions: 1 << g_shift
+  int cus;                        // CUs of the device
 };
 
 // Texel row `sub` (4 texels x CH bytes) of block id of texture t: from the block-major copy (the block's
@@ -1010,9 +1012,10 @@ __device__ __forceinline__ void loss_load(const LossArgs& a, int64_t p, int t, i
   }
 }
 
-template <int CH>
-__device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in, float* row_c, int t, int sub, float* le,
-                                             float* lc, float* lcde, float* lcdc, bool* bad, float de0[3], float de1[3]) {
+template <int CH, bool TILE>
+__device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in, const float* row_y, float* row_c, int t, int sub,
+                                             float* le, float* lc, float* lcde, float* lcdc, bool* bad, float de0[3],
+                                             float de1[3]) {
 #pragma clang fp contract(fast)
   constexpr bool bc1 = CH == 3;
   constexpr int N = bc1 ? 4 : 8;
@@ -1041,6 +1044,14 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in
   for (int ch = 0; ch < CH; ++ch) {
     eh0[ch] = in.eh[ch];
     eh1[ch] = in.eh[CH + ch];
+  }
+  // (the predicted colours of the lane's four texels, loaded before the palettes are built)
+  float chat4[TILE ? 1 : 4][CH];
+  if constexpr (!TILE) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int ch = 0; ch < CH; ++ch) chat4[x][ch] = row_y[(4 * sub + x) * a.C + a.ch_off[t] + ch];
   }
   const bool eight_hat = bc1 ? true : eh0[0] > eh1[0];
 #pragma unroll
@@ -1078,7 +1089,8 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in
       const int b = x * CH + ch;  // byte of the row (run-time x: words chosen by selects, no indexing)
       const uint32_t word = CH == 1 ? rw0 : (b < 4 ? rw0 : (b < 8 ? rw1 : rw2));
       c[ch] = (float)((word >> (8 * (b & 3))) & 255u) * k255;
-      chat[ch] = row_c[ci + ch];
+      if constexpr (TILE) chat[ch] = row_c[ci + ch];
+      else chat[ch] = x == 0 ? chat4[0][ch] : (x == 1 ? chat4[1][ch] : (x == 2 ? chat4[2][ch] : chat4[3][ch]));
       const float d = chat[ch] - c[ch];
       *lc += d * d;
       dchat[ch] = a.w_c * 2.0f * d * a.inv_nc;
@@ -1159,19 +1171,19 @@ __device__ __forceinline__ void texture_loss(const LossArgs& a, const LossIn& in
   }
 }
 
-// Four lanes per (texture, position).  A wave works on one texture of 16 positions at a time; a team of four
-// waves covers 1 << g_shift groups of 16 positions, and its waves take the (texture, group) pairs in turn,
-// texture by texture.  A block is one, two or four teams.  Four waves, because a block's waves go to the CU's SIMDs in turn: with one wave per texture
-// (five) the first SIMD got two of each block, two blocks filled it, and it had 40% of the CU's work.  The colours
-// of the positions come into LDS by direct copies, each lane replaces a value by its gradient there, and the
-// rows are stored in whole lines; in place, a lane's values 4 C bytes apart were a request of their own each
-// (6.7 M write requests for 42 MB), and four groups of four waves then thrash L1 (163 us).  Bound by instruction issue
-// (palette distances, softmax and straight-through gradients: some 1,500 VALU instructions per texture of 16
-// positions, 64 exponentials among them).  65,536 positions of five textures: 113 us with a wave per texture
-// and values in place, 83 so, 77 with the sign and the hard choice below.  The loss sums are reduced per block
-// and added with one atomic per block and loss (same-address atomics from every wave serialise in L2, and each
-// addition rounds the sum).
-constexpr int kLossWaves = 4, kLossTeams = 4;
+// Four lanes per (texture, position); a wave works on one texture of 16 positions at a time.  Both kernels are bound by
+// instruction issue (palette distances, softmax and straight-through gradients: some 1,500 VALU instructions per
+// texture of 16 positions, 64 exponentials among them), and differ in who takes which texture:
+//   k_loss_wave   a wave per texture, the colours read and their gradients written in place
+//   k_loss_grad   teams of four waves, two a block, that cover 1 << g_shift groups of 16 positions and take the
+//                 (texture, group) pairs in turn.  A block's waves go to the CU's SIMDs in turn, so that with five waves
+//                 the first SIMD got two of each block, two blocks filled it, and it had 40% of the CU's work.  The
+//                 colours come into LDS by direct copies, each lane replaces a value by its gradient there, and the
+//                 rows are stored in whole lines: in place, a lane's values 4 C bytes apart are a request of their own
+//                 each (6.7 M write requests for 42 MB), which the caches bear up to some size (loss_share)
+// The loss sums are reduced per block and added with one atomic per block and loss (same-address atomics from every
+// wave serialise in L2, and each addition rounds the sum: 2,048 of them left it off by 1.1e-6, 512 by 3e-7).
+constexpr int kLossWaves = 4, kLossTeams = 2;
 
 // Blocks that are resident at once with waves_per_block waves each, as a CU holds 16 of their waves at four waves
 // per SIMD, and no more than the positions fill.
@@ -1188,6 +1200,31 @@ int loss_blocks(int64_t n, int waves_per_block) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 16), resident));
 }
 
+// How a loss launch shares out `groups` groups of 16 positions: sets > 0: k_loss_wave, so many sets of waves a block; else
+// k_loss_grad with 1 << g_shift groups a team.  From 16 to 131,072 positions of 21 mixes of one to eight textures, by
+// groups a CU: a wave per texture is the shortest way while the chip is not full, and after it as long as the waves of
+// the resident blocks fill the four SIMDs about evenly and their rows stay in the caches.  Sets make a block that
+// does: eight or twelve waves of one to three textures, fifteen of five (65,536 positions of two textures 30 us, teams
+// 32 to 34; of four 51 and 55; 40,000 of five 43 and 47).  Teams take over where the rows, read and written 4 C bytes
+// apart, no longer stay there: five textures from some dozen groups a CU (65,536 positions: 74 us, teams of four
+// groups 65), six a little later (77 and 75), seven and eight from six (40,000 positions of seven colour textures 86
+// and 74).  No more than 512 blocks add to the loss sums.
+struct LossShare {
+  int sets, g_shift;
+};
+
+LossShare loss_share(int n_tex, int64_t groups, int64_t cus) {
+  constexpr double kWaves[NTBC_MAX_TEXTURES + 1] = {0, 1e18, 1e18, 24, 1e18, 13, 14, 6.5, 6.5};
+  const double load = (double)groups / (double)cus;
+  if (load <= kWaves[n_tex]) {
+    if (load <= 1) return {1, 0};
+    if (n_tex <= 2) return {n_tex == 1 && load > 4 ? 8 : 4, 0};
+    return {load <= 2 || n_tex == 4 || n_tex >= 6 ? 2 : (n_tex == 3 ? 4 : 3), 0};
+  }
+  if (n_tex >= 7 && load <= 13) return {0, 0};
+  return {0, n_tex == 6 || n_tex == 8 ? 1 : 2};
+}
+
 // Floats between a tile's rows: odd, so that a wave's 16 rows start in different banks.
 __host__ __device__ inline int loss_row(int channels) { return (16 * channels) | 1; }
 inline size_t loss_lds(int g_shift, int channels) { return (size_t)(16 << g_shift) * loss_row(channels) * sizeof(float); }
@@ -1202,11 +1239,12 @@ __device__ __forceinline__ float quad_sum(float x) {
 
 // Texture t of format CH (CH = 3: BC1, CH = 1: BC4) of position p's row `tile` of colours, all lanes of a position
 // alike in `active`; the loss sums accumulate in le .. lcdc, non-finite gradients in bad.
-template <int CH>
-__device__ __forceinline__ void loss_group(const LossArgs& a, const LossIn& in, float* tile, int64_t p, bool active, int t,
-                                           int sub, float& le, float& lc, float& lcde, float& lcdc, bool& bad) {
+template <int CH, bool TILE>
+__device__ __forceinline__ void loss_group(const LossArgs& a, const LossIn& in, const float* row_y, float* row_c, int64_t p,
+                                           bool active, int t, int sub, float& le, float& lc, float& lcde, float& lcdc,
+                                           bool& bad) {
   float de0[3] = {0, 0, 0}, de1[3] = {0, 0, 0};
-  if (active) texture_loss<CH>(a, in, tile, t, sub, &le, &lc, &lcde, &lcdc, &bad, de0, de1);
+  if (active) texture_loss<CH, TILE>(a, in, row_y, row_c, t, sub, &le, &lc, &lcde, &lcdc, &bad, de0, de1);
   // combine the endpoint gradients of the four lanes of a position (an aligned group of the wave)
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
@@ -1258,6 +1296,37 @@ __device__ __forceinline__ void loss_finish(const LossArgs& a, float le, float l
   }
 }
 
+// Texture t of format CH, every gridDim.x * teams-th group of 16 positions from `grp` on.
+template <int CH>
+__device__ __forceinline__ void loss_wave(const LossArgs& a, int t, int64_t grp, int64_t step, int lane, float& le, float& lc,
+                                          float& lcde, float& lcdc, bool& bad) {
+  const int64_t groups = (a.n + 15) / 16;
+  for (; grp < groups; grp += step) {
+    const int64_t p = grp * 16 + (lane >> 2);
+    const int sub = lane & 3;
+    const bool active = p < a.n;
+    LossIn in{};
+    if (active) loss_load<CH>(a, p, t, clamp_id(a.ids[p], a.n_positions), sub, &in);
+    loss_group<CH, false>(a, in, a.y + p * a.ld + a.E, a.dy + p * a.ld + a.E, p, active, t, sub, le, lc, lcde, lcdc, bad);
+  }
+}
+
+// A wave per texture: n_textures waves cover a group of 16 positions, the colours read and their gradients written where
+// they are; a block is one such set of waves or a few.  FMT as below.
+template <int FMT>
+__global__ void __launch_bounds__(64 * 2 * NTBC_MAX_TEXTURES) __attribute__((amdgpu_waves_per_eu(4))) k_loss_wave(LossArgs a) {
+  __shared__ float part[2 * NTBC_MAX_TEXTURES][4];
+  __shared__ int part_bad[2 * NTBC_MAX_TEXTURES];
+  float le = 0.0f, lc = 0.0f, lcde = 0.0f, lcdc = 0.0f;
+  bool bad = false;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), set = w / a.n_textures;
+  const int k = w - set * a.n_textures, lane = threadIdx.x & 63;
+  const int64_t first = blockIdx.x + (int64_t)set * gridDim.x, step = (int64_t)gridDim.x * (blockDim.x / 64 / a.n_textures);
+  if (FMT == 3 || (FMT == 0 && k < a.n_bc1)) loss_wave<3>(a, a.tex_of[k], first, step, lane, le, lc, lcde, lcdc, bad);
+  else loss_wave<1>(a, a.tex_of[k], first, step, lane, le, lc, lcde, lcdc, bad);
+  loss_finish(a, le, lc, lcde, lcdc, bad, part, part_bad);
+}
+
 // FMT = 3 or 1: materials of BC1 or of BC4 textures only; 0: of both (a wave-uniform branch).
 template <int FMT>
 __global__ void __launch_bounds__(kLossWaves * 64 * kLossTeams) __attribute__((amdgpu_waves_per_eu(4))) k_loss_grad(LossArgs a) {
@@ -1266,40 +1335,62 @@ __global__ void __launch_bounds__(kLossWaves * 64 * kLossTeams) __attribute__((a
   float le = 0.0f, lc = 0.0f, lcde = 0.0f, lcdc = 0.0f;
   bool bad = false;
   extern __shared__ float tiles[];
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), team = w / kLossWaves, wave = w % kLossWaves;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), team = w / kLossWaves;
+  // the place of the wave in its team, turned on from team to team of a CU: the first places have a texture more
+  // where the textures do not divide by four, and a block's waves go to the SIMDs in turn
+  const int wave = (w + team + ((int)blockIdx.x >= a.cus ? kLossTeams : 0)) & (kLossWaves - 1);
   const int lane = threadIdx.x & 63, sub = lane & 3, q = lane >> 2;
   const int S = loss_row(a.C), cols = 16 * a.C, per = 16 << a.g_shift, items = a.n_textures << a.g_shift;
-  const int64_t block = (int64_t)per * (blockDim.x / (64 * kLossWaves));
+  const int64_t turn = (int64_t)gridDim.x * kLossTeams;
   float* tile = tiles + team * per * S;
   const bool own = a.g_shift == 2;  // a wave's rows are its own: nothing to wait for
   const int r0 = own ? 16 * wave : wave, dr = own ? 1 : kLossWaves;
-  for (int64_t b0 = blockIdx.x * block; b0 < a.n; b0 += gridDim.x * block) {
-    const int64_t p0 = b0 + team * per;
+  // blocks first, then their teams: the last turn's teams are spread over the CUs
+  for (int64_t u0 = blockIdx.x; u0 * per < a.n; u0 += turn) {
+    const int64_t p0 = (u0 + (int64_t)team * gridDim.x) * per;
     const int rows = a.n - p0 < per ? (int)(a.n > p0 ? a.n - p0 : 0) : per, r1 = own ? min(rows, r0 + 16) : rows;
     for (int r = r0; r < r1; r += dr)
       for (int c = 0; c < cols; c += 64)
         if (c + lane < cols)
           __builtin_amdgcn_global_load_lds(a.y + (p0 + r) * a.ld + a.E + c + lane,
                                            (__attribute__((address_space(3))) void*)(tile + r * S + c), 4, 0, 0);
-    LossIn in{};
-    const auto load = [&](int i, LossIn* to) {
-      const int row = 16 * (i & ((1 << a.g_shift) - 1)) + q;
-      if (i >= items || row >= rows) return;
-      const int64_t p = p0 + row;
-      const int k = i >> a.g_shift, id = clamp_id(a.ids[p], a.n_positions);
-      if (FMT == 3 || (FMT == 0 && k < a.n_bc1)) loss_load<3>(a, p, a.tex_of[k], id, sub, to);
-      else loss_load<1>(a, p, a.tex_of[k], id, sub, to);
+    // item i: texture i >> g_shift (the BC1 ones first) of the team's group i & mask
+    const int mask = (1 << a.g_shift) - 1;
+    const auto load = [&](auto ch, int i, LossIn* in) {
+      const int row = 16 * (i & mask) + q;
+      if (i < items && row < rows)
+        loss_load<decltype(ch)::value>(a, p0 + row, a.tex_of[i >> a.g_shift], clamp_id(a.ids[p0 + row], a.n_positions), sub, in);
     };
-    load(wave, &in);
-    dma_arrived();
-    if (!own) __syncthreads();
-    for (int i = wave; i < items; i += kLossWaves) {
-      const int row = 16 * (i & ((1 << a.g_shift) - 1)) + q, k = i >> a.g_shift;
-      if (FMT == 3 || (FMT == 0 && k < a.n_bc1))
-        loss_group<3>(a, in, tile + row * S, p0 + row, row < rows, a.tex_of[k], sub, le, lc, lcde, lcdc, bad);
-      else
-        loss_group<1>(a, in, tile + row * S, p0 + row, row < rows, a.tex_of[k], sub, le, lc, lcde, lcdc, bad);
-      load(i + kLossWaves, &in);
+    const auto work = [&](auto ch, int i, const LossIn& in) {
+      const int row = 16 * (i & mask) + q;
+      loss_group<decltype(ch)::value, true>(a, in, nullptr, tile + row * S, p0 + row, row < rows, a.tex_of[i >> a.g_shift], sub, le,
+                                            lc, lcde, lcdc, bad);
+    };
+    if constexpr (FMT == 0) {
+      // (loaded when its turn comes: with the next item of either format held as well the registers do not suffice)
+      dma_arrived();
+      if (!own) __syncthreads();
+      const auto item = [&](auto ch, int i) {
+        constexpr int CH = decltype(ch)::value;
+        const int row = 16 * (i & mask) + q, k = a.tex_of[i >> a.g_shift];
+        LossIn in{};
+        if (row < rows) loss_load<CH>(a, p0 + row, k, clamp_id(a.ids[p0 + row], a.n_positions), sub, &in);
+        loss_group<CH, true>(a, in, nullptr, tile + row * S, p0 + row, row < rows, k, sub, le, lc, lcde, lcdc, bad);
+      };
+      const int items1 = a.n_bc1 << a.g_shift;
+      int i = wave;
+      for (; i < items1; i += kLossWaves) item(std::integral_constant<int, 3>{}, i);
+      for (; i < items; i += kLossWaves) item(std::integral_constant<int, 1>{}, i);
+    } else {
+      const std::integral_constant<int, FMT> ch;
+      LossIn in{};
+      load(ch, wave, &in);
+      dma_arrived();
+      if (!own) __syncthreads();
+      for (int i = wave; i < items; i += kLossWaves) {
+        work(ch, i, in);
+        load(ch, i + kLossWaves, &in);
+      }
     }
     if (!own) __syncthreads();
     for (int r = r0; r < r1; r += dr)
@@ -2682,25 +2773,24 @@ int loss_grad(const Shape& s, const ntbc_targets* t, const float* heads, const i
   a.n_bc1 = n_tex;
   for (int i = 0; i < s.n_textures; ++i)
     if (s.formats[i] != NTBC_BC1) a.tex_of[n_tex++] = i;
-  // One group a team while the teams are resident: the textures of a position side by side is the shortest way
-  // (16,384 positions of five textures 28 us, with four groups a team 38).  Beyond that, the groups that give the
-  // waves equal shares, as far as four teams of a CU have LDS for them (65,536 positions: five textures 90 us with
-  // one group, 78 with two, 77 with four; six textures 95, 86, 91).
   const int64_t groups = ceil_div(n, 16), cus = loss_blocks((int64_t)1 << 40, 16);
-  if (groups > 4 * cus)
-    while ((s.n_textures << a.g_shift) % kLossWaves != 0 && loss_lds(a.g_shift + 1, s.channels) <= 39 * 1024) ++a.g_shift;
-  // Teams share a block where there are more than 512, for fewer additions to the loss sums (one team a block left
-  // the sum of 2,048 off by 1.1e-6; 512 and 256 blocks by 3e-7, as the one wave per texture did).  Four only where
-  // each has several groups or more than one turn: they wait for each other (16,384 positions of five textures 33 us,
-  // with two a block 28).
+  a.cus = (int)cus;
+  const LossShare share = loss_share(n_tex, groups, cus);
+  if (share.sets > 0) {
+    void (*const kern)(LossArgs) = a.n_bc1 == 0 ? k_loss_wave<1> : a.n_bc1 == n_tex ? k_loss_wave<3> : k_loss_wave<0>;
+    const int64_t resident = cus * std::max<int64_t>(1, 16 / (n_tex * share.sets));
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, std::min(ceil_div(groups, share.sets), resident))),
+                       dim3(64 * n_tex * share.sets), 0, strm, a);
+    return check_launch("k_loss_wave");
+  }
+  a.g_shift = share.g_shift;
+  while (a.g_shift > 0 && loss_lds(a.g_shift, s.channels) > 39 * 1024) --a.g_shift;  // (two blocks a CU)
   const int64_t need = ceil_div(groups, (int64_t)1 << a.g_shift);
-  const int teams = groups > 4 * cus && need >= 4 * cus ? kLossTeams : (need > 2 * cus ? 2 : 1);
-  const size_t lds = teams * loss_lds(a.g_shift, s.channels);
-  const dim3 block(64 * kLossWaves * teams);
-  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(need, teams), teams == kLossTeams ? cus : 2 * cus)));
+  const size_t lds = kLossTeams * loss_lds(a.g_shift, s.channels);
   void (*const kern)(LossArgs) = a.n_bc1 == 0 ? k_loss_grad<1> : a.n_bc1 == n_tex ? k_loss_grad<3> : k_loss_grad<0>;
   NTBC_HIP(allow_lds((const void*)kern, lds));
-  hipLaunchKernelGGL(kern, grid, block, lds, strm, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, std::min(ceil_div(need, kLossTeams), 2 * cus))),
+                     dim3(64 * kLossWaves * kLossTeams), lds, strm, a);
   return check_launch("k_loss_grad");
 }
 

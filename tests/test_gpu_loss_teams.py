@@ -1,5 +1,5 @@
-"""The loss at the batches of which a block has two or four teams of waves, a team with no positions, and a second
-turn of the blocks over the batch: quarters of a batch, launched alone, differ from it by the mean's 1/n, a
+"""The loss at batches of every way of sharing them out (sets of waves, teams of one, two or four groups, a team with no
+positions, a second turn of the blocks): quarters of a batch, launched alone, differ from it by the mean's 1/n, a
 factor of exactly 4 (the smaller launches are compared with the oracle in test_gpu_loss_groups.py)."""
 import numpy as np
 import pytest
@@ -13,9 +13,9 @@ pytestmark = pytest.mark.gpu
 
 
 # 40,000: 2,500 groups of 16; 65,640 = 65,536 + 104: past one turn of 256 blocks of 256 positions, the last group ragged;
-# 81,940: ragged in the quarters too
+# 81,940: ragged in the quarters too; 104,000: teams for three textures
 @pytest.mark.parametrize("formats", FORMATS + ["ccsss"])
-@pytest.mark.parametrize("quarter", [10000, 16410, 20485])
+@pytest.mark.parametrize("quarter", [10000, 16410, 20485, 26000])
 def test_quarters(formats, quarter):
     ensure_built()
     side, n = 64, 4 * quarter
