@@ -16,6 +16,7 @@ from __future__ import annotations
 import json
 import os
 import sys
+import time
 
 import torch
 
@@ -44,9 +45,20 @@ def _time(batch, reps: int, warmup: int = 2) -> float:
     return start.elapsed_time(end) / reps
 
 
+def _settle(batch, seconds: float = 0.2):
+    """Runs the batch until the GPU has been busy with it for `seconds`, so that its clocks hold the rate of the work
+    when the shapes are timed."""
+    torch.cuda.synchronize()
+    end = time.perf_counter() + seconds
+    while time.perf_counter() < end:
+        batch.run()
+        torch.cuda.synchronize()
+
+
 def tune(batch, reps: int = 10):
     """{key: {"waves": best, "ms": {shape: batch ms}}} for every instance of the batch (non-BF16
     instances have the 4-wave shape only); leaves the batch at the chosen shapes."""
+    _settle(batch)
     table = {}
     for gi, g in enumerate(batch.groups()):
         times = {}
