@@ -1720,9 +1720,9 @@ bool res_batch_instance_fp16(int hid, int ks0, int nh, const void** fn, BatchLau
   NTBC_LDS_INSTANCE_L(LP, 256, 4, 2, 2, 3)
 
 // Batched instances: the same shapes with the LDS-staged epilogue in every precision, BF16 with the register
-// epilogue for two BC1 + one to three BC4 textures at width 256 (two middle layers unrolled), and bfloat16
-// and half with the any-mix epilogue and one or two middle layers: resident weights at width 64, streamed at 128
-// and 256 with three or four input K-steps.
+// epilogue for two BC1 + one to three BC4 textures at widths 64 and 128 (run-time layer count) and 256 (two middle
+// layers unrolled), and bfloat16 and half with the any-mix epilogue and one or two middle layers: resident weights at
+// width 64, streamed at 128 and 256 with three or four input K-steps.
 #define NTBC_BATCH_INSTANCE_L(LP, H, K, NH, NB1, NB4)                                                         \
   if (hid == H && ks0 == K && nh == NH && nb1 == NB1 && (NB1 < 0 || nb4 == NB4) && waves == NTBC_BATCH_W) {   \
     *fn = (const void*)k_infer_lds_batch<LP, H, K, NH, NB1, NB4, NTBC_BATCH_W>;                              \
@@ -1775,7 +1775,8 @@ bool lds_instance_fp8(int hid, int ks0, int nh, int nb1, int nb4, const void** f
   bool batch_instance_bf16_w##WV(int hid, int ks0, int nh, int nb1, int nb4, int waves, const void** fn,         \
                                  BatchLaunch* launch) {                                                         \
     NTBC_BATCH_INSTANCES(Lp::BF16)                                                                              \
-    NTBC_BATCH_REG(256, 4, 2) NTBC_BATCH_ANY(Lp::BF16)                                                          \
+    NTBC_BATCH_REG(64, 4, -1) NTBC_BATCH_REG(128, 4, -1) NTBC_BATCH_REG(256, 4, 2)                              \
+    NTBC_BATCH_ANY(Lp::BF16)                                                                                    \
     return false;                                                                                               \
   }
 bool batch_instance_bf16_w2(int, int, int, int, int, int, const void**, BatchLaunch*);
@@ -1941,8 +1942,8 @@ constexpr int kTileWaves[3] = {2, 4, 8};
 int waves_index(int w) { return w == 2 ? 0 : (w == 8 ? 2 : 1); }
 
 // Whether a group runs with resident weights: any mix at width 64, where a CU holds two four-wave workgroups'
-// copies.  (At width 128 a copy fills the CU: eight-wave workgroups of it decoded 16 materials with their mip
-// chains in 2.48 ms against 2.44 streamed in four-wave tiles.)
+// copies.  (At width 128 a copy fills the CU: four materials with their mip chains, all on the any-mix epilogue, took
+// 507 us in eight-wave workgroups of it, 478 streamed in four-wave tiles.)
 bool batch_resident(const BatchGroup& gr) { return gr.any && gr.hid == 64; }
 
 // Numbers the tiles of a group's items for its tile shape.  Resident weights: a workgroup takes the fewest rounds
@@ -2018,10 +2019,14 @@ bool any_mix(const Plan& p) {
 
 // Instances with the register epilogue of one mix: single range (any precision) for two BC1 + three BC4
 // textures at the paper-scale shape (FP8: the 1024^2 one too); batched (BF16) for two BC1 + one to three BC4
-// textures at width 256 (four K-steps, two middle layers).
+// textures at widths 64, 128 (four input K-steps, run-time layer count) and 256 (four K-steps, two middle layers).
+// Their epilogue has every slot at compile time, the any-mix one asks which texture a channel belongs to: materials of
+// those mixes with their mip chains, four of each width, 272 us against 422 (64), 392 against 478 (128), 762
+// against 796 (256).
 bool reg_instance(const Plan& p, int nb1, int nb4, bool batch) {
   if (batch) {
-    const bool shape = p.hid_inst == 256 && p.ksteps[0] == 4 && batch_nh(p) == 2;
+    const bool shape = (p.hid_inst == 256 && p.ksteps[0] == 4 && batch_nh(p) == 2) ||
+                       ((p.hid_inst == 64 || p.hid_inst == 128) && p.ksteps[0] == 4 && batch_nh(p) == -1);
     return p.precision == NTBC_BF16 && shape && nb1 == 2 && nb4 >= 1 && nb4 <= 3;
   }
   const bool shape =
@@ -2041,6 +2046,8 @@ RegPlan reg_plan(const Plan& p, bool batch = false) {
     r.nb1 = nb1;
     r.nb4 = nb4;
   } else if (any_mix(p) && (!batch || p.hid_inst == 64 || p.ksteps[0] >= 3)) {
+    // (batched at widths 128 and 256 the any-mix instances, three tile shapes each, exist for three and four input
+    // K-steps, i.e. five levels of eight features and more; below, the staged epilogue, not timed against them)
     r.nb1 = nb1;
     r.nb4 = nb4;
     r.any = true;

@@ -52,7 +52,7 @@ def test_batch_rounds(precision):
     # width 64: 512 workgroups of four waves are resident, so 65,536 positions are one round; two items of more
     ensure_built()
     prec = ntbc.PRECISIONS[precision]
-    made = [model(64, 3, 8, (1, 1, 4), 300, 300, 1), model(64, 3, 8, (4, 1, 4, 4), 411, 205, 2)]
+    made = [model(64, 3, 8, (1, 4, 4), 300, 300, 1), model(64, 3, 8, (4, 1, 4, 4), 411, 205, 2)]
     ranges = [(11, 300 * 300 - 11 - 3), (0, 411 * 205)]
     batch = ntbc.Batch([(m, m.desc, *r) for (_, _, _, m), r in zip(made, ranges)], prec, tiles={})
     assert len(batch.groups()) == 1
