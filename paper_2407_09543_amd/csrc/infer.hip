@@ -339,18 +339,21 @@ __global__ void __launch_bounds__(64 * kWaves) k_infer_lp(InferArgs a) {
   int bx, by;
   dev::block_of(id, last, a.grid.blocks_w, &bx, &by);
 
+  // the operands go through the wave's LDS (its heads' place later), for the gather to be a loop: unrolled sixteen
+  // times it was 150 KB of code, and beyond what the compiler unrolls the operands were indexed in scratch, which
+  // cost 7% at width 256 (288 outputs, 16,384 positions: 127.7 us against 119.1 unrolled)
+  const int wave_floats = max(32 * a.head_stride, S * 64 * 4);
+  float* y = lds + wave * wave_floats;
+  u32x4* xs = reinterpret_cast<u32x4*>(y) + lane;
+#pragma unroll 1
+  for (int s = 0; s < a.ksteps[0]; ++s) {
+    float v[8];
+    dev::features<8>(a.grid, 16 * s + 8 * g, bx, by, v);
+    xs[s * 64] = x8_of<L>(v);
+  }
   u32x4 bin[S];
 #pragma unroll
-  for (int s = 0; s < S; ++s) {
-    float v[8];
-    if (s < a.ksteps[0]) {
-      dev::features<8>(a.grid, 16 * s + 8 * g, bx, by, v);
-    } else {
-#pragma unroll
-      for (int m = 0; m < 8; ++m) v[m] = 0.0f;
-    }
-    bin[s] = x8_of<L>(v);
-  }
+  for (int s = 0; s < S; ++s) bin[s] = s < a.ksteps[0] ? xs[s * 64] : u32x4{};
 
   const u32x4* wp = reinterpret_cast<const u32x4*>(a.wpack);
   // hidden layers
@@ -390,7 +393,6 @@ __global__ void __launch_bounds__(64 * kWaves) k_infer_lp(InferArgs a) {
     for (int s = 0; s < S; ++s) bin[s] = bout[s];
   }
   // head layer: sigmoid outputs into LDS
-  float* y = lds + wave * 32 * a.head_stride;
   {
     const int layer = a.n_layers - 1;
     const int ks = a.ksteps[layer];
@@ -2312,7 +2314,8 @@ int infer_blocks(const Plan& p, const ntbc_model_desc* d, const ntbc_params* prm
     return check_launch("ntbc_infer_blocks");
   }
   const int64_t nwg = ceil_div(n_blocks, (int64_t)ppw * kWaves);
-  const size_t lds = (size_t)kWaves * ppw * a.head_stride * sizeof(float);
+  // (16-bit: a wave's place holds its first layer's operands before its heads)
+  const size_t lds = kWaves * std::max<size_t>((size_t)ppw * a.head_stride * sizeof(float), lp16 ? (size_t)p.hid_inst * 64 : 0);
   const dim3 grid((unsigned)nwg), block(64 * kWaves);
   NTBC_REQUIRE(lds <= 160 * 1024, "head_dim %d needs %zu bytes of LDS", s.head_dim, lds);
   if (lds > 64 * 1024) {
