@@ -367,6 +367,11 @@ typedef struct {
 /* Training precision (ntbc_forward, ntbc_backward, ntbc_hparams.precision): NTBC_FP32 or NTBC_BF16
  * (bfloat16 operands of the MLP products, FP32 accumulation); others return NTBC_EUNSUPPORTED. */
 
+/* ntbc_backward and the training steps (both precisions, the two-network layout too) may put part of a large
+ * batch's grid scatter on a stream of the library's own, which is joined back into `stream` within the call: the
+ * call stays ordered on `stream`, and a capture of it holds both branches.  Calls on different streams and
+ * threads take different ones, or none. */
+
 /* Forward pass for a batch (paper Sec. 3.2, Fig. NTBC training, network part): the sigmoid heads of
  * block positions ids[0..n) from the FP32 master grid (fake-quantised per level when qat = 1: Sec. 3.3,
  * Eq. quantizer with s, z from the level's min/max) and FP32 weights.  heads_out: float[n][head_dim].

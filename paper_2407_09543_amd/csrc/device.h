@@ -387,9 +387,9 @@ __device__ __forceinline__ Bc4Pal bc4_from_heads(const float* ep, const float* t
 // monotone in weight order in both modes (eight: e0 > interpolants > e1; six: 0 <= e0 <= interpolants
 // <= e1 <= 1) and rounding is monotone, so the float32 squared distances are unimodal in the weight
 // index: the first minimum is the last index whose distance is strictly below its predecessor's.
-// Squares of differing |d| differ too (their gap is at least two units in the last place before
-// rounding, and no two distinct entries are both near enough to x to underflow), so the |d| themselves
-// are compared: a subtraction, a comparison and a select per entry.
+// Squares of differing |d| differ too (adjacent |d| have squares at least 1.41 units in the last place apart before
+// rounding, and more than one suffices; no two distinct entries are both near enough to x to underflow), so the |d|
+// themselves are compared: a subtraction, a comparison and a select per entry.
 __device__ __forceinline__ uint32_t bc4_code(const Bc4Pal& p, float x) {
   float prev = __fsub_rn(x, p.pal[0]);
   uint32_t sh = 0;  // 3 * weight index of the first minimum so far

@@ -1048,9 +1048,11 @@ k_infer_lds(InferArgs a, ChunkTable ct) {
 // copied into LDS once and the waves then run tile after tile on their own.  Streamed in chunks, these
 // networks' products (512 cycles a chunk at width 128) are shorter than the latency of the next chunk's copy,
 // so every chunk ended in a wait and a barrier.  Eight waves share a copy (one workgroup a CU, two waves a
-// SIMD by registers) and take a contiguous run of tiles; fewer waves while that gives more CUs work.
-// 1024^2, 48-128x3-162, half: 23.4 -> 23.0 us (one tile a wave);
-// 4096^2 of that network and 64 inputs, bfloat16: 446 -> 252; 256^2, 16-64x2-72: 15.1 -> 10.5.
+// SIMD by registers) and take a contiguous run of tiles; as many as a CU has tiles while those are fewer, but four at
+// least.  Pack and decode against the streamed kernels, 48-128x3: 1024^2 texture (one tile a wave), half, 162 heads
+// 24.8 -> 24.2 us, 144 heads (no instance of their mix) 31.1 -> 22.9; 4096^2, bfloat16, 273 -> 241 and 382 -> 223; 256^2,
+// 16-64x2-72, 18.6 -> 12.6.  With the weights packed before, up to 32,768 positions of the 162 heads
+// take 0.2 to 0.6 us longer (15.8 -> 16.4): the first product waits for the whole copy.
 constexpr int kResWaves = 8;
 
 struct ResArgs {
@@ -2751,7 +2753,8 @@ extern "C" int ntbc_infer_batch(const void* table, const void* table_device, voi
 // texel's codes are taken as its colours come out and shifted into the lane's words.  The colour
 // network's weights are read from LDS.  Four waves a SIMD (128 registers) instead of two with 1.5 filled
 // (249 registers and the staged heads, 23 KB a wave): 4096^2, two BC1 and four BC4 textures, uint8
-// grids, 2,997 -> 1,044 us.
+// grids, 2,997 -> 1,044 us.  <2,3>, <3,2> and <4,1> (five textures a lane, mixed) spill 13 to
+// 20 registers.
 #if NTBC_PART(9) || NTBC_PART(11)
 namespace {
 
@@ -3282,8 +3285,9 @@ extern "C" int ntbc_faithful_infer(const ntbc_faithful_desc* d, const ntbc_faith
   FaLaunch launch = nullptr;
   NTBC_REQUIRE(s.n1 <= 1 ? fa_instance_lo(s.n1, s.n4, &fn, &launch) : fa_instance_hi(s.n1, s.n4, &fn, &launch),
                "no kernel instance for %d BC1 and %d BC4 slots", s.n1, s.n4);
-  // waves per workgroup: eight share the weights' LDS copy (two such workgroups fill a CU); fewer while that
-  // leaves CUs without a workgroup
+  // waves per workgroup: eight share the weights' LDS copy; two such workgroups fill a CU with up to seven palette
+  // words a lane (3 n1 + 2 n4; 81 KB), one fits with more, which leaves two waves a SIMD; fewer waves while
+  // that leaves CUs without a workgroup
   const int64_t tiles = ceil_div(n_blocks, 32);
   int waves = kFaMaxWaves;
   while (waves > 1 && tiles < 512 * (int64_t)waves) waves /= 2;

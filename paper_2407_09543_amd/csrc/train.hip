@@ -7,8 +7,8 @@
 //     k_features, k_f32_fwd         FP32 products, layers chained in registers (train_f32.h)
 //     k_f32_fwd_narrow              the same for the two-network layout, features included (train_f32.h)
 //     k_features, k_gemm(_bf16)     other shapes, layer by layer (bias + ReLU / sigmoid epilogues)
-//   k_loss_grad                     L_e, L_c and both decoded-colour terms, dL/dY with the STE
-//   k_dsigmoid                      dZ_out = dY * Y (1 - Y) (in the training step: inside k_loss_grad)
+//   k_loss_wave or k_loss_grad      L_e, L_c and both decoded-colour terms, dL/dY with the STE (loss_share)
+//   k_dsigmoid                      dZ_out = dY * Y (1 - Y) (in the training step: inside the loss kernel)
 //   the backward, one of
 //     k_train_bwd, k_train_dw       dZ chained down to dX, then dW and db; k_train_dw_reduce adds the ranges
 //     k_f32_bwd, k_f32_dw           the same in FP32 (train_f32.h)
@@ -1466,7 +1466,7 @@ __device__ __forceinline__ void naive_texture_loss(const NaiveLossArgs& a, int64
   }
 }
 
-// Four lanes per (texture, position), one wave per texture, as k_loss_grad.
+// Four lanes per (texture, position), one wave per texture, as k_loss_wave.
 __global__ void __launch_bounds__(64 * NTBC_MAX_TEXTURES) k_loss_naive(NaiveLossArgs a) {
   __shared__ float part[NTBC_MAX_TEXTURES];
   __shared__ int part_bad[NTBC_MAX_TEXTURES];
@@ -1642,7 +1642,7 @@ __global__ void k_export_qparams(const int* __restrict__ stats, int n_levels, fl
 //                  activations never leave registers between layers; writes the heads, the ReLU
 //                  masks (one bit per activation) and the bfloat16 layer inputs position-contiguous
 //                  ([neuron][position], the K-major operand of the weight gradient)
-//   k_loss_grad    dL/dZ of the head (as for the unfused step)
+//   the loss       dL/dZ of the head (as for the unfused step)
 //   k_train_bwd    per 128 positions: dZ_head -> dZ_k = (W_{k+1}^T dZ_{k+1}) * mask_k down to
 //                  dX = W_0^T dZ_0, chained in registers like the forward; writes every dZ_k
 //                  position-contiguous in bfloat16 and dX in FP32 for the grid scatter
@@ -1677,7 +1677,6 @@ __device__ __forceinline__ u32x4 fpack8(const float* v) {
   return u32x4{fbf2(v[0], v[1]), fbf2(v[2], v[3]), fbf2(v[4], v[5]), fbf2(v[6], v[7])};
 }
 
-__device__ __forceinline__ uint16_t fbf1(float x) { return (uint16_t)(fbf2(x, 0.0f) & 0xFFFFu); }
 
 // Sigmoid from the hardware exp2 and reciprocal (each within about one ulp): |error| < 3e-7 for |z| < 64,
 // far inside the bfloat16 products' rounding.
