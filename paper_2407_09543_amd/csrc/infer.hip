@@ -681,15 +681,21 @@ __device__ __forceinline__ void last_middle_fp8(const u32x2 (&in)[S], u32x4 (&ou
 // texels 8g .. 8g+7 and endpoint g:
 //   BC1 texture k: colour channel c of texel 8g+i at slot 24k + 3i + c, endpoint g (R, G, B) at kE1 + 3k + c
 //   BC4 texture k: texel 8g+i at slot kC4 + 8k + i, endpoint g at kE4 + k
-// (27 NB1 + 9 NB4 = head_dim / 2 slots).  The two lanes of a position exchange their quantised
+// (27 NB1 + 9 NB4 = head_dim / 2 slots); or BY_CH, batches at widths 64 and 128: the any-mix order below with
+// the BC1 textures first, so that a plan may decode such a model with either epilogue from the same packed
+// weights.  The two lanes of a position exchange their quantised
 // endpoint g and their half of the index bits with one lane swap each, so the BC words are made
 // without staging the heads in LDS, and each palette is built by two lanes instead of four.
-template <int NB1, int NB4>
+template <int NB1, int NB4, bool BY_CH = false>
 struct RegLayout {
   static constexpr int kC4 = 24 * NB1;
   static constexpr int kE1 = kC4 + 8 * NB4;
   static constexpr int kE4 = kE1 + 3 * NB1;
   static constexpr int kUsed = kE4 + NB4;
+  static constexpr int bc1(int k, int i, int c) { return BY_CH ? 9 * (3 * k + c) + i : 24 * k + 3 * i + c; }
+  static constexpr int bc4(int k, int i) { return BY_CH ? 9 * (3 * NB1 + k) + i : kC4 + 8 * k + i; }
+  static constexpr int ep1(int k, int c) { return BY_CH ? 9 * (3 * k + c) + 8 : kE1 + 3 * k + c; }
+  static constexpr int ep4(int k) { return BY_CH ? 9 * (3 * NB1 + k) + 8 : kE4 + k; }
   static_assert(NB1 <= 2 && NB4 <= 4 && kUsed <= 16 * kHeadTiles, "slot layout");
 };
 
@@ -703,10 +709,10 @@ __device__ __forceinline__ int reg_canonical(ArgsT a, int slot, int g) {
   return a.reg_ep[NB1 + slot - Y::kE4] + g;
 }
 
-template <int NB1, int NB4, typename ArgsT>
+template <int NB1, int NB4, bool BY_CH, typename ArgsT>
 __device__ __forceinline__ void reg_epilogue(ArgsT a, const f32x16_t (&h)[kHeadTiles], const float* tab, int g,
                                              int64_t id, bool valid) {
-  using Y = RegLayout<NB1, NB4>;
+  using Y = RegLayout<NB1, NB4, BY_CH>;
 #define NTBC_SLOT(x) h[(x) / 16][(x) % 16]
   // value of the partner lane (lane ^ 32): one LDS-crossbar permute with a fixed address
   const int partner = (((int)threadIdx.x & 63) ^ 32) << 2;
@@ -715,9 +721,9 @@ __device__ __forceinline__ void reg_epilogue(ArgsT a, const f32x16_t (&h)[kHeadT
   uint32_t w1 = 0, w4 = 0;
 #pragma unroll
   for (int k = 0; k < NB1; ++k)
-    w1 |= dev::rgb565(NTBC_SLOT(Y::kE1 + 3 * k), NTBC_SLOT(Y::kE1 + 3 * k + 1), NTBC_SLOT(Y::kE1 + 3 * k + 2)) << (16 * k);
+    w1 |= dev::rgb565(NTBC_SLOT(Y::ep1(k, 0)), NTBC_SLOT(Y::ep1(k, 1)), NTBC_SLOT(Y::ep1(k, 2))) << (16 * k);
 #pragma unroll
-  for (int k = 0; k < NB4; ++k) w4 |= (uint32_t)dev::quant_bits(NTBC_SLOT(Y::kE4 + k), 255.0f) << (8 * k);
+  for (int k = 0; k < NB4; ++k) w4 |= (uint32_t)dev::quant_bits(NTBC_SLOT(Y::ep4(k)), 255.0f) << (8 * k);
   const uint32_t o1 = NB1 > 0 ? swap(w1) : 0u;
   const uint32_t o4 = NB4 > 0 ? swap(w4) : 0u;
   const uint32_t a1 = g ? o1 : w1, b1 = g ? w1 : o1;  // endpoint 0 / endpoint 1 words
@@ -729,7 +735,7 @@ __device__ __forceinline__ void reg_epilogue(ArgsT a, const f32x16_t (&h)[kHeadT
     uint32_t codes = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      codes |= dev::bc1_code(p, NTBC_SLOT(24 * k + 3 * i), NTBC_SLOT(24 * k + 3 * i + 1), NTBC_SLOT(24 * k + 3 * i + 2))
+      codes |= dev::bc1_code(p, NTBC_SLOT(Y::bc1(k, i, 0)), NTBC_SLOT(Y::bc1(k, i, 1)), NTBC_SLOT(Y::bc1(k, i, 2)))
                << (2 * i);
     const uint32_t hi = swap(codes);  // texels 8..15 from lane group 1
     if (g == 0 && valid)
@@ -740,22 +746,23 @@ __device__ __forceinline__ void reg_epilogue(ArgsT a, const f32x16_t (&h)[kHeadT
     const dev::Bc4Pal p = dev::bc4_palette((int)((a4 >> (8 * k)) & 255u), (int)((b4 >> (8 * k)) & 255u), tab);
     uint32_t codes = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) codes |= dev::bc4_code(p, NTBC_SLOT(Y::kC4 + 8 * k + i)) << (3 * i);
+    for (int i = 0; i < 8; ++i) codes |= dev::bc4_code(p, NTBC_SLOT(Y::bc4(k, i))) << (3 * i);
     const uint32_t hi = swap(codes);
     if (g == 0 && valid)
       a.out[(int64_t)a.reg_tex[NB1 + k] * a.n + row] =
           (uint64_t)p.e0 | ((uint64_t)p.e1 << 8) | (((uint64_t)codes | ((uint64_t)hi << 24)) << 16);
   }
-  if (a.heads && valid) {
-    float* hr = a.heads + row * a.head_dim;
+  if constexpr (!BY_CH)  // (batches write no heads)
+    if (a.heads && valid) {
+      float* hr = a.heads + row * a.head_dim;
 #pragma unroll
-    for (int x = 0; x < Y::kUsed; ++x) hr[reg_canonical<NB1, NB4>(a, x, g)] = NTBC_SLOT(x);
-  }
+      for (int x = 0; x < Y::kUsed; ++x) hr[reg_canonical<NB1, NB4>(a, x, g)] = NTBC_SLOT(x);
+    }
 #undef NTBC_SLOT
 }
 
 // The same epilogue for any mix of textures with at most kRegChannels colour channels in all: colour channel
-// q (in the texel's order) has slots 9q .. 9q+7 for its eight texels and 9q + 8 for its endpoint g, so that
+// q (in the texel's order; in batches, which write no heads, the BC1 textures' first) has slots 9q .. 9q+7 for its eight texels and 9q + 8 for its endpoint g, so that
 // every slot is a compile-time register and only which texture a channel belongs to is a run-time
 // (uniform) question.  9 C slots, as many head tiles as the canonical order.
 constexpr int kRegChannels = kRegSlots;
@@ -1009,7 +1016,8 @@ __device__ __forceinline__ void infer_tile(ArgsT a, ChunksT ct, int64_t tile) {
     }
   }
   if constexpr (NB1 >= 0) {
-    reg_epilogue<NB1, NB4>(a, hacc, tab, g, id, pos0 + j <= last);
+    constexpr bool kByChannel = HID <= 128 && L != Lp::FP8;
+    reg_epilogue<NB1, NB4, kByChannel>(a, hacc, tab, g, id, pos0 + j <= last);
     return;
   }
   // otherwise staged in LDS 16 positions at a time for the pack
@@ -2014,8 +2022,10 @@ int launch_batch_group(const BatchGroup& gr, const BatchItem* items, unsigned* d
 // an instance for its texture mix and network shape, else nb1 = -1 (heads staged in LDS).
 struct RegPlan {
   int nb1 = -1, nb4 = 0;
-  bool any = false;  // the any-mix slots (reg_any_epilogue)
+  bool any = false;         // the any-mix epilogue (reg_any_epilogue)
+  bool by_channel = false;  // its slots: channel chan[q] has 9q .. 9q + 8
   int tex[NTBC_MAX_TEXTURES] = {};
+  int chan[kRegSlots] = {};
 };
 
 // Any-mix instances: bfloat16 and half, one or two middle layers, at most kRegChannels colour channels.
@@ -2042,7 +2052,9 @@ bool reg_instance(const Plan& p, int nb1, int nb4, bool batch) {
   return shape && batch_nh(p) == 2 && nb1 == 2 && nb4 == 3;
 }
 
-RegPlan reg_plan(const Plan& p, bool batch = false) {
+// `any`: a batch decodes the model with the any-mix epilogue though its mix has an instance (batch_merge).  The order
+// of the packed weights does not depend on it.
+RegPlan reg_plan(const Plan& p, bool batch = false, bool any = false) {
   const Shape& s = p.s;
   RegPlan r;
   int nb1 = 0, nb4 = 0;
@@ -2050,17 +2062,64 @@ RegPlan reg_plan(const Plan& p, bool batch = false) {
     if (s.formats[t] == NTBC_BC1) r.tex[nb1++] = t;
   for (int t = 0; t < s.n_textures; ++t)
     if (s.formats[t] == NTBC_BC4) r.tex[nb1 + nb4++] = t;
-  if (!s.naive && reg_instance(p, nb1, nb4, batch) && 27 * nb1 + 9 * nb4 <= 16 * p.otiles[s.n_layers - 1]) {
+  if (!any && !s.naive && reg_instance(p, nb1, nb4, batch) && 27 * nb1 + 9 * nb4 <= 16 * p.otiles[s.n_layers - 1]) {
     r.nb1 = nb1;
     r.nb4 = nb4;
+    r.by_channel = batch && p.hid_inst <= 128;
   } else if (any_mix(p) && (!batch || p.hid_inst == 64 || p.ksteps[0] >= 3)) {
     // (batched at widths 128 and 256 the any-mix instances, three tile shapes each, exist for three and four input
     // K-steps, i.e. five levels of eight features and more; below, the staged epilogue, not timed against them)
     r.nb1 = nb1;
     r.nb4 = nb4;
-    r.any = true;
+    r.any = r.by_channel = true;
+  }
+  if (r.by_channel) {
+    int q = 0;
+    for (int k = 0; k < s.n_textures; ++k) {
+      const int t = batch ? r.tex[k] : k;
+      for (int c = 0; c < (s.formats[t] == NTBC_BC1 ? 3 : 1); ++c) r.chan[q++] = s.ch_off[t] + c;
+    }
   }
   return r;
+}
+
+// Which of a batch's items leave the instance of their mix for the any-mix one: fewer launches against a shorter
+// epilogue.  A launch of its own costs a group some 12 us (its first copy, its last tiles); with the instance of
+// its mix it gains that back at the positions of own_launch, by materials of width 64 and 128 with their mip
+// chains: one 2048^2 material of three to five textures (350,000 positions) 73.8 -> 51.1, 81.6 -> 64.2 and 88.6 -> 68.3 us
+// (64), 89.4 -> 72.6, 99.9 -> 78.9 and 107.2 -> 102.3 (128).  So three small materials, one of each mix, share a launch
+// (512^2: 32 us, 53 in three, at width 64; 40 and 60 at 128) and three large ones do not (3072^2: 510 and 366; 655 and
+// 527).  Of the 2^3 choices of a width and depth, the one with the least of both.
+std::vector<char> batch_merge(const std::vector<Plan>& plans, const ntbc_batch_item* items) {
+  const auto own_launch = [](int hid, int nb4) { return hid == 64 ? 180e3 : nb4 < 3 ? 160e3 : 780e3; };
+  std::vector<char> any(plans.size(), 0);
+  for (int hid = 64; hid <= 128; hid *= 2)
+    for (int mid = 1; mid <= 2; ++mid) {
+      int64_t n[3] = {0, 0, 0};  // positions by the number of BC4 textures less one
+      bool others = false;       // items of other mixes, which launch the any-mix instance anyway
+      std::vector<int> mix(plans.size(), -1);
+      for (size_t i = 0; i < plans.size(); ++i) {
+        const Plan& p = plans[i];
+        if (p.hid_inst != hid || p.s.n_layers - 2 != mid || p.ksteps[0] != 4 || !any_mix(p)) continue;
+        const RegPlan r = reg_plan(p, true);
+        if (r.any) others = others || items[i].n_blocks > 0;
+        else if (r.nb1 >= 0) n[mix[i] = r.nb4 - 1] += items[i].n_blocks;
+      }
+      int best = 0;
+      double least = 1e30;
+      for (int merged = 0; merged < 8; ++merged) {
+        double cost = others || merged != 0;
+        for (int k = 0; k < 3; ++k)
+          cost += merged >> k & 1 ? (double)n[k] / own_launch(hid, k + 1) : (double)(n[k] > 0);
+        if (cost < least) {
+          least = cost;
+          best = merged;
+        }
+      }
+      for (size_t i = 0; i < plans.size(); ++i)
+        if (mix[i] >= 0) any[i] = best >> mix[i] & 1;
+    }
+  return any;
 }
 
 // Head offset of endpoint g of colour channel q.
@@ -2073,10 +2132,10 @@ int channel_endpoint(const Shape& s, int q, int g) {
 // Canonical head neuron of packed head row `row` under the register layout, -1 for a padding row.
 int reg_source(const Shape& s, const RegPlan& r, int row) {
   const int t = row / 32, g = (row % 8) / 4, slot = 16 * t + 4 * ((row % 32) / 8) + row % 4;
-  if (r.any) {
+  if (r.by_channel) {
     const int q = slot / 9, i = slot % 9;
     if (q >= s.channels) return -1;
-    return i < 8 ? s.endpoint_dim + (8 * g + i) * s.channels + q : channel_endpoint(s, q, g);
+    return i < 8 ? s.endpoint_dim + (8 * g + i) * s.channels + r.chan[q] : channel_endpoint(s, r.chan[q], g);
   }
   const int c4 = 24 * r.nb1, e1 = c4 + 8 * r.nb4, e4 = e1 + 3 * r.nb1, used = e4 + r.nb4;
   if (slot < c4)
@@ -2096,10 +2155,11 @@ void apply_reg_plan(const Shape& s, const RegPlan& r, PackArgs* pa, InferArgs* a
   if (!a) return;
   if (r.any) {
     for (int q = 0; q < kRegSlots; ++q) a->reg_tex[q] = -1;
-    for (int t = 0; t < s.n_textures; ++t) a->reg_tex[s.ch_off[t]] = t;
     for (int q = 0; q < s.channels; ++q) {
-      a->reg_ep[q] = channel_endpoint(s, q, 0);
-      a->reg_ep1[q] = channel_endpoint(s, q, 1);
+      for (int t = 0; t < s.n_textures; ++t)
+        if (s.ch_off[t] == r.chan[q]) a->reg_tex[q] = t;
+      a->reg_ep[q] = channel_endpoint(s, r.chan[q], 0);
+      a->reg_ep1[q] = channel_endpoint(s, r.chan[q], 1);
     }
     return;
   }
@@ -2560,7 +2620,12 @@ extern "C" int ntbc_batch_plan(const ntbc_batch_item* items, int32_t n_items, in
                    "item %d: model_id %d shared by items with different weights, layer shapes or textures", i, it.model_id);
     }
     model_of[i] = m;
-    const RegPlan rp = reg_plan(p, true);
+  }
+  std::vector<char> any = batch_merge(plans, items);
+  for (int i = 0; i < n_items; ++i) {
+    const Plan& p = plans[i];
+    const Shape& s = p.s;
+    const RegPlan rp = reg_plan(p, true, any[i]);
     const BatchGroup want{precision, p.hid_inst, p.ksteps[0], rp.any ? s.n_layers - 2 : batch_nh(p),
                           rp.any ? kAnyMix : rp.nb1, rp.any ? 0 : rp.nb4,
                           0, 0, 0, 0, kLdsWaves, rp.any ? 1 : 0, {0, 0, 0}};
@@ -2570,6 +2635,13 @@ extern "C" int ntbc_batch_plan(const ntbc_batch_item* items, int32_t n_items, in
           groups[q].nb1 == want.nb1 && groups[q].nb4 == want.nb4 && groups[q].any == want.any)
         gi = (int)q;
     if (gi < 0) {
+      if ((int)groups.size() == kMaxBatchGroups && std::count(any.begin(), any.end(), 1) > 0) {
+        // (a mix of two depths can keep its instance for one of them and so take one more: group by mix alone)
+        any.assign(n_items, 0);
+        groups.clear();
+        i = -1;
+        continue;
+      }
       NTBC_REQUIRE((int)groups.size() < kMaxBatchGroups, "more than %d kernel instances in one batch", kMaxBatchGroups);
       gi = (int)groups.size();
       groups.push_back(want);
@@ -2626,14 +2698,15 @@ extern "C" int ntbc_batch_plan(const ntbc_batch_item* items, int32_t n_items, in
       const Plan& p = plans[i];
       BatchItem bi{};
       bi.a = infer_args(p, &items[i].desc, &items[i].params);
-      apply_reg_plan(p.s, reg_plan(p, true), nullptr, &bi.a);
+      const RegPlan rp = reg_plan(p, true, any[i]);
+      apply_reg_plan(p.s, rp, nullptr, &bi.a);
       bi.a.wpack = packs[model_of[i]].pack;
       bi.a.bias = packs[model_of[i]].bias;
       bi.a.first = items[i].first_block;
       bi.a.n = items[i].n_blocks;
       bi.a.out = items[i].blocks_out;
       bi.a.heads = nullptr;
-      const bool fp8 = precision == NTBC_FP8_E4M3, staged = reg_plan(p, true).nb1 < 0;
+      const bool fp8 = precision == NTBC_FP8_E4M3, staged = rp.nb1 < 0;
       size_t lds = 0;
       int st = make_chunks(p, fp8, bi.a.head_stride, staged, &bi.ct, &lds, gr.waves);
       if (st != NTBC_OK) return st;
