@@ -255,8 +255,9 @@ int ntbc_batch_set_waves(void* table, int32_t group, int32_t waves);
 
 /* Decodes every item of a plan: `table` is the host image, `table_device` the caller's device copy of
  * it.  stamps (optional, device uint64[n_items + 1]): [0] = the real-time counter (100 MHz) when the
- * batch starts, [1 + i] = when item i's last tile finished.  Stream-ordered and allocation-free, so a
- * caller may capture it in a HIP graph and replay it. */
+ * batch starts, [1 + i] = when item i's last tile finished (times, not flags: the blocks become visible to
+ * other work by stream order).  Stream-ordered and allocation-free, so a caller may capture it in a HIP graph and
+ * replay it. */
 int ntbc_infer_batch(const void* table, const void* table_device, void* workspace, size_t workspace_bytes,
                      uint64_t* stamps, void* stream);
 
